@@ -481,80 +481,100 @@ __global__ __launch_bounds__(64 * TPW) void k_render_fwd(int ntiles, int W, int 
 
 // Wave sums of ten values at once, by a transposing butterfly: at each
 // exchange a lane keeps half of its values and hands the other half to its
-// partner, so the number of values per lane halves as the partial sums
-// double (10 -> 5 -> 3 -> 2 -> 1 over lane bits 0..3, then bits 4 and 5 on
-// the single value).  Lane l < 16 ends with the total of value sum10_index(l)
-// (-1: no value); lanes 16..63 hold partial sums.  About 45 lane operations
-// instead of 70 for ten separate reductions, none through LDS.
-// z plus a second register after swapping z's odd 16-lane rows (R = 16) or
-// its upper 32 lanes (R = 32) with that register's even rows / lower lanes:
-// lane l of row 0 (and of row 2 for R = 16) gets z_l + z_{l+R}, whatever the
-// second register held (its values reach only rows 1 and 3, or lanes 32..63,
-// of the sum), so a value that is dead at this point serves and no register
-// is cleared for it.  Both registers are written by the swap, so it is
-// spelled out with both as in-out operands; the two wait states before it
-// cover a vector write of its operands just ahead of it.
-template <int R>
-__device__ __forceinline__ float row_swap_sum(float z, float spare) {
-  float o = spare;
-  if (R == 16)
-    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(z), "+v"(o));
-  else
-    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(z), "+v"(o));
-  return z + o;
+// partner, so the values per lane halve as the partial sums double.  The two
+// widest exchanges (10 -> 5 over lane bit 5, 5 -> 3 over bit 4) are the
+// vector unit's half and row swaps, which move a pair of registers without
+// any select: a swap of (p, q) leaves both partners of p in the one half (or
+// row parity) and both of q in the other, and one addition sums both.  Then
+// 3 -> 2 -> 1 over bits 0 and 1 by quad permutes and the one value left over
+// the row's four quads by two rotations: 25 vector instructions for the ten
+// sums (43 when the quad and row exchanges came first and the swaps last;
+// together with the output pass below, backward of the 48-view 640x480 batch
+// 1.36 -> 1.28 ms, of 32 views of 3M Gaussians at 1200x680 3.39 -> 3.21 ms).  Lane l ends with the total of value
+// sum10_index(l) (-1: none).
+//
+// The swaps write both registers and are spelled out with both as in-out
+// operands; the two wait states before a group cover a vector write of its
+// operands just ahead of it.
+__device__ __forceinline__ void half_swap5(float (&p)[5], float (&q)[5]) {
+  asm("s_nop 1\n\t"
+      "v_permlane32_swap_b32 %0, %5\n\t"
+      "v_permlane32_swap_b32 %1, %6\n\t"
+      "v_permlane32_swap_b32 %2, %7\n\t"
+      "v_permlane32_swap_b32 %3, %8\n\t"
+      "v_permlane32_swap_b32 %4, %9\n\t"
+      "s_nop 1"
+      : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]), "+v"(p[4]), "+v"(q[0]), "+v"(q[1]),
+        "+v"(q[2]), "+v"(q[3]), "+v"(q[4]));
+}
+__device__ __forceinline__ void row_swap3(float& p0, float& q0, float& p1, float& q1, float& p2,
+                                          float& q2) {
+  asm("s_nop 1\n\t"
+      "v_permlane16_swap_b32 %0, %1\n\t"
+      "v_permlane16_swap_b32 %2, %3\n\t"
+      "v_permlane16_swap_b32 %4, %5\n\t"
+      "s_nop 1"
+      : "+v"(p0), "+v"(q0), "+v"(p1), "+v"(q1), "+v"(p2), "+v"(q2));
 }
 
-// A DPP lane move; a lane whose source lane lies outside its row reads 0
-// (bound control set, so no zeroed register is needed for the old value).
+// A DPP lane move within a row of 16 lanes.
 template <int CTRL>
 __device__ __forceinline__ float dpp_mov(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL,
                                                             0xF, 0xF, true));
 }
 __host__ __device__ constexpr int sum10_index(int l) {
-  const int b0 = l & 1, b1 = (l >> 1) & 1, b2 = (l >> 2) & 1, b3 = (l >> 3) & 1;
-  const int xi = b3 + 2 * b2, m = xi + 3 * b1;
-  return (l < 16 && xi < 3 && m < 5) ? m + 5 * b0 : -1;
+  const int r = l >> 4, q = l & 15, m = 2 * (r & 1) + (r >> 1);
+  return q == 0 ? m : q == 1 ? 4 + m : (q == 2 && (r & 1) == 0) ? 8 + (r >> 1) : -1;
 }
 __device__ __forceinline__ float wave_sum10(const float (&v)[10], int lane) {
-  const bool b0 = lane & 1, b1 = (lane >> 1) & 1, b2 = (lane >> 2) & 1, b3 = (lane >> 3) & 1;
-  // lane bit 0 (quad_perm [1,0,3,2]): keep values 0..4 (b0 = 0) or 5..9
-  float w[6];
+  const bool b0 = lane & 1, b1 = (lane >> 1) & 1;
+  // lane bit 5: x[i] = value 2i in lanes 0..31, 2i + 1 in lanes 32..63
+  float x[5] = {v[0], v[2], v[4], v[6], v[8]}, o[5] = {v[1], v[3], v[5], v[7], v[9]};
+  half_swap5(x, o);
 #pragma unroll
-  for (int i = 0; i < 5; ++i) {
-    const float keep = b0 ? v[i + 5] : v[i], send = b0 ? v[i] : v[i + 5];
-    w[i] = keep + dpp_mov<0xB1>(send);
-  }
-  w[5] = 0.f;
-  // lane bit 1 (quad_perm [2,3,0,1]): keep w 0..2 or 3..5
-  float x[4];
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    const float keep = b1 ? w[i + 3] : w[i], send = b1 ? w[i] : w[i + 3];
-    x[i] = keep + dpp_mov<0x4E>(send);
-  }
-  x[3] = 0.f;
-  // lane bit 2 (row_shl:4 from lane l+4, row_shr:4 from lane l-4)
-  float y[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const float keep = b2 ? x[i + 2] : x[i], send = b2 ? x[i] : x[i + 2];
-    const float up = dpp_mov<0x104>(send), dn = dpp_mov<0x114>(send);
-    y[i] = keep + (b2 ? dn : up);
-  }
-  // lane bit 3 (row_ror:8)
-  float z = (b3 ? y[1] : y[0]) + dpp_mov<0x128>(b3 ? y[0] : y[1]);
-  // lane bits 4 and 5: the same value index in both partners, by the row
-  // swaps of the vector unit.  Swapping the odd 16-lane rows of z with the
-  // even rows of a zero register leaves z's even rows in z and z's odd rows,
-  // moved down one row, in the other register, so their sum holds the pair
-  // totals in rows 0 and 2; the 32-lane swap adds row 2 to row 0 the same
-  // way.
-  // y is dead once z is formed: its registers take the swaps' second
-  // operands (the first reaches rows 1 and 3 of the first sum and through
-  // them lanes 16..31 of the result, the second lanes 32..63; lanes 0..15,
-  // which hold the totals, depend on neither)
-  return row_swap_sum<32>(row_swap_sum<16>(z, y[1]), y[0]);
+  for (int i = 0; i < 5; ++i) x[i] += o[i];
+  // lane bit 4: x[0] | x[1] and x[2] | x[3] in even | odd rows; x[4] in the even
+  // rows (its partner is a dead register, whose values reach odd rows only)
+  row_swap3(x[0], x[1], x[2], x[3], x[4], o[0]);
+  const float y0 = x[0] + x[1], y1 = x[2] + x[3], y2 = x[4] + o[0];
+  // lane bit 0 (quad_perm [1,0,3,2]): y0 in even lanes, y1 in odd ones
+  const float z0 = (b0 ? y1 : y0) + dpp_mov<0xB1>(b0 ? y0 : y1);
+  const float z1 = y2 + dpp_mov<0xB1>(y2);
+  // lane bit 1 (quad_perm [2,3,0,1]): z0 in lanes 0 and 1 of a quad, z1 in 2, 3
+  float u = (b1 ? z1 : z0) + dpp_mov<0x4E>(b1 ? z0 : z1);
+  u += dpp_mov<0x124>(u);  // row_ror:4
+  u += dpp_mov<0x128>(u);  // row_ror:8
+  return u;
+}
+
+// An entry's ten sums over a region's pixels (t, at pitch RED) turned in place
+// into its screen-space gradients; (a, b) is its record, (x0, y0) the region's
+// first pixel centre.  With (DX, DY) the entry's offset from (x0, y0) and T0,
+// TU, TV, TUU, TUV, TVV the sums of gp, gp u, gp v, gp u^2, gp u v, gp v^2:
+// sum gp dx = DX T0 - TU, sum gp dx^2 = DX (DX T0 - 2 TU) + TUU, sum gp dx dy =
+// DX (DY T0 - TV) - DY TU + TUV, and likewise for dy; d(power)/du = -(A dx + B
+// dy) = ln2 (2A' dx + B' dy), etc.; dL/dsigma = T0 / sigma, by the hardware
+// reciprocal.  The colour and depth sums (6..9) are gradients already.
+constexpr int RED = GRAD2D + 1;  // pitch of an entry's sums: a wave's lanes hit distinct banks
+__device__ __forceinline__ void grads_in_place(float* t, const float4& a, const float4& b,
+                                               float x0, float y0) {
+  const float TU = t[0], TV = t[1], TUU = t[2], TUV = t[3], TVV = t[4], T0 = t[5];
+  const float DX = a.x - x0, DY = a.y - y0;
+  const float m0 = fmaf(DX, T0, -TU), m1 = fmaf(DY, T0, -TV);
+  t[0] = LN2 * (2.f * a.z * m0 + a.w * m1);
+  t[1] = LN2 * (a.w * m0 + 2.f * b.x * m1);
+  t[2] = -0.5f * fmaf(DX, fmaf(DX, T0, -2.f * TU), TUU);
+  t[3] = -fmaf(DX, m1, fmaf(-DY, TU, TUV));
+  t[4] = -0.5f * fmaf(DY, fmaf(DY, T0, -2.f * TV), TVV);
+  t[5] = T0 * rcp_fast(b.y);
+}
+
+// i / 10 for i < 16384 (24-bit product, full rate).
+__device__ __forceinline__ uint32_t div10(uint32_t i) { return __umul24(i, 6554u) >> 16; }
+__device__ __forceinline__ float* grad_at(float* grad2d, uint32_t row, uint32_t idx) {
+  return reinterpret_cast<float*>(reinterpret_cast<char*>(grad2d) +
+                                  ((unsigned long long)row * (GRAD2D * 4u) + 4u * idx));
 }
 
 // One tile, or CP adjacent tiles of a tile row, of the backward on one wave.
@@ -626,6 +646,7 @@ __device__ __forceinline__ void bwd_tile(int g, int W, int H, int TX, int TY,
     for (int d = 32; d >= 1; d >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, d, 64));
     blast[k] = (uint32_t)__builtin_amdgcn_readfirstlane((int)m);
   }
+  const int sidx = sum10_index(lane);  // the sum the lane ends with
   // the lane's pixel offset within an 8x8 block
   const float lxf = (float)(lane & 7), lyf = (float)(lane >> 3);
   // the region's first pixel centre
@@ -708,7 +729,7 @@ __device__ __forceinline__ void bwd_tile(int g, int W, int H, int TX, int TY,
       }
     }
     // the round's wave sums start at zero (entries that reach no pixel keep it)
-    for (uint32_t i = (uint32_t)lane; i < n * GRAD2D; i += 64u) red[i] = 0.f;
+    for (uint32_t i = (uint32_t)lane; i < n * RED; i += 64u) red[i] = 0.f;
     __builtin_amdgcn_wave_barrier();
     // Walk the staged entries (back-to-front order) that can reach a block
     // of the region (set bits of a ballot per staging round).
@@ -795,50 +816,26 @@ __device__ __forceinline__ void bwd_tile(int g, int W, int H, int TX, int TY,
         if (__ballot(act) != 0ull) {
           static_assert(GRAD2D == 10, "ten splat gradients");
           const float tot = wave_sum10(acc, lane);
-          const int idx = sum10_index(lane);
-          if (idx >= 0) red[GRAD2D * j + idx] = tot;
+          if (sidx >= 0) red[RED * j + sidx] = tot;
         }
       }
     }
     __builtin_amdgcn_wave_barrier();
-    // The round's wave sums to screen-space gradients, one (entry, value)
-    // per lane, and one atomic each (zero results, as for entries no pixel
-    // blended, are skipped).  With (DX, DY) the entry's offset from the
-    // region's first pixel centre and T0, TU, TV, TUU, TUV, TVV the sums of
-    // gp, gp u, gp v, gp u^2, gp u v, gp v^2: sum gp dx = DX T0 - TU, sum gp
-    // dx^2 = DX (DX T0 - 2 TU) + TUU, sum gp dx dy = DX (DY T0 - TV) - DY TU +
-    // TUV, and likewise for dy; d(power)/du = -(A dx + B dy) = ln2 (2A' dx +
-    // B' dy), etc.; dL/dsigma = T0 / sigma, by the hardware reciprocal.
-    for (uint32_t i0 = 0; i0 < n * GRAD2D; i0 += 64u) {
-      const uint32_t i = i0 + (uint32_t)lane;
-      if (i < n * GRAD2D) {
-        const uint32_t j = i / GRAD2D, idx = i - j * GRAD2D;
-        const float tot = red[i];
-        float out = tot;
-        if (idx <= 5u) {
-          const float4 a = s0[j];
-          const float T0 = red[GRAD2D * j + 5];
-          if (idx == 5u) {
-            out = tot * rcp_fast(s1[j].y);
-          } else {
-            const float TU = red[GRAD2D * j], TV = red[GRAD2D * j + 1];
-            const float DX = a.x - x0r, DY = a.y - y0r;
-            const float m0 = fmaf(DX, T0, -TU), m1 = fmaf(DY, T0, -TV);
-            if (idx == 0u) {
-              out = LN2 * (2.f * a.z * m0 + a.w * m1);
-            } else if (idx == 1u) {
-              out = LN2 * (a.w * m0 + 2.f * s1[j].x * m1);
-            } else if (idx == 2u) {
-              out = -0.5f * fmaf(DX, fmaf(DX, T0, -2.f * TU), tot);
-            } else if (idx == 3u) {
-              out = -fmaf(DX, m1, fmaf(-DY, TU, tot));
-            } else {
-              out = -0.5f * fmaf(DY, fmaf(DY, T0, -2.f * TV), tot);
-            }
-          }
-        }
-        if (out != 0.f) atomicAdd(grad2d + (size_t)GRAD2D * sp[j] + idx, out);
-      }
+    // The round's wave sums to screen-space gradients, an entry per lane, then
+    // out with one atomic per (entry, value), one of them per lane: the lanes
+    // of an atomic cover whole rows.  Zeros, as for entries no pixel blended,
+    // are skipped.  (One (entry, value) per lane for both cost a division, a
+    // choice among six formulas and 64-bit products per value.)
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const uint32_t j = (uint32_t)(lane + 64 * r);
+      if (j < n) grads_in_place(red + RED * j, s0[j], s1[j], x0r, y0r);
+    }
+    __builtin_amdgcn_wave_barrier();
+    for (uint32_t i = (uint32_t)lane; i < n * GRAD2D; i += 64u) {
+      const uint32_t j = div10(i), idx = i - GRAD2D * j;
+      const float out = red[RED * j + idx];
+      if (out != 0.f) atomicAdd(grad_at(grad2d, sp[j], idx), out);
     }
     head += n;
 #pragma unroll
@@ -867,7 +864,7 @@ __global__ __launch_bounds__(64 * TPW, CP == 2 ? 16 / TPW : 1) void k_render_bwd
   __shared__ uint32_t LP[TPW][B];
   __shared__ uint32_t LR[TPW][RingSize<B>::value];
   __shared__ uint32_t LX[TPW][CP > 1 ? RingSize<B>::value : 1];
-  __shared__ float LS[TPW][B * GRAD2D];
+  __shared__ float LS[TPW][B * RED];
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   if (!PERSIST) {
     const int blk = xcd_remap(blockIdx.x, (ntiles + TPW - 1) / TPW);
@@ -1040,6 +1037,7 @@ static void bwd_b(int nv, int W, int H, int TX, int TY, bool persist, int cols,
                   unsigned long long mask, const CamDev& cam, StateDev st, unsigned int* sched,
                   const float* gc, const float* gd, const float* ga, float* grad2d,
                   hipStream_t s) {
+  const int ntiles = nv * TX * TY;
   if constexpr (TW <= 16 && 2 * TW * TH <= 512) {
     if (cols == 2) {
       // two tiles of a tile row per wave (grid form only)
@@ -1050,7 +1048,6 @@ static void bwd_b(int nv, int W, int H, int TX, int TY, bool persist, int cols,
       return;
     }
   }
-  const int ntiles = nv * TX * TY;
   if (persist) {
     const auto k = k_render_bwd_w<TW, TH, B, BWD_TPW, true, 1>;
     const int need = (ntiles + BWD_TPW - 1) / BWD_TPW;
