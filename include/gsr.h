@@ -121,7 +121,11 @@ typedef struct gsr_plan_desc {
   int32_t bwd_cols;      /* tiles of a tile row per backward wave: 1 or 2
                             (0 = 1); 2 needs tile_w <= 16 and
                             2 tile_w tile_h <= 512, and its backward always
-                            runs one wave per pair of tiles (no queue) */
+                            runs one wave per pair of tiles (no queue).
+                            fwd_batch, bwd_batch and bwd_cols shape the
+                            one-wave kernels; a call with few tiles (and
+                            persistent = 0) takes a workgroup per tile
+                            whatever they say, with the same results */
 } gsr_plan_desc;
 
 /* Gaussians, concatenated over sets; set s owns [set_offsets[s], set_offsets[s+1]). */

@@ -22,6 +22,19 @@ __device__ __forceinline__ int xcd_remap(int b, int n) {
   return l < n ? l : -1;
 }
 
+// The same with the XCDs taking runs of XCD_RUN consecutive items in turn:
+// neighbours still share an L2, and uneven work along the range (a dense
+// part of an image, a large submap) is spread over every XCD.
+constexpr int XCD_RUN = 4;
+__host__ __device__ __forceinline__ int xcd_grid_mixed(int n) {
+  return 8 * XCD_RUN * ((n + 8 * XCD_RUN - 1) / (8 * XCD_RUN));
+}
+__device__ __forceinline__ int xcd_remap_mixed(int b, int n) {
+  const int k = b >> 3;
+  const int l = ((k / XCD_RUN) * 8 + (b & 7)) * XCD_RUN + k % XCD_RUN;
+  return l < n ? l : -1;
+}
+
 // Index s with off[s] <= b < off[s+1] for a non-decreasing off[0..n].
 __device__ __forceinline__ int find_seg(const int* off, int n, int b) {
   int lo = 0, hi = n;

@@ -9,6 +9,9 @@
 // (an LDS broadcast) for all of its pixels in the blocks the entry reaches.
 // The tile stops once every pixel has terminated.
 //
+// A call with few tiles takes a workgroup of one wave per 8x8 block per tile
+// instead, in both directions (k_render_fwd_coop, k_render_bwd_coop).
+//
 // Backward: one wave per (view, region), a region being one tile or two
 // adjacent tiles of a tile row, PPL = region pixels / 64 per lane, TPW
 // regions per workgroup with a private LDS slice each (no workgroup
@@ -445,7 +448,9 @@ __device__ __forceinline__ void fwd_tile(int g, int W, int H, int TX, int TY, co
 
 // TPW waves per workgroup, each with a private LDS slice and no workgroup
 // barrier.  Grid form: wave w of workgroup b takes tile b TPW + w (XCD-aware
-// order).  Persistent form: a grid sized to the resident waves, each wave
+// order, runs of four tiles per XCD: with a contiguous eighth of the tiles
+// each, the XCD with the densest part of the call finishes last; 48-view batch
+// 692 -> 683 us, nine uneven views at 517x389 168 -> 140 us).  Persistent form: a grid sized to the resident waves, each wave
 // taking tiles from the length-ordered queue (longest lists first) until it
 // is empty.
 template <int TW, int TH, int FB, int TPW, bool PERSIST, bool NEVAL>
@@ -459,7 +464,7 @@ __global__ __launch_bounds__(64 * TPW) void k_render_fwd(int ntiles, int W, int 
   __shared__ uint32_t LR[TPW][RingSize<B>::value];
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   if (!PERSIST) {
-    const int blk = xcd_remap(blockIdx.x, (ntiles + TPW - 1) / TPW);
+    const int blk = xcd_remap_mixed(blockIdx.x, (ntiles + TPW - 1) / TPW);
     if (blk < 0) return;
     const int g = blk * TPW + wv;
     if (g >= ntiles) return;
@@ -476,6 +481,174 @@ __global__ __launch_bounds__(64 * TPW) void k_render_fwd(int ntiles, int W, int 
                         L0[wv], L1[wv], L2[wv], LR[wv]);
     // the next tile's staging overwrites this wave's LDS slice
     __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// ---------------------------------------------- one workgroup per tile
+// The forms above give a tile (or more) to one wave: the least work per
+// entry, but a call with few tiles leaves most SIMDs idle and lasts as long
+// as its longest tile.  Here a workgroup of one wave per 8x8 block shares a
+// tile: its threads filter the row list and stage the records together, then
+// every wave walks the staged entries that reach its own block, and the
+// workgroup meets once per round.  (Independent waves per block each scan
+// and stage the whole list, and four times as many atomics meet on the rows
+// of large splats: backward 177 -> 433 us on one 1200x680 view of 300k
+// Gaussians.)
+template <int NB>
+struct CoopFill {
+  static constexpr int NT = 64 * NB;             // threads
+  static constexpr int STEP = 2 * NT;            // row entries per fill step
+  static constexpr int RING = NB <= 4 ? 1024 : 2048;  // >= B + STEP - 1
+};
+
+// Row entries per thread ahead of the fill: loaded one step early, so their
+// latency passes while the round before is walked.
+__device__ __forceinline__ uint2 row_at(const uint2* rows, uint32_t i, uint32_t lo, uint32_t hi) {
+  return i - lo < hi - lo ? rows[i] : make_uint2(0u, 0u);
+}
+
+// Appends the visible positions of one step's row entries that cover column
+// tx to the ring, in list order (entry k of thread t is number k NT + t of
+// the step).  wc: NB counts per half.  Contains __syncthreads().
+template <int NB>
+__device__ __forceinline__ void coop_append(const uint2 (&e)[2], uint32_t tx, uint32_t* ring,
+                                            uint32_t* wc, uint32_t& tail) {
+  constexpr uint32_t RM = CoopFill<NB>::RING - 1;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  unsigned long long m[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    m[k] = __ballot(covers(e[k].y, tx));
+    if (lane == 0) wc[k * NB + w] = (uint32_t)__popcll(m[k]);
+  }
+  __syncthreads();
+  uint32_t run = tail, at[2] = {0u, 0u};
+#pragma unroll
+  for (int i = 0; i < 2 * NB; ++i) {
+    if (i % NB == w) at[i / NB] = run;
+    run += wc[i];
+  }
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+    if (covers(e[k].y, tx))
+      ring[(at[k] + __builtin_amdgcn_mbcnt_hi((uint32_t)(m[k] >> 32),
+                                              __builtin_amdgcn_mbcnt_lo((uint32_t)m[k], 0u))) &
+           RM] = e[k].x;
+  tail = run;
+  __syncthreads();
+}
+
+template <int TW, int TH, bool NEVAL>
+__global__ __launch_bounds__(TW* TH) void k_render_fwd_coop(int ntiles, int W, int H, int TX,
+                                                           int TY, CamDev cam, StateDev st,
+                                                           float* color, float* depth,
+                                                           float* alpha, int32_t* n_eval) {
+  constexpr int NB = TW * TH / 64, BX = TW / 8, B = 64;
+  constexpr int NT = CoopFill<NB>::NT;
+  constexpr uint32_t RM = CoopFill<NB>::RING - 1;
+  __shared__ float4 s0[B], s1[B], s2[B];
+  __shared__ uint32_t sm[B];
+  __shared__ uint32_t ring[CoopFill<NB>::RING];
+  __shared__ uint32_t wc[2 * NB];
+  const int g = xcd_remap_mixed(blockIdx.x, ntiles);
+  if (g < 0) return;
+  const int T = TX * TY;
+  const int v = g / T, tl = g - v * T;
+  const int ty = tl / TX, tx = tl - ty * TX;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // the wave's block of the tile
+  uint2 rr = st.row_rg[(size_t)v * TY + ty];
+  if (st.hdr->overflow) rr = make_uint2(0u, 0u);
+  const int px = tx * TW + 8 * (w % BX) + (lane & 7);
+  const int py = ty * TH + 8 * (w / BX) + (lane >> 3);
+  const float fx = (float)px + 0.5f, fy = (float)py + 0.5f;
+  const float x0c = (float)(tx * TW) + 0.5f, y0c = (float)(ty * TH) + 0.5f;
+  const bool inside = px < W && py < H;
+  // the alpha threshold of a running pixel, or a value no alpha reaches (as in
+  // the one-wave form)
+  float thr = inside ? ALPHA_MIN : 2.f;
+  float Tc = 1.f, c0 = 0.f, c1 = 0.f, c2 = 0.f, dz = 0.f;
+  uint32_t last = 0u;
+  bool live = __ballot(inside) != 0ull;
+  uint32_t q = rr.x, head = 0u, tail = 0u, tbase = 0u;
+  uint2 e[2] = {row_at(st.rows, q + (uint32_t)tid, rr.x, rr.y),
+                row_at(st.rows, q + (uint32_t)(NT + tid), rr.x, rr.y)};
+  for (;;) {
+    while (tail - head < (uint32_t)B && q < rr.y) {
+      const uint2 c[2] = {e[0], e[1]};
+      q = rr.y - q > (uint32_t)(2 * NT) ? q + (uint32_t)(2 * NT) : rr.y;
+      e[0] = row_at(st.rows, q + (uint32_t)tid, rr.x, rr.y);
+      e[1] = row_at(st.rows, q + (uint32_t)(NT + tid), rr.x, rr.y);
+      coop_append<NB>(c, (uint32_t)tx, ring, wc, tail);
+    }
+    const uint32_t n = min((uint32_t)B, tail - head);
+    if (n == 0u) break;
+    if ((uint32_t)tid < n) {
+      const float4* rp = st.rec + 3 * (size_t)ring[(head + (uint32_t)tid) & RM];
+      const float4 r0 = rp[0], r1 = rp[1], r2 = rp[2];
+      uint32_t m = 0u;
+#pragma unroll
+      for (int by = 0; by < TH / 8; ++by) {
+        float xl, xr;
+        if (row_extent(r0, r1.x, r2.w, y0c + (float)(8 * by), y0c + (float)(8 * by + 7), xl, xr)) {
+#pragma unroll
+          for (int bx = 0; bx < BX; ++bx)
+            m |= (uint32_t)cols_reached(xl, xr, r1.w, x0c + (float)(8 * bx),
+                                        x0c + (float)(8 * bx + 7))
+                 << (by * BX + bx);
+        }
+      }
+      s0[tid] = r0;
+      s1[tid] = r1;
+      s2[tid] = r2;
+      sm[tid] = m;
+    }
+    __syncthreads();
+    if (live) {
+      unsigned long long rel =
+          __ballot((uint32_t)lane < n && ((sm[lane] >> w) & 1u) != 0u);
+      while (rel) {
+        if (__ballot(thr < 1.f) == 0ull) {
+          live = false;
+          break;
+        }
+        const int j = (int)__builtin_ctzll(rel);
+        rel &= rel - 1ull;
+        const uint32_t pos1 = tbase + (uint32_t)j + 1u;
+        const float stopv = NEVAL ? 2.f + (float)pos1 : 2.f;
+        const float4 a = s0[j], b = s1[j], c = s2[j];
+        const float p = splat_power(a, b, fx, fy);
+        const float al = fminf(ALPHA_MAX, b.y * exp2_fast(p));
+        const bool use = !(p > 0.f || al < thr);
+        const float Tn = fmaf(-al, Tc, Tc);
+        const bool stop = use && Tn < T_MIN;
+        const bool ok = use && !stop;
+        thr = stop ? stopv : thr;
+        const float wgt = ok ? al * Tc : 0.f;
+        c0 += c.x * wgt;
+        c1 += c.y * wgt;
+        c2 += c.z * wgt;
+        dz += b.z * wgt;
+        Tc = ok ? Tn : Tc;
+        last = ok ? pos1 : last;
+      }
+    }
+    head += n;
+    tbase += n;
+    // every wave has read the round's records; the tile ends with its last
+    // running block
+    if (!__syncthreads_or(live)) break;
+  }
+  if (inside) {
+    const size_t HW = (size_t)W * H, p = (size_t)py * W + px;
+    color[(3 * (size_t)v + 0) * HW + p] = c0 + Tc * cam.bg0;
+    color[(3 * (size_t)v + 1) * HW + p] = c1 + Tc * cam.bg1;
+    color[(3 * (size_t)v + 2) * HW + p] = c2 + Tc * cam.bg2;
+    depth[v * HW + p] = dz;
+    alpha[v * HW + p] = 1.f - Tc;
+    st.tfinal[v * HW + p] = Tc;
+    st.last[v * HW + p] = last;
+    if (NEVAL) n_eval[v * HW + p] = (int)(thr >= 2.f ? (uint32_t)(thr - 2.f) : tbase);
   }
 }
 
@@ -889,6 +1062,215 @@ __global__ __launch_bounds__(64 * TPW, CP == 2 ? 16 / TPW : 1) void k_render_bwd
   }
 }
 
+// Backward of one tile by a workgroup of one wave per 8x8 block, one pixel per
+// lane (the forward's workgroup form).  The waves' sums of a round meet in
+// LDS and leave as one atomic per (entry, value) and tile.
+template <int TW, int TH>
+__global__ __launch_bounds__(TW* TH) void k_render_bwd_coop(int ntiles, int W, int H, int TX,
+                                                           int TY, unsigned long long grad_mask,
+                                                           CamDev cam, StateDev st,
+                                                           const float* gcol, const float* gdep,
+                                                           const float* galp, float* grad2d) {
+  constexpr int NB = TW * TH / 64, BX = TW / 8, B = 64;
+  constexpr int NT = CoopFill<NB>::NT;
+  constexpr uint32_t RM = CoopFill<NB>::RING - 1;
+  __shared__ float4 s0[B], s1[B];
+  __shared__ float2 s2[B];
+  __shared__ uint32_t sp[B], sm[B];
+  __shared__ uint32_t ring[CoopFill<NB>::RING];
+  __shared__ uint32_t wc[2 * NB];
+  __shared__ uint32_t bl[NB];
+  __shared__ float red[NB][B * RED];
+  const int g = xcd_remap_mixed(blockIdx.x, ntiles);
+  if (g < 0) return;
+  const int T = TX * TY;
+  const int v = g / T, tl = g - v * T;
+  if (!((grad_mask >> v) & 1ull)) return;
+  if (st.hdr->overflow) return;
+  const int ty = tl / TX, tx = tl - ty * TX;
+  const uint2 rr = st.row_rg[(size_t)v * TY + ty];
+  if (rr.x == rr.y) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // the wave's block of the tile
+  const size_t HW = (size_t)W * H;
+  const int px = tx * TW + 8 * (w % BX) + (lane & 7);
+  const int py = ty * TH + 8 * (w / BX) + (lane >> 3);
+  const float fx = (float)px + 0.5f, fy = (float)py + 0.5f;
+  float Tc = 1.f, g0 = 0.f, g1 = 0.f, g2 = 0.f, gd = 0.f, ga = 0.f;
+  uint32_t last = 0u;
+  if (px < W && py < H) {
+    const size_t q = (size_t)py * W + px;
+    Tc = st.tfinal[v * HW + q];
+    last = st.last[v * HW + q];
+    if (gcol) {
+      g0 = gcol[(3 * (size_t)v + 0) * HW + q];
+      g1 = gcol[(3 * (size_t)v + 1) * HW + q];
+      g2 = gcol[(3 * (size_t)v + 2) * HW + q];
+    }
+    if (gdep) gd = gdep[v * HW + q];
+    if (galp) ga = galp[v * HW + q];
+  }
+  float Q = Tc * (cam.bg0 * g0 + cam.bg1 * g1 + cam.bg2 * g2) - Tc * ga;
+  {
+    uint32_t m = last;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, d, 64));
+    if (lane == 0) bl[w] = m;
+  }
+  __syncthreads();
+  // each block's largest last-contributor position, and the tile's
+  uint32_t nwalk = 0u;
+#pragma unroll
+  for (int k = 0; k < NB; ++k) nwalk = max(nwalk, bl[k]);
+  if (nwalk == 0u) return;
+  // the row position just after the nwalk-th entry covering the tile's column
+  uint32_t qb = rr.y;
+  {
+    uint32_t cnt = 0u;
+    for (uint32_t q = rr.x; q < rr.y;
+         q = rr.y - q > (uint32_t)(2 * NT) ? q + (uint32_t)(2 * NT) : rr.y) {
+      unsigned long long m[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        m[k] = __ballot(covers(row_at(st.rows, q + (uint32_t)(k * NT + tid), rr.x, rr.y).y,
+                               (uint32_t)tx));
+        if (lane == 0) wc[k * NB + w] = (uint32_t)__popcll(m[k]);
+      }
+      __syncthreads();
+      uint32_t run = cnt, at = ~0u;
+#pragma unroll
+      for (int i = 0; i < 2 * NB; ++i) {
+        // the 64 entries that hold the nwalk-th: wave i % NB finds its place
+        if (run < nwalk && nwalk <= run + wc[i] && i % NB == w) {
+          const unsigned long long mk = i < NB ? m[0] : m[1];
+          const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
+              (uint32_t)(mk >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk, 0u));
+          const unsigned long long hit =
+              __ballot(((mk >> lane) & 1ull) != 0ull && rank == nwalk - run - 1u);
+          at = q + (uint32_t)(i * 64) + (uint32_t)__builtin_ctzll(hit) + 1u;
+        }
+        run += wc[i];
+      }
+      cnt = run;
+      __syncthreads();
+      if (cnt >= nwalk) {
+        if (at != ~0u && lane == 0) wc[0] = at;
+        __syncthreads();
+        qb = wc[0];
+        __syncthreads();
+        break;
+      }
+    }
+  }
+  const float x0c = (float)(tx * TW) + 0.5f, y0c = (float)(ty * TH) + 0.5f;
+  // the lane's pixel offset within the tile, and the sum it ends with
+  const float lxf = (float)(8 * (w % BX) + (lane & 7)), lyf = (float)(8 * (w / BX) + (lane >> 3));
+  const int sidx = sum10_index(lane);
+  uint32_t head = 0u, tail = 0u, top = nwalk;
+  // back to front: entry k of thread t is number k NT + t of the step,
+  // counted down from qb (below rr.x the difference wraps: no entry)
+  uint2 e[2] = {row_at(st.rows, qb - 1u - (uint32_t)tid, rr.x, qb),
+                row_at(st.rows, qb - 1u - (uint32_t)(NT + tid), rr.x, qb)};
+  for (;;) {
+    while (tail - head < (uint32_t)B && qb > rr.x) {
+      const uint2 c[2] = {e[0], e[1]};
+      qb = qb - rr.x > (uint32_t)(2 * NT) ? qb - (uint32_t)(2 * NT) : rr.x;
+      e[0] = row_at(st.rows, qb - 1u - (uint32_t)tid, rr.x, qb);
+      e[1] = row_at(st.rows, qb - 1u - (uint32_t)(NT + tid), rr.x, qb);
+      coop_append<NB>(c, (uint32_t)tx, ring, wc, tail);
+    }
+    const uint32_t n = min((uint32_t)B, tail - head);
+    if (n == 0u) break;
+    if ((uint32_t)tid < n) {
+      const uint32_t pr = ring[(head + (uint32_t)tid) & RM];
+      const float4* rp = st.rec + 3 * (size_t)pr;
+      const float4 r0 = rp[0], r1 = rp[1], r2 = rp[2];
+      const uint32_t pos = top - 1u - (uint32_t)tid;
+      uint32_t m = 0u;
+#pragma unroll
+      for (int by = 0; by < TH / 8; ++by) {
+        float xl, xr;
+        if (row_extent(r0, r1.x, r2.w, y0c + (float)(8 * by), y0c + (float)(8 * by + 7), xl, xr)) {
+#pragma unroll
+          for (int bx = 0; bx < BX; ++bx)
+            m |= (uint32_t)(pos < bl[by * BX + bx] &&
+                            cols_reached(xl, xr, r1.w, x0c + (float)(8 * bx),
+                                         x0c + (float)(8 * bx + 7)))
+                 << (by * BX + bx);
+        }
+      }
+      s0[tid] = r0;
+      s1[tid] = make_float4(r1.x, r1.y, r1.z, r2.x);
+      s2[tid] = make_float2(r2.y, r2.z);
+      sp[tid] = pr;
+      sm[tid] = m;
+    }
+    for (uint32_t i = (uint32_t)lane; i < n * RED; i += 64u) red[w][i] = 0.f;
+    __syncthreads();
+    unsigned long long rel = __ballot((uint32_t)lane < n && ((sm[lane] >> w) & 1u) != 0u);
+    while (rel) {
+      const int j = (int)__builtin_ctzll(rel);
+      rel &= rel - 1ull;
+      const int pos = (int)(top - 1u) - j;
+      const float4 a = s0[j], b = s1[j];
+      const float2 c = s2[j];
+      const float power = splat_power(a, b, fx, fy);
+      const float G = exp2_fast(power);
+      const float raw = b.y * G;
+      const float al = fminf(ALPHA_MAX, raw);
+      const bool ok = pos < (int)last && !(power > 0.f || al < ALPHA_MIN);
+      if (__ballot(ok) == 0ull) continue;
+      // as in the one-wave form: an entry the pixel does not blend has zero
+      // alpha, whose transmittance factor is exactly 1
+      const float ab = ok ? al : 0.f;
+      const float inv = rcp_fast(1.f - ab);
+      const float Tb = Tc * inv;
+      const float wgt = ab * Tb;
+      const float cg = b.w * g0 + c.x * g1 + c.y * g2 + b.z * gd;
+      const float dA = Tb * cg - inv * Q;
+      Q += wgt * cg;
+      Tc = Tb;
+      const float gp = raw <= ALPHA_MAX ? ab * dA : 0.f;
+      float acc[GRAD2D];
+      acc[5] = gp;
+      acc[0] = lxf * gp;
+      acc[1] = lyf * gp;
+      acc[2] = lxf * acc[0];
+      acc[3] = lxf * acc[1];
+      acc[4] = lyf * acc[1];
+      acc[6] = wgt * g0;
+      acc[7] = wgt * g1;
+      acc[8] = wgt * g2;
+      acc[9] = wgt * gd;
+      const float tot = wave_sum10(acc, lane);
+      if (sidx >= 0) red[w][RED * j + sidx] = tot;
+    }
+    __syncthreads();
+    // the waves' sums added up and turned into screen-space gradients, an
+    // entry per lane, then out as in the one-wave form
+    if ((uint32_t)tid < n) {
+      float* t = red[0] + RED * tid;
+#pragma unroll
+      for (int k = 0; k < GRAD2D; ++k) {
+        float x = t[k];
+#pragma unroll
+        for (int u = 1; u < NB; ++u) x += red[u][RED * tid + k];
+        t[k] = x;
+      }
+      grads_in_place(t, s0[tid], s1[tid], x0c, y0c);
+    }
+    __syncthreads();
+    for (uint32_t i = (uint32_t)tid; i < n * GRAD2D; i += (uint32_t)NT) {
+      const uint32_t j = div10(i), idx = i - GRAD2D * j;
+      const float out = red[0][RED * j + idx];
+      if (out != 0.f) atomicAdd(grad_at(grad2d, sp[j], idx), out);
+    }
+    head += n;
+    top -= n;
+    __syncthreads();
+  }
+}
+
 // Clears the pose gradients (the per-pair screen-space gradient rows are
 // kept at zero between backward calls: the projection backward clears the
 // rows it consumes).
@@ -986,6 +1368,15 @@ static int resident_blocks(const void* kernel, int threads) {
 // its longest tile ended: 0.72 -> 0.70 ms forward, 1.46 -> 1.39 ms backward)
 constexpr int FWD_TPW = 1;
 
+// Largest call (tiles) whose tiles go to a workgroup each instead of a wave
+// each, where neither the plan asks for the persistent queue.  The workgroup
+// form spends more instructions per entry and far less time per tile.
+// Forward (16x16 tiles, one-wave form -> workgroup form): 48 tiles 94 -> 40 us,
+// 3,225 tiles (1200x680) 86 -> 64 us, 7,425 tiles 168 -> 134 us, 9,600 tiles
+// 167 -> 160 us, 57,600 tiles 684 -> 851 us.  Backward: 48 tiles 166 -> 70 us,
+// 105 tiles 270 -> 137 us, 3,225 tiles 163 -> 165 us, 7,425 tiles 309 -> 347 us.
+constexpr int FWD_COOP_TILES = 10000, BWD_COOP_TILES = 2500;
+
 template <int TW, int TH, int FB, bool NEVAL>
 static void fwd_fbn(int nv, int W, int H, int TX, int TY, bool persist, const CamDev& cam,
                     StateDev st, unsigned int* sched, float* color, float* depth, float* alpha,
@@ -998,7 +1389,7 @@ static void fwd_fbn(int nv, int W, int H, int TX, int TY, bool persist, const Ca
     hipLaunchKernelGGL(k, dim3(std::max(1, grid)), dim3(64 * FWD_TPW), 0, s, ntiles, W, H, TX, TY,
                        cam, st, sched, color, depth, alpha, n_eval);
   } else {
-    hipLaunchKernelGGL((k_render_fwd<TW, TH, FB, FWD_TPW, false, NEVAL>), dim3(xcd_grid(need)),
+    hipLaunchKernelGGL((k_render_fwd<TW, TH, FB, FWD_TPW, false, NEVAL>), dim3(xcd_grid_mixed(need)),
                        dim3(64 * FWD_TPW), 0, s, ntiles, W, H, TX, TY, cam, st, sched, color,
                        depth, alpha, n_eval);
   }
@@ -1021,6 +1412,13 @@ template <int TW, int TH>
 static hipError_t fwd_t(int nv, int W, int H, int TX, int TY, const RenderCfg& rc,
                         const CamDev& cam, StateDev st, unsigned int* sched, float* color,
                         float* depth, float* alpha, int32_t* n_eval, hipStream_t s) {
+  const int nt = nv * TX * TY;
+  if (!rc.persistent && nt <= FWD_COOP_TILES) {
+    const auto k = n_eval ? k_render_fwd_coop<TW, TH, true> : k_render_fwd_coop<TW, TH, false>;
+    hipLaunchKernelGGL(k, dim3(xcd_grid_mixed(nt)), dim3(TW * TH), 0, s, nt, W, H, TX, TY, cam, st,
+                       color, depth, alpha, n_eval);
+    return hipGetLastError();
+  }
   if (rc.fwd_batch == 2)
     fwd_fb<TW, TH, 2>(nv, W, H, TX, TY, rc.persistent, cam, st, sched, color, depth, alpha,
                       n_eval, s);
@@ -1066,6 +1464,12 @@ static hipError_t bwd_t(int nv, int W, int H, int TX, int TY, const RenderCfg& r
                         unsigned long long mask, const CamDev& cam, StateDev st,
                         unsigned int* sched, const float* gc, const float* gd, const float* ga,
                         float* grad2d, hipStream_t s) {
+  const int nt = nv * TX * TY;
+  if (!rc.persistent && nt <= BWD_COOP_TILES) {
+    hipLaunchKernelGGL((k_render_bwd_coop<TW, TH>), dim3(xcd_grid_mixed(nt)), dim3(TW * TH), 0, s,
+                       nt, W, H, TX, TY, mask, cam, st, gc, gd, ga, grad2d);
+    return hipGetLastError();
+  }
   if (rc.bwd_batch == 1)
     bwd_b<TW, TH, 64>(nv, W, H, TX, TY, rc.persistent, rc.bwd_cols, mask, cam, st, sched, gc, gd,
                       ga, grad2d, s);

@@ -1,0 +1,70 @@
+"""The compositing kernels' two forms against each other: a call with many
+tiles gives each tile (or pair of tiles) to a wave, one with few tiles gives
+each tile to a workgroup of one wave per 8x8 block.  The same views rendered
+in one large call and one call per view take the two forms; images, entry
+counts and saved last contributors must match bit for bit, gradients to the
+rounding of their sums (RERUN_TOL of the tensor's largest value: the sums
+run over float atomics in no fixed order in either form)."""
+import numpy as np
+import pytest
+
+from gpu_harness import RERUN_TOL, announce
+from synth.scenes import ROOM_HI, ROOM_LO, Scene, Views, draw_gaussians, look_at, pinhole
+
+pytestmark = pytest.mark.gpu
+
+PARAMS = ("d_means", "d_log_scales", "d_quats", "d_opacity_logits", "d_colors")
+
+
+def _case(n, n_views, W, H):
+    rng = np.random.default_rng(900 + n)
+    scene = Scene(*draw_gaussians(rng, n, ROOM_LO, ROOM_HI), set_offsets=np.array([0, n], np.int64))
+    vm = [look_at(rng.uniform(-1, 1, 3) * [1.5, 0.3, 1.0], rng.uniform(-1, 1, 3), 0.2)
+          for _ in range(n_views)]
+    return scene, Views(np.array(vm, np.float32),
+                        np.array([pinhole(W, H, W / 2.0)] * n_views, np.float32),
+                        np.zeros(n_views, np.int32), W, H)
+
+
+# (tile, tiles per backward wave, image size): 5 views of 2,450 16x16 tiles, 65 x
+# 33 = 2,145 32x16 tiles (an odd edge on both axes), 49 x 50 8x8 tiles; each
+# large call passes 10,000 tiles
+@pytest.mark.parametrize("tile,cols,W,H,n_views", [
+    ((16, 16), 1, 784, 800, 5), ((16, 16), 2, 777, 795, 5), ((32, 16), 1, 2077, 521, 5),
+    ((8, 8), 1, 391, 399, 5)])
+def test_wave_and_workgroup_forms(tile, cols, W, H, n_views):
+    import torch
+    from paper_2605_10760_amd import Rasterizer, SceneTensors, ViewTensors
+    announce(f"forms {tile} cols {cols} {W}x{H}")
+    scene, views = _case(4000, n_views, W, H)
+    tiles = -(-W // tile[0]) * -(-H // tile[1])
+    assert tiles <= 2500 and n_views * tiles > 10000
+    st, vt = SceneTensors.from_numpy(scene), ViewTensors.from_numpy(views)
+    rng = np.random.default_rng(5)
+    up = [torch.from_numpy((rng.choice([-1.0, 1.0], s) / s[-1]).astype(np.float32)).cuda()
+          for s in ((n_views, 3, H, W), (n_views, H, W), (n_views, H, W))]
+    big = Rasterizer(W, H, n_views * scene.n, n_views, tile=tile, bwd_cols=cols)
+    c, d, a, state, ne = big.forward(st, vt, bg=(0.2, 0.4, 0.6), n_eval=True)
+    g = big.backward(st, vt, state, *up, bg=(0.2, 0.4, 0.6))
+    dbg = big.debug_export(state, n_views, n_views * scene.n, 0)
+    c2, d2, a2, _ = big.forward(st, vt, bg=(0.2, 0.4, 0.6))
+    assert torch.equal(c, c2) and torch.equal(d, d2) and torch.equal(a, a2)
+    one = Rasterizer(W, H, scene.n, 1, tile=tile, bwd_cols=1)
+    total = {k: torch.zeros_like(g[k]) for k in PARAMS}
+    for k in range(n_views):
+        vk = vt.select([k])
+        ck, dk, ak, sk, nk = one.forward(st, vk, bg=(0.2, 0.4, 0.6), n_eval=True)
+        assert torch.equal(ck[0], c[k]) and torch.equal(dk[0], d[k]) and torch.equal(ak[0], a[k])
+        assert torch.equal(nk[0], ne[k])
+        ek = one.debug_export(sk, 1, scene.n, 0)
+        np.testing.assert_array_equal(ek["last"][0], dbg["last"][k])
+        np.testing.assert_array_equal(ek["t_final"][0], dbg["t_final"][k])
+        gk = one.backward(st, vk, sk, *[x[k:k + 1].contiguous() for x in up],
+                          bg=(0.2, 0.4, 0.6))
+        for q in PARAMS:
+            total[q] += gk[q]
+        pose = g["d_pose"][k]
+        assert float((gk["d_pose"][0] - pose).abs().max()) <= RERUN_TOL * float(pose.abs().max())
+    for q in PARAMS:
+        err = float((total[q] - g[q]).abs().max())
+        assert err <= RERUN_TOL * float(g[q].abs().max()), (q, err)
