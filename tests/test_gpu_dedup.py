@@ -150,3 +150,26 @@ def test_dedup_full_size_sampled():
                 if in_free:
                     break
         assert keep[i] == (not in_occ and not in_free), (int(i), in_occ, in_free)
+
+
+@pytest.mark.parametrize("far", [0.0, 900.0])
+def test_dedup_bitmap_and_hash_set(far):
+    """The set as a bitmap over the inputs' box, and, with one more target
+    Gaussian too far away for a bitmap to fit the workspace, as a hash set: the
+    same decisions and count as the oracle's sets."""
+    announce(f"dedup forms far={far}")
+    import torch
+    from paper_2605_10760_amd import dedup as gpu_dedup
+    tm, tls, sm, vms, intr, depth = _case(3)
+    v, k = 0.05, 1.0
+    occ, fr = occupied(tm, tls, v, k), free(depth, vms, intr, v)[0]
+    more = 0
+    if far:
+        tm = np.concatenate([tm, np.full((1, 3), far, np.float32)])
+        tls = np.concatenate([tls, np.full((1, 3), -2.0, np.float32)])
+        more = len(occupied(tm[-1:], tls[-1:], v, k))
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    keep, nvox = gpu_dedup(t(sm), t(tm), t(tls), t(depth), t(vms), t(intr), v, k)
+    ref = np.array([tuple(q) not in occ and tuple(q) not in fr for q in voxel_of(sm, v)])
+    np.testing.assert_array_equal(keep.cpu().numpy().astype(bool), ref)
+    assert nvox == len(occ | fr) + more
