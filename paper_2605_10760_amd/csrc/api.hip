@@ -811,8 +811,7 @@ gsr_status gsr_dedup(const gsr_dedup_params* p, const float* tgt_means,
                               tgt_log_scales, n_tgt, depth, viewmats, intrinsics, n_keyframes,
                               width, height, src_means, n_src, keep, st, &dc);
   unsigned int h[2] = {0u, 0u};
-  if (e == hipSuccess) e = hipMemcpyAsync(h, dc, sizeof(h), hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  if (e == hipSuccess) e = hipMemcpyWithStream(h, dc, sizeof(h), hipMemcpyDeviceToHost, st);
   if (e != hipSuccess) return GSR_E_DEVICE;
   if (n_voxels) *n_voxels = (int64_t)h[1];
   if (h[0] & 2u) return GSR_E_INVALID_ARG;  // inputs outside the voxel key range
@@ -850,20 +849,20 @@ gsr_status gsr_prune(const gsr_scene* sc, float min_opacity, float* means_out,
   SceneDev in = scene_dev(sc);
   hipStream_t st = (hipStream_t)stream;
   const size_t nb = (size_t)((n + 255) / 256);
-  void* tmp = nullptr;
-  if (hipMalloc(&tmp, 4 * (nb + 1) + 8 * (GSR_MAX_SETS + 1) + 256) != hipSuccess) {
+  CallScratch tmp;
+  if (tmp.get(4 * (nb + 1) + 8 * (GSR_MAX_SETS + 1) + 256) != hipSuccess) {
     (void)hipGetLastError();
     return GSR_E_OOM;
   }
-  uint32_t* blk = (uint32_t*)tmp;
-  long long* bounds = (long long*)((char*)tmp + ((4 * (nb + 1) + 255) / 256) * 256);
+  uint32_t* blk = (uint32_t*)tmp.ptr;
+  long long* bounds = (long long*)((char*)tmp.ptr + ((4 * (nb + 1) + 255) / 256) * 256);
   hipError_t e = launch_prune(n, in, cstride, thr, tab, blk, bounds, means_out, log_scales_out,
                               quats_out, opacity_out, colors_out, st);
+  // the scratch goes back with the stream at rest, whatever failed
   if (e == hipSuccess)
-    e = hipMemcpyAsync(set_offsets_out, bounds, 8 * (size_t)(sc->n_sets + 1),
-                       hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  (void)hipFree(tmp);
+    e = hipMemcpyWithStream(set_offsets_out, bounds, 8 * (size_t)(sc->n_sets + 1),
+                            hipMemcpyDeviceToHost, st);
+  if (e != hipSuccess) (void)hipStreamSynchronize(st);
   return e == hipSuccess ? GSR_OK : GSR_E_DEVICE;
 }
 
@@ -906,20 +905,20 @@ gsr_status gsr_seed(const float* depth, const float* color, const float* viewmat
   const long gm = (long)((width + stride - 1) / stride) * ((height + stride - 1) / stride);
   if ((double)width * height * 3 > 2147483647.0 || gm > 0x7FFFFFFFL) return GSR_E_INVALID_ARG;
   const size_t nb = (size_t)((gm + 255) / 256);
-  void* tmp = nullptr;
-  if (hipMalloc(&tmp, 4 * (nb + 1)) != hipSuccess) {
+  CallScratch tmp;
+  if (tmp.get(4 * (nb + 1)) != hipSuccess) {
     (void)hipGetLastError();
     return GSR_E_OOM;
   }
   hipStream_t st = (hipStream_t)stream;
-  uint32_t* blk = (uint32_t*)tmp;
+  uint32_t* blk = (uint32_t*)tmp.ptr;
   uint32_t total = 0;
   hipError_t e = launch_seed(width, height, stride, depth, color, viewmat, intrinsics,
-                             opacity_logit, (long)max_out, blk, means_out, log_scales_out,
-                             quats_out, opacity_out, colors_out, st);
-  if (e == hipSuccess) e = hipMemcpyAsync(&total, blk + nb, 4, hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  (void)hipFree(tmp);
+                             opacity_logit, (long)max_out, blk, nullptr, means_out,
+                             log_scales_out, quats_out, opacity_out, colors_out, st);
+  // the scratch goes back with the stream at rest, whatever failed
+  if (e == hipSuccess) e = hipMemcpyWithStream(&total, blk + nb, 4, hipMemcpyDeviceToHost, st);
+  if (e != hipSuccess) (void)hipStreamSynchronize(st);
   if (e != hipSuccess) return GSR_E_DEVICE;
   *n_out = (int64_t)total;
   return (int64_t)total > max_out ? GSR_E_OVERFLOW : GSR_OK;
@@ -956,7 +955,6 @@ gsr_status gsr_seed_noalloc(const float* depth, const float* color, const float*
   if ((double)width * height * 3 > 2147483647.0) return GSR_E_INVALID_ARG;
   const long gm = (long)((width + stride - 1) / stride) * ((height + stride - 1) / stride);
   if (gm > SEED_NOALLOC_MAX_POINTS) return GSR_E_CAPACITY;
-  const int nb = (int)((gm + 255) / 256);
   uint32_t* blk = nullptr;
   hipError_t e = seed_scratch(&blk);
   if (e != hipSuccess) {
@@ -965,9 +963,8 @@ gsr_status gsr_seed_noalloc(const float* depth, const float* color, const float*
   }
   hipStream_t st = (hipStream_t)stream;
   e = launch_seed(width, height, stride, depth, color, viewmat, intrinsics, opacity_logit,
-                  (long)max_out, blk, means_out, log_scales_out, quats_out, opacity_out,
+                  (long)max_out, blk, n_out_dev, means_out, log_scales_out, quats_out, opacity_out,
                   colors_out, st);
-  if (e == hipSuccess) e = launch_seed_total(blk, nb, n_out_dev, st);
   return e == hipSuccess ? GSR_OK : GSR_E_DEVICE;
 }
 

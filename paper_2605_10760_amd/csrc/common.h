@@ -113,6 +113,23 @@ __device__ __forceinline__ unsigned long long wg_excl_scan(unsigned long long x,
   return r;
 }
 
+// Sum of cnt[0 .. blockIdx.x) (16-byte aligned) over a workgroup of 256
+// threads, in every thread (sh: four words of LDS).  Contains __syncthreads().
+__device__ __forceinline__ uint32_t block_prefix_256(const uint32_t* cnt, uint32_t* sh) {
+  uint32_t s = 0u;
+  const int n = (int)blockIdx.x, n4 = n & ~3;
+  for (int i = 4 * (int)threadIdx.x; i < n4; i += 1024) {
+    const uint4 q = *reinterpret_cast<const uint4*>(cnt + i);
+    s += q.x + q.y + q.z + q.w;
+  }
+  if ((int)threadIdx.x < n - n4) s += cnt[n4 + (int)threadIdx.x];
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) s += (uint32_t)__shfl_xor((int)s, d, 64);
+  if (lane_id() == 0) sh[threadIdx.x >> 6] = s;
+  __syncthreads();
+  return sh[0] + sh[1] + sh[2] + sh[3];
+}
+
 // FP64 3D covariance Sigma = M M^T, M = R diag(s), of a Gaussian from its
 // FP32 log-scales and (unnormalised) quaternion (w, x, y, z).  The scales,
 // the normalised quaternion and the rotation are formed in FP32 (a ~1e-7

@@ -211,11 +211,20 @@ hipError_t launch_normal_grad(int nv, int W, int H, const float* depth, const fl
                               const float* intr, float w, float* g_dep, hipStream_t s);
 hipError_t launch_seed(int W, int H, int stride, const float* depth, const float* color,
                        const float* vm, const float* intr, float opac_logit, long max_out,
-                       uint32_t* blk, float* m, float* ls, float* q, float* o, float* c,
-                       hipStream_t s);
+                       uint32_t* blk, int64_t* n_out, float* m, float* ls, float* q, float* o,
+                       float* c, hipStream_t s);
 hipError_t launch_adam(const gsr_adam_group* gr, int ng, double b1, double b2, double eps,
                        int32_t* step, hipStream_t s);
 hipError_t seed_scratch(uint32_t** out);
-hipError_t launch_seed_total(const uint32_t* blk, int nb, int64_t* n_out, hipStream_t s);
+
+// Device scratch of one host call that synchronises before it returns.
+constexpr int CALL_SLOTS = 4;
+constexpr size_t CALL_SLOT_BYTES = 256 * 1024;
+struct CallScratch {
+  void* ptr = nullptr;
+  int dev = -1, slot = -1;
+  hipError_t get(size_t bytes);
+  ~CallScratch();
+};
 
 }  // namespace gsr

@@ -128,8 +128,9 @@ __global__ __launch_bounds__(256) void k_prune_count(long n, const float* opac, 
   if (threadIdx.x == 0) blk[blockIdx.x] = (uint32_t)c;
 }
 
-// One workgroup: exclusive scan of the block counts, in place; total at blk[nb].
-__global__ __launch_bounds__(1024) void k_prune_scan(int nb, uint32_t* blk) {
+// One workgroup: exclusive scan of the block counts, in place; total at
+// blk[nb].
+__device__ __forceinline__ void scan_blocks_1024(int nb, uint32_t* blk) {
   __shared__ unsigned long long sh[17];
   unsigned long long carry = 0;
   for (int base = 0; base < nb; base += 1024) {
@@ -143,21 +144,30 @@ __global__ __launch_bounds__(1024) void k_prune_scan(int nb, uint32_t* blk) {
   if (threadIdx.x == 0) blk[nb] = (uint32_t)carry;
 }
 
+__global__ __launch_bounds__(1024) void k_block_scan(int nb, uint32_t* blk) {
+  scan_blocks_1024(nb, blk);
+}
+
 hipError_t launch_block_scan(int nb, uint32_t* blk, hipStream_t s) {
-  hipLaunchKernelGGL(k_prune_scan, dim3(1), dim3(1024), 0, s, nb, blk);
+  hipLaunchKernelGGL(k_block_scan, dim3(1), dim3(1024), 0, s, nb, blk);
   return hipGetLastError();
 }
 
-// Kept count before each set boundary (one thread per boundary).
-__global__ void k_prune_bounds(SimSetTab tab, const float* opac, float thr, const uint32_t* blk,
-                               long long* out) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k > tab.ns) return;
-  const long e = tab.off[k];
-  const long b = e / 256;
-  uint32_t c = blk[b];
-  for (long i = b * 256; i < e; ++i) c += opac[i] >= thr ? 1u : 0u;
-  out[k] = c;
+// The scan, then the kept count before each set boundary (a wave per
+// boundary: the boundary's block up to it).
+__global__ __launch_bounds__(1024) void k_prune_scan(int nb, uint32_t* blk, SimSetTab tab,
+                                                     const float* opac, float thr,
+                                                     long long* out) {
+  scan_blocks_1024(nb, blk);
+  __syncthreads();  // the workgroup's own writes to blk
+  for (int k = threadIdx.x >> 6; k <= tab.ns; k += 16) {
+    const long e = tab.off[k], b = e / 256;
+    uint32_t c = 0u;
+    for (long i = b * 256 + lane_id(); i < e; i += 64) c += opac[i] >= thr ? 1u : 0u;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) c += (uint32_t)__shfl_xor((int)c, d, 64);
+    if (lane_id() == 0) out[k] = (long long)blk[b] + c;
+  }
 }
 
 __global__ __launch_bounds__(256) void k_prune_gather(long n, float thr, const uint32_t* blk,
@@ -190,9 +200,7 @@ hipError_t launch_prune(long n, const SceneDev& in, int color_stride, float thr,
   const int nb = (int)((n + 255) / 256);
   if (nb > 0)
     hipLaunchKernelGGL(k_prune_count, dim3(nb), dim3(256), 0, s, n, in.opac, thr, blk);
-  hipLaunchKernelGGL(k_prune_scan, dim3(1), dim3(1024), 0, s, nb, blk);
-  hipLaunchKernelGGL(k_prune_bounds, dim3(1), dim3(MAXS + 1), 0, s, sets, in.opac, thr, blk,
-                     bounds);
+  hipLaunchKernelGGL(k_prune_scan, dim3(1), dim3(1024), 0, s, nb, blk, sets, in.opac, thr, bounds);
   if (nb > 0)
     hipLaunchKernelGGL(k_prune_gather, dim3(nb), dim3(256), 0, s, n, thr, blk, in, color_stride,
                        m, ls, q, o, col);

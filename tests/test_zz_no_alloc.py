@@ -80,3 +80,35 @@ def test_seed_noalloc_capacity_and_args():
     st = lib.gsr_seed_noalloc(d.data_ptr(), col.data_ptr(), vm.data_ptr(), intr.data_ptr(), W, H,
                               1, 0.0, 4, *p, None, None)
     assert st == _lib.GSR_E_INVALID_ARG
+
+
+@pytest.mark.parametrize("shape", [(1023, 1025, 1), (1025, 1025, 1), (33, 63, 2)])
+def test_seed_counts_around_the_scan_size(shape):
+    """Up to 4096 blocks of 256 grid points each block sums the counts before
+    it, beyond them a scan kernel runs: the same rows in grid order on both
+    sides of the line, with a hole every seventh point, from both entry
+    points."""
+    import torch
+    from paper_2605_10760_amd import seed, seed_noalloc
+    H, W, stride = shape
+    announce(f"seed scan size {H}x{W} stride {stride}")
+    js, is_ = np.arange(0, H, stride), np.arange(0, W, stride)
+    depth = np.full((H, W), 2.0, np.float32)
+    grid = np.arange(js.size * is_.size).reshape(js.size, is_.size)
+    sub = depth[::stride, ::stride]
+    sub[grid % 7 == 3] = 0.0
+    col = np.zeros((3, H, W), np.float32)
+    col[0] = np.arange(H)[:, None]
+    col[1] = np.arange(W)[None]
+    vm = np.concatenate([np.eye(3), np.zeros((3, 1))], 1).astype(np.float32)
+    intr = np.array([100.0, 100.0, W / 2.0, H / 2.0], np.float32)
+    want = np.argwhere(depth[::stride, ::stride] > 0) * stride
+    got = seed(_t(depth), _t(col), _t(vm), _t(intr), stride=stride)
+    np.testing.assert_array_equal(got["colors"][:, :2].cpu().numpy(), want.astype(np.float32))
+    rows = _rows(grid.size)
+    n_dev = torch.full((1,), -1, dtype=torch.int64, device="cuda")
+    seed_noalloc(_t(depth), _t(col), _t(vm), _t(intr), rows, n_dev, stride=stride)
+    torch.cuda.synchronize()
+    assert int(n_dev.item()) == want.shape[0]
+    for key in rows:
+        assert torch.equal(rows[key][:want.shape[0]], got[key]), key
