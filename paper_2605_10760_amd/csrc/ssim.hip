@@ -2,28 +2,55 @@
 // exposure-compensated render I~ = exp(a_v) I^ + b_v, and its gradient.
 //
 // Statistics under an 11 x 11 Gaussian window (sigma 1.5, zero outside the
-// image), per colour channel, in one pass over 32 x 32 pixel tiles (k_ssim):
-// the five moments of (x, y) -> S and the gradient maps f1 = dS/dmx -
-// 2 mx dS/dsxx - my dS/dsxy, f2 = dS/dsxx, f3 = dS/dsxy on the tile plus a
-// 5-pixel halo, then blurs of f1..f3 -> d mean(S)/dx = (w*f1 + 2 x w*f2 +
-// y w*f3) / N at the tile's pixels, chained through the exposure into
-// d_color (accumulated); the maps never leave LDS.  k_ssim_reduce: per-block
-// partial sums (S, and the exposure gradients) summed per view in a fixed
-// order: no float atomics on a few hot addresses.
+// image), per colour channel: the moments of (x, y) -> S and the gradient maps
+// f1 = dS/dmx - 2 mx dS/dsxx - my dS/dsxy, f2 = dS/dsxx, f3 = dS/dsxy, then
+// blurs of f1..f3 -> d mean(S)/dx = (w*f1 + 2 x w*f2 + y w*f3) / N, chained
+// through the exposure into d_color (accumulated).  S and its derivatives need
+// sxx and syy only as their sum, so four moments are blurred: x, y, x^2 + y^2
+// and xy.
+//
+// k_ssim: a workgroup of one to four waves takes a strip of output columns (40,
+// 104, 168 or 232: its columns less two windows, in fours) and marches down
+// the image four rows at a time, a column per lane.  A separable blur is a product with a
+// band matrix, and it runs on the matrix unit in 4 x 4 blocks (4x4x1, FP32
+// throughout, a fused multiply-add per element): four output rows of 64
+// columns take the 14 input rows of their windows, one instruction per row
+// with the weights as the left operand (vertical), or four columns of 16
+// column groups take 14 columns each, one instruction per column with the
+// weights as the right operand (horizontal).  The narrow blocks keep the band
+// dense (11 of 14; 11 of 26 in a 16 x 16 block), and both products leave a
+// column per lane and a row per register, so only the horizontal blurs'
+// left operands pass through LDS (four 16-byte reads per map and four rows).
+// The rows of x and y, and of f1..f3, that the next windows need stay in
+// registers (rings of 16 rows, the march unrolled by four steps).
+// One workgroup per 32 x 32 tile with blurs through LDS took 1050 us at 48 x 3
+// x 480 x 640 (bound by LDS reads: about 118 per pixel, and 310 multiply-adds
+// with the tile's halo); this form
+// 463 us (one wave per strip, 40 of its 64 columns its own: 585 us; loads at
+// their use instead of a step ahead and one chain of products at a time: 692).
+//
+// k_ssim_reduce: per-wave partial sums (S, and the exposure gradients) summed
+// per view in a fixed order: no float atomics on a few hot addresses.
+#include <algorithm>
+
 #include "common.h"
 
 namespace gsr {
 
-constexpr int SS_T = 32, SS_R = 5;   // tile, window radius
+constexpr int SS_R = 5;                // window radius
 constexpr int SS_K = 2 * SS_R + 1;     // taps
-constexpr int SS_P = 4;                // outputs per thread and blur
-constexpr int SS_L = SS_P + 2 * SS_R;  // the values they read
-static_assert(SS_T * SS_T == 256 * SS_P, "the tile's blur: SS_P outputs per thread");
+constexpr int SS_W = SS_K + 3;         // inputs of four neighbouring outputs
+constexpr int SS_MAXW = 4;             // waves per workgroup at most
+// statistics and output columns of a workgroup of nw waves
+constexpr int ss_stats(int nw) { return 4 * ((64 * nw - SS_W) / 4 + 1); }
+constexpr int ss_out(int nw) { return 4 * ((ss_stats(nw) - SS_W) / 4 + 1); }
+constexpr int SS_T = 32;               // tile edge the workspace is sized for
 constexpr float SS_C1 = 0.01f * 0.01f, SS_C2 = 0.03f * 0.03f;
 
 struct SsimArgs {
-  float w[2 * SS_R + 1];
-  int W, H, TX, nv;
+  float w[SS_K];
+  int W, H, TX, nv;     // TX: strips
+  int rows;             // output rows of a workgroup (a multiple of 4)
   float weight_over_n;  // weight / (3 V H W)
 };
 
@@ -36,216 +63,213 @@ __device__ __forceinline__ float block_sum_256(float x, float* red) {
   return t;
 }
 
-// One workgroup per 32 x 32 tile of one channel of one view, in LDS only:
-//  A  x~ = exp(a) I^ + b and the target, on the tile plus a 10-pixel halo
-//     (zero outside the image), SS_X x SS_X staged;
-//  B/C the five window moments on the SS_S x SS_S statistics region (the tile
-//     plus a 5-pixel halo, two spare rows and columns): horizontal blurs into
-//     LDS, then vertical blurs into registers, in two groups (x, y, xy; then
-//     xx, yy) so that one buffer of three maps serves both;
-//  D  S and the gradient maps f1..f3 of the region (zero outside the image)
-//     into the staging buffer, S summed over the tile;
-//  E/F the blurred maps at the tile's pixels, chained through the exposure
-//     into d_color.
-// Each thread blurs SS_P consecutive outputs of a row or column from SS_L
-// values held in registers.
-constexpr int SS_S = 44, SS_X = SS_S + 2 * SS_R;  // statistics region, staged edge
-constexpr int SS_SG = SS_S / SS_P;                // row groups of the region
-static_assert(SS_S >= SS_T + 2 * SS_R && SS_S % SS_P == 0, "statistics region");
+typedef float ss_v4 __attribute__((ext_vector_type(4)));
+// LDS row pitch: the workgroup's columns and the last groups' overhang; 16 mod
+// 64 words, so the four rows a read touches hit distinct banks
+constexpr int ss_ld(int nw) { return 64 * nw + 16; }
 
-// Horizontal blur of rows [0, nrow) of NM maps (or of the products of (x, y)
-// when PROD > 0: PROD = 1 blurs x, y, xy; PROD = 2 blurs xx, yy) into NO maps
-// of nout columns (a multiple of SS_P).
-template <int NM, int NO, int PROD, int SW, int DW, int NROW>
-__device__ __forceinline__ void ss_hblur(const SsimArgs& A, const float (*src)[NROW][SW],
-                                         float (*dst)[NROW][DW], int nout) {
-  const int runs = nout / SS_P;
-  for (int it = threadIdx.x; it < NROW * runs; it += 256) {
-    const int r = it / runs, c0 = (it - r * runs) * SS_P;
-    float acc[NO][SS_P];
+// Vertical blurs of four rows of NM maps: in(k, t) is row t of the 14 of map k
+// (a column per lane); d[k][i] is its output row i.  The maps' chains of
+// dependent products are interleaved.
+template <int NM, class F>
+__device__ __forceinline__ void ss_vert(const float (&wt)[SS_W], const F& in, ss_v4 (&d)[NM]) {
 #pragma unroll
-    for (int k = 0; k < NO; ++k)
+  for (int k = 0; k < NM; ++k) d[k] = ss_v4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int o = 0; o < SS_P; ++o) acc[k][o] = 0.f;
+  for (int t = 0; t < SS_W; ++t)
 #pragma unroll
-    for (int t = 0; t < SS_L; ++t) {
-      float q[NO];
-      if constexpr (PROD == 1) {
-        const float x = src[0][r][c0 + t], y = src[1][r][c0 + t];
-        q[0] = x; q[1] = y; q[2 % NO] = x * y;
-      } else if constexpr (PROD == 2) {
-        const float x = src[0][r][c0 + t], y = src[1][r][c0 + t];
-        q[0] = x * x; q[1 % NO] = y * y;
-      } else {
-#pragma unroll
-        for (int k = 0; k < NO; ++k) q[k] = src[k % NM][r][c0 + t];
-      }
-#pragma unroll
-      for (int o = 0; o < SS_P; ++o) {
-        const int d = t - o;
-        if (d >= 0 && d < SS_K) {
-#pragma unroll
-          for (int k = 0; k < NO; ++k) acc[k][o] += A.w[d] * q[k];
-        }
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < NO; ++k)
-#pragma unroll
-      for (int o = 0; o < SS_P; ++o) dst[k][r][c0 + o] = acc[k][o];
-  }
+    for (int k = 0; k < NM; ++k)
+      d[k] = __builtin_amdgcn_mfma_f32_4x4x1f32(wt[t], in(k, t), d[k], 0, 0, 0);
 }
 
-// Vertical blur of one map at column j, output rows i0 .. i0 + SS_P - 1
-// (input rows i0 .. i0 + SS_L - 1).
-template <int DW, int NROW>
-__device__ __forceinline__ void ss_vblur(const SsimArgs& A, const float (*m)[DW], int i0, int j,
-                                         float (&out)[SS_P]) {
-  float val[SS_L];
+// Horizontal blurs of the four rows of NM maps, handed over through buf (row i
+// of map k at [k][i]): output column o (thread o) is the window over columns o
+// .. o + 10.  One barrier: a step's two calls use two buffers, so a buffer is
+// written again only after a barrier behind its last read.
+template <int NM, int NW>
+__device__ __forceinline__ void ss_horiz(const float (&wt)[SS_W], float (*buf)[4][ss_ld(NW)],
+                                         ss_v4 (&d)[NM]) {
+  const int lane = threadIdx.x;
 #pragma unroll
-  for (int t = 0; t < SS_L; ++t) val[t] = m[i0 + t][j];
+  for (int k = 0; k < NM; ++k)
 #pragma unroll
-  for (int o = 0; o < SS_P; ++o) {
-    float a = 0.f;
+    for (int i = 0; i < 4; ++i) buf[k][i][lane] = d[k][i];
+  if (NW > 1)
+    __syncthreads();
+  else
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int d = 0; d < SS_K; ++d) a += A.w[d] * val[o + d];
-    out[o] = a;
+  for (int k = 0; k < NM; ++k) d[k] = ss_v4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    float4 x[NM];
+#pragma unroll
+    for (int k = 0; k < NM; ++k)
+      x[k] = *reinterpret_cast<const float4*>(&buf[k][lane & 3][(lane & ~3) + 4 * c]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (4 * c + e < SS_W) {
+#pragma unroll
+        for (int k = 0; k < NM; ++k)
+          d[k] = __builtin_amdgcn_mfma_f32_4x4x1f32(
+              e == 0 ? x[k].x : e == 1 ? x[k].y : e == 2 ? x[k].z : x[k].w, wt[4 * c + e], d[k], 0,
+              0, 0);
+      }
   }
+  if (NW == 1) __builtin_amdgcn_wave_barrier();
 }
 
-struct SsimSmem {
-  union {
-    float sxy[2][SS_X][SS_X + 1];  // A-B: x~ and the target
-    float f[3][SS_S][SS_S + 1];    // D-E: f1, f2, f3 on the statistics region
-  } u0;
-  union {
-    float hm[3][SS_X][SS_S + 1];   // B-C: horizontal moment blurs
-    float hf[3][SS_S][SS_T + 1];   // E-F: horizontal blurs of f1..f3
-  } u1;
-  float red[4];
-};
-
-constexpr int SS_ITEMS = SS_S * SS_SG;                     // vertical statistics items
-constexpr int SS_IPT = (SS_ITEMS + 255) / 256;              // per thread
-
-__global__ __launch_bounds__(256) void k_ssim(SsimArgs A, const float* color, const float* target,
-                                              const float* expo, float* d_color,
-                                              float* ssim_part, float* e_part) {
-  __shared__ SsimSmem sm;
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_ssim(SsimArgs A, const float* color, const float* target,
+                                             const float* expo, float* d_color, float* ssim_part,
+                                             float* e_part) {
+  constexpr int OW = ss_out(NW), SW = ss_stats(NW);
+  __shared__ __align__(16) float buf[4][4][ss_ld(NW)], buf2[3][4][ss_ld(NW)];
+  __shared__ float red[3][NW];
+  const int lane = threadIdx.x;  // the thread's column
   const int vc = blockIdx.y, v = vc / 3;
-  const int ty = blockIdx.x / A.TX, tx = blockIdx.x - ty * A.TX;
-  // pixel of staged (0, 0) and of statistics-region (0, 0)
-  const int XS = tx * SS_T - 2 * SS_R, YS = ty * SS_T - 2 * SS_R;
-  const int XR = tx * SS_T - SS_R, YR = ty * SS_T - SS_R;
+  const int sy = blockIdx.x / A.TX, sx = blockIdx.x - sy * A.TX;
+  const int y0 = sy * A.rows, y1 = min(y0 + A.rows, A.H);  // the workgroup's output rows
+  const int xi = sx * OW - 2 * SS_R + lane;                // the lane's input column,
+  const int xs = xi + SS_R, xo = xs + SS_R;                // statistics and output column
   const float ea = expo ? expf(expo[2 * v]) : 1.f, eb = expo ? expo[2 * v + 1] : 0.f;
   const size_t plane = (size_t)A.W * A.H;
   const float* ci = color + (size_t)vc * plane;
   const float* ti = target + (size_t)vc * plane;
-  for (int i = threadIdx.x; i < SS_X * SS_X; i += 256) {
-    const int r = i / SS_X, c = i - r * SS_X;
-    const int gx = XS + c, gy = YS + r;
-    const bool in = gx >= 0 && gx < A.W && gy >= 0 && gy < A.H;
-    const size_t q = (size_t)gy * A.W + gx;
-    sm.u0.sxy[0][r][c] = in ? ea * ci[q] + eb : 0.f;
-    sm.u0.sxy[1][r][c] = in ? ti[q] : 0.f;
-  }
-  __syncthreads();
-  // moments of the statistics items: item = (column c, row group g)
-  float mom[SS_IPT][5][SS_P];
-  ss_hblur<2, 3, 1, SS_X + 1, SS_S + 1, SS_X>(A, sm.u0.sxy, sm.u1.hm, SS_S);
-  __syncthreads();
+  float* di = d_color + (size_t)vc * plane;
+  // the weight of input t in output lane mod 4: both operands' tables
+  float wt[SS_W];
 #pragma unroll
-  for (int u = 0; u < SS_IPT; ++u) {
-    const int it = (int)threadIdx.x + 256 * u;
-    if (it < SS_ITEMS) {
-      const int c = it % SS_S, g = it / SS_S;
-      ss_vblur<SS_S + 1, SS_X>(A, sm.u1.hm[0], g * SS_P, c, mom[u][0]);  // x
-      ss_vblur<SS_S + 1, SS_X>(A, sm.u1.hm[1], g * SS_P, c, mom[u][1]);  // y
-      ss_vblur<SS_S + 1, SS_X>(A, sm.u1.hm[2], g * SS_P, c, mom[u][4]);  // xy
+  for (int t = 0; t < SS_W; ++t) {
+    wt[t] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (t - i >= 0 && t - i < SS_K) wt[t] = (lane & 3) == i ? A.w[t - i] : wt[t];
+  }
+  const bool xi_in = xi >= 0 && xi < A.W, xs_in = xs >= 0 && xs < A.W && lane < SW;
+  const bool own_col = lane >= SS_R && lane < SS_R + OW && xs < A.W;  // counted in S
+  const bool xo_in = lane < OW && xo < A.W;
+  const int xc = min(max(xi, 0), A.W - 1), oxc = min(max(xo, 0), A.W - 1);
+  float rx[4][4], ry[4][4];  // input rows y0 - 10 + 4 g + i at [g mod 4][i]
+  float f[3][4][4];          // gradient maps of statistics rows y0 - 5 + 4 s + i at [.][s mod 4][i]
+  // raw rows of input group g, and their values (loaded a step ahead of use)
+  const auto fetch = [&](int g, float (&x)[4], float (&y)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = min(max(y0 - 2 * SS_R + 4 * g + i, 0), A.H - 1);
+      x[i] = (ci + (size_t)r * A.W)[xc];
+      y[i] = (ti + (size_t)r * A.W)[xc];
     }
-  }
-  __syncthreads();
-  ss_hblur<2, 2, 2, SS_X + 1, SS_S + 1, SS_X>(A, sm.u0.sxy, sm.u1.hm, SS_S);
-  __syncthreads();
+  };
+  const auto place = [&](int g, const float (&a)[4], const float (&b)[4], float (&x)[4],
+                         float (&y)[4]) {
 #pragma unroll
-  for (int u = 0; u < SS_IPT; ++u) {
-    const int it = (int)threadIdx.x + 256 * u;
-    if (it < SS_ITEMS) {
-      const int c = it % SS_S, g = it / SS_S;
-      ss_vblur<SS_S + 1, SS_X>(A, sm.u1.hm[0], g * SS_P, c, mom[u][2]);  // xx
-      ss_vblur<SS_S + 1, SS_X>(A, sm.u1.hm[1], g * SS_P, c, mom[u][3]);  // yy
+    for (int i = 0; i < 4; ++i) {
+      const int r = y0 - 2 * SS_R + 4 * g + i;
+      const bool in = r >= 0 && r < A.H && xi_in;
+      x[i] = in ? ea * a[i] + eb : 0.f;
+      y[i] = in ? b[i] : 0.f;
     }
+  };
+  float nx[4], ny[4];
+#pragma unroll
+  for (int g = 0; g < 3; ++g) {
+    fetch(g, nx, ny);
+    place(g, nx, ny, rx[g], ry[g]);
   }
-  __syncthreads();  // the staging buffer becomes the f maps
-  float s = 0.f;
+  fetch(3, nx, ny);
+  float s = 0.f, sa = 0.f, sb = 0.f;
+  const int steps = (y1 - y0 + 3) / 4 + 3;
+  for (int s0 = 0; s0 < steps; s0 += 4) {
 #pragma unroll
-  for (int u = 0; u < SS_IPT; ++u) {
-    const int it = (int)threadIdx.x + 256 * u;
-    if (it < SS_ITEMS) {
-      const int c = it % SS_S, g = it / SS_S;
-      const int gx = XR + c;
+    for (int u = 0; u < 4; ++u) {
+      const int st = s0 + u;
+      if (st >= steps) break;  // uniform
+      place(st + 3, nx, ny, rx[(u + 3) & 3], ry[(u + 3) & 3]);
+      fetch(st + 4, nx, ny);
+      // the output rows' own pixels, for the end of the step
+      float oc[4], oy[4], od[4];
 #pragma unroll
-      for (int o = 0; o < SS_P; ++o) {
-        const int r = g * SS_P + o, gy = YR + r;
-        float f1 = 0.f, f2 = 0.f, f3 = 0.f;
-        if (gx >= 0 && gx < A.W && gy >= 0 && gy < A.H) {
-          const float mx = mom[u][0][o], my = mom[u][1][o];
-          const float sxx = mom[u][2][o] - mx * mx, syy = mom[u][3][o] - my * my;
-          const float sxy = mom[u][4][o] - mx * my;
-          const float a1 = 2.f * mx * my + SS_C1, a2 = 2.f * sxy + SS_C2;
-          const float b1 = mx * mx + my * my + SS_C1, b2 = sxx + syy + SS_C2;
-          // b1, b2 >= C1, C2 > 0: reciprocals by the hardware (about 1 ulp)
-          const float rb1 = __builtin_amdgcn_rcpf(b1), rb2 = __builtin_amdgcn_rcpf(b2);
-          const float ib = rb1 * rb2;
-          const float so = a1 * a2 * ib;
-          const float d_mx = 2.f * my * a2 * ib - 2.f * mx * so * rb1;
-          const float d_sxx = -so * rb2;
-          const float d_sxy = 2.f * a1 * ib;
-          f1 = d_mx - 2.f * mx * d_sxx - my * d_sxy;
-          f2 = d_sxx;
-          f3 = d_sxy;
-          // the tile's own pixels carry S
-          if (r >= SS_R && r < SS_R + SS_T && c >= SS_R && c < SS_R + SS_T) s += so;
-        }
-        sm.u0.f[0][r][c] = f1;
-        sm.u0.f[1][r][c] = f2;
-        sm.u0.f[2][r][c] = f3;
+      for (int i = 0; i < 4; ++i) {
+        const size_t q = (size_t)min(max(y0 + 4 * (st - 3) + i, 0), A.H - 1) * A.W;
+        oc[i] = (ci + q)[oxc];
+        oy[i] = (ti + q)[oxc];
+        od[i] = (di + q)[oxc];
+      }
+      // moments of the statistics rows y0 - 5 + 4 st + i
+      ss_v4 m[4];
+      ss_vert<4>(
+          wt,
+          [&](int k, int t) {
+            const float x = rx[(u + (t >> 2)) & 3][t & 3], y = ry[(u + (t >> 2)) & 3][t & 3];
+            return k == 0 ? x : k == 1 ? y : k == 2 ? x * x + y * y : x * y;
+          },
+          m);
+      ss_horiz<4, NW>(wt, buf, m);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = y0 - SS_R + 4 * st + i;
+        const float mx = m[0][i], my = m[1][i];
+        const float mm = mx * mx + my * my;
+        const float a1 = 2.f * mx * my + SS_C1, a2 = 2.f * (m[3][i] - mx * my) + SS_C2;
+        const float b1 = mm + SS_C1, b2 = (m[2][i] - mm) + SS_C2;
+        // b1, b2 >= C1, C2 > 0: reciprocals by the hardware (about 1 ulp)
+        const float rb1 = __builtin_amdgcn_rcpf(b1), rb2 = __builtin_amdgcn_rcpf(b2);
+        const float ib = rb1 * rb2;
+        const float so = a1 * a2 * ib;
+        const float d_mx = 2.f * my * a2 * ib - 2.f * mx * so * rb1;
+        const float d_sxx = -so * rb2;
+        const float d_sxy = 2.f * a1 * ib;
+        const bool in = r >= 0 && r < A.H && xs_in;
+        f[0][u][i] = in ? d_mx - 2.f * mx * d_sxx - my * d_sxy : 0.f;
+        f[1][u][i] = in ? d_sxx : 0.f;
+        f[2][u][i] = in ? d_sxy : 0.f;
+        // the workgroup's own pixels carry S
+        if (r >= y0 && r < y1) s += own_col ? so : 0.f;
+      }
+      if (st < 3) {  // uniform: the first output rows need four groups
+        if (NW > 1) __syncthreads();
+        continue;
+      }
+      // blurred maps at the output rows y0 + 4 (st - 3) + i
+      ss_v4 bl[3];
+      ss_vert<3>(wt, [&](int k, int t) { return f[k][(u + 1 + (t >> 2)) & 3][t & 3]; }, bl);
+      ss_horiz<3, NW>(wt, buf2, bl);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = y0 + 4 * (st - 3) + i;
+        const float x = ea * oc[i] + eb;
+        // loss = weight (1 - mean S): dL/dx~ = -weight/N (w*f1 + 2 x w*f2 + y w*f3)
+        float g = -A.weight_over_n * (bl[0][i] + 2.f * x * bl[1][i] + oy[i] * bl[2][i]);
+        g = r < y1 && xo_in ? g : 0.f;
+        if (r < y1 && xo_in) (di + (size_t)r * A.W)[oxc] = od[i] + ea * g;
+        sa += g * oc[i];
+        sb += g;
       }
     }
   }
-  __syncthreads();
-  ss_hblur<3, 3, 0, SS_S + 1, SS_T + 1, SS_S>(A, sm.u0.f, sm.u1.hf, SS_T);
-  __syncthreads();
-  // thread: column j, rows i0 .. i0 + SS_P - 1 of the tile
-  const int j = threadIdx.x % SS_T, i0 = (threadIdx.x / SS_T) * SS_P;
-  float bl[3][SS_P];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) ss_vblur<SS_T + 1, SS_S>(A, sm.u1.hf[k], i0, j, bl[k]);
-  const int gx = tx * SS_T + j;
-  float sa = 0.f, sb = 0.f;
-#pragma unroll
-  for (int o = 0; o < SS_P; ++o) {
-    const int gy = ty * SS_T + i0 + o;
-    if (gx < A.W && gy < A.H) {
-      const size_t q = (size_t)gy * A.W + gx;
-      const float c = ci[q];
-      const float x = ea * c + eb, y = ti[q];
-      // loss = weight (1 - mean S): dL/dx~ = -weight/N (w*f1 + 2 x w*f2 + y w*f3)
-      const float g = -A.weight_over_n * (bl[0][o] + 2.f * x * bl[1][o] + y * bl[2][o]);
-      d_color[(size_t)vc * plane + q] += ea * g;
-      sa += g * c;
-      sb += g;
-    }
-  }
   const size_t bb = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
-  const float t = block_sum_256(s, sm.red);
-  if (threadIdx.x == 0) ssim_part[bb] = t;
-  if (!e_part) return;  // uniform
-  const float ta = block_sum_256(sa, sm.red);
-  const float tb = block_sum_256(sb, sm.red);
-  if (threadIdx.x == 0) {
-    e_part[2 * bb] = ea * ta;
-    e_part[2 * bb + 1] = tb;
+  s = wave_total(s);
+  sa = wave_total(sa);
+  sb = wave_total(sb);
+  const int w = lane >> 6;
+  if (lane_id() == 0) {
+    red[0][w] = s;
+    red[1][w] = sa;
+    red[2][w] = sb;
+  }
+  __syncthreads();
+  if (lane == 0) {
+    for (int k = 1; k < NW; ++k) {
+      s += red[0][k];
+      sa += red[1][k];
+      sb += red[2][k];
+    }
+    ssim_part[bb] = s;
+    if (e_part) {
+      e_part[2 * bb] = ea * sa;
+      e_part[2 * bb + 1] = sb;
+    }
   }
 }
 
@@ -299,24 +323,37 @@ hipError_t launch_ssim(int nv, int W, int H, float weight, const float* color,
                        const float* target, const float* expo, void* ws, float* d_color,
                        float* d_expo, float* ssim_out, hipStream_t s) {
   SsimArgs A{};
-  double g[2 * SS_R + 1], tot = 0.0;
+  double g[SS_K], tot = 0.0;
   for (int d = -SS_R; d <= SS_R; ++d) tot += g[d + SS_R] = exp(-(double)(d * d) / (2.0 * 1.5 * 1.5));
   for (int d = 0; d <= 2 * SS_R; ++d) A.w[d] = (float)(g[d] / tot);
   A.W = W;
   A.H = H;
-  A.TX = (W + SS_T - 1) / SS_T;
+  // waves per workgroup: the fewest waves over the strips of a row (each strip
+  // recomputes two windows of columns), the larger workgroup on a tie (640
+  // columns: 3 x 4 waves 463 us, 4 x 3 572, 7 x 2 534, 16 x 1 585)
+  int nw = 1;
+  const auto strips_of = [&](int k) { return (W + ss_out(k) - 1) / ss_out(k); };
+  for (int k = 2; k <= SS_MAXW; ++k)
+    if (k * strips_of(k) <= nw * strips_of(nw)) nw = k;
+  A.TX = strips_of(nw);
   A.nv = nv;
+  // rows per workgroup: it recomputes the statistics of 12 rows, so long marches
+  // are cheaper, but about 8192 waves fill the chip (8 per SIMD); never below
+  // SS_T rows (the partials then fit the workspace)
+  const int waves = 3 * nv * A.TX * nw, most = (H + SS_T - 1) / SS_T;
+  const int segs = std::min(most, std::max(1, (8192 + waves - 1) / waves));
+  A.rows = std::max(SS_T, ((H + segs - 1) / segs + 3) / 4 * 4);
   const double n = 3.0 * nv * (double)W * H;
   A.weight_over_n = (float)(weight / n);
-  const int TY = (H + SS_T - 1) / SS_T;
-  const int nb_view = A.TX * TY;
+  const int nb_view = A.TX * ((H + A.rows - 1) / A.rows);
   const size_t nb = (size_t)nb_view * 3 * nv;
   char* w8 = (char*)ws;
   float* s_part = (float*)w8;
   float* e_part = (float*)(w8 + align_up(nb * 4));
   float* s_view = (float*)(w8 + align_up(nb * 4) + align_up(nb * 8));
   const dim3 grid(nb_view, 3 * nv);
-  hipLaunchKernelGGL(k_ssim, grid, dim3(256), 0, s, A, color, target, expo, d_color, s_part,
+  const auto k = nw == 1 ? k_ssim<1> : nw == 2 ? k_ssim<2> : nw == 3 ? k_ssim<3> : k_ssim<4>;
+  hipLaunchKernelGGL(k, grid, dim3(64 * nw), 0, s, A, color, target, expo, d_color, s_part,
                      d_expo ? e_part : (float*)nullptr);
   if (d_expo || ssim_out)
     hipLaunchKernelGGL(k_ssim_reduce, dim3(nv), dim3(256), 0, s, nb_view, s_part,

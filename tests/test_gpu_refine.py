@@ -144,3 +144,36 @@ def test_ssim_grad_full_size_sampled():
                                    atol=1e-4 * abs(ref["d_a"][0] / V))
         np.testing.assert_allclose(ge[v, 1], ref["d_b"][0] / V, rtol=1e-3,
                                    atol=1e-4 * abs(ref["d_b"][0] / V))
+
+
+# image widths at the edges of the strips of one to four waves (40, 104, 168 and
+# 232 output columns), heights at the edges of the row segments (32 rows and
+# multiples of four) and below a window
+@pytest.mark.parametrize("H,W", [(33, 40), (32, 41), (67, 104), (5, 105), (36, 168), (41, 169),
+                                 (64, 232), (35, 233), (1, 1)])
+def test_ssim_grad_strip_edges(H, W):
+    announce(f"ssim strips {H}x{W}")
+    import torch
+    from oracle.ssim import ssim, ssim_term_grad
+    from paper_2605_10760_amd import ssim_grad
+    V = 2
+    rng = np.random.default_rng(H * 1000 + W)
+    c = rng.random((V, 3, H, W)).astype(np.float32)
+    tgt = np.clip(c + 0.1 * rng.standard_normal(c.shape), 0, 1).astype(np.float32)
+    ex = np.array([[0.05, 0.01], [-0.08, 0.02]], np.float32)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    d_color = torch.full((V, 3, H, W), 0.5, device="cuda")
+    d_exp = torch.zeros((V, 2), device="cuda")
+    out = torch.zeros(1, device="cuda")
+    weight = 0.2 * c.size  # gradients of order one next to the 0.5 they add to
+    ssim_grad(t(c), t(tgt), d_color, t(ex), d_exp, weight, ssim_out=out)
+    ref = ssim_term_grad(c, tgt, ex[:, 0], ex[:, 1], weight)
+    xt = np.exp(ex[:, 0])[:, None, None, None] * c.astype(np.float64) + ex[:, 1][:, None, None, None]
+    # the variances cancel to about 6e-8 of the squares, against C2 = 9e-4
+    assert abs(out.item() - ssim(xt, tgt)) <= 2e-5
+    got = d_color.cpu().numpy().astype(np.float64) - 0.5
+    assert np.abs(got - ref["d_color"]).max() <= 1e-3 * np.abs(ref["d_color"]).max()
+    ge = d_exp.cpu().numpy()
+    for k, key in ((0, "d_a"), (1, "d_b")):
+        scale = np.abs(ref["d_color"]).sum(axis=(1, 2, 3)).max()
+        assert np.abs(ge[:, k] - ref[key]).max() <= 1e-3 * scale, key
