@@ -71,8 +71,15 @@ constexpr int ss_ld(int nw) { return 64 * nw + 16; }
 // Vertical blurs of four rows of NM maps: in(k, t) is row t of the 14 of map k
 // (a column per lane); d[k][i] is its output row i.  The maps' chains of
 // dependent products are interleaved.
+//
+// The band product also multiplies the rows outside an output's window, by
+// zero: an infinite or NaN input there would reach outputs it must not.  Each
+// output row sums all 14 inputs, so row 0 shows whether there is one; the
+// wave then sums its windows alone, by vector instructions.  Returns whether
+// it did (uniform over the wave): the horizontal blur of these rows must too.
 template <int NM, class F>
-__device__ __forceinline__ void ss_vert(const float (&wt)[SS_W], const F& in, ss_v4 (&d)[NM]) {
+__device__ __forceinline__ bool ss_vert(const SsimArgs& A, const float (&wt)[SS_W], const F& in,
+                                        ss_v4 (&d)[NM]) {
 #pragma unroll
   for (int k = 0; k < NM; ++k) d[k] = ss_v4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -80,41 +87,73 @@ __device__ __forceinline__ void ss_vert(const float (&wt)[SS_W], const F& in, ss
 #pragma unroll
     for (int k = 0; k < NM; ++k)
       d[k] = __builtin_amdgcn_mfma_f32_4x4x1f32(wt[t], in(k, t), d[k], 0, 0, 0);
+  float all = d[0][0];
+#pragma unroll
+  for (int k = 1; k < NM; ++k) all += d[k][0];
+  if (__ballot(!(fabsf(all) < INFINITY)) == 0ull) return false;
+#pragma unroll
+  for (int k = 0; k < NM; ++k)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float a = 0.f;
+#pragma unroll
+      for (int t = 0; t < SS_K; ++t) a = fmaf(A.w[t], in(k, i + t), a);
+      d[k][i] = a;
+    }
+  return true;
 }
 
 // Horizontal blurs of the four rows of NM maps, handed over through buf (row i
 // of map k at [k][i]): output column o (thread o) is the window over columns o
 // .. o + 10.  One barrier: a step's two calls use two buffers, so a buffer is
-// written again only after a barrier behind its last read.
+// written again only after a barrier behind its last read.  alone: this wave's
+// rows hold infinite or NaN values; the workgroup agrees through *flag, which
+// holds the last step (counted from 1) where a wave's did.
 template <int NM, int NW>
-__device__ __forceinline__ void ss_horiz(const float (&wt)[SS_W], float (*buf)[4][ss_ld(NW)],
-                                         ss_v4 (&d)[NM]) {
+__device__ __forceinline__ void ss_horiz(const SsimArgs& A, const float (&wt)[SS_W],
+                                         float (*buf)[4][ss_ld(NW)], bool alone, int step,
+                                         int* flag, ss_v4 (&d)[NM]) {
   const int lane = threadIdx.x;
 #pragma unroll
   for (int k = 0; k < NM; ++k)
 #pragma unroll
     for (int i = 0; i < 4; ++i) buf[k][i][lane] = d[k][i];
-  if (NW > 1)
+  if (NW > 1) {
+    if (alone && lane_id() == 0) *flag = step;
     __syncthreads();
-  else
+    alone = __builtin_amdgcn_readfirstlane(*flag) == step;
+  } else {
     __builtin_amdgcn_wave_barrier();
-#pragma unroll
-  for (int k = 0; k < NM; ++k) d[k] = ss_v4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    float4 x[NM];
+  }
+  if (alone) {
 #pragma unroll
     for (int k = 0; k < NM; ++k)
-      x[k] = *reinterpret_cast<const float4*>(&buf[k][lane & 3][(lane & ~3) + 4 * c]);
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (4 * c + e < SS_W) {
+      for (int i = 0; i < 4; ++i) {
+        float a = 0.f;
 #pragma unroll
-        for (int k = 0; k < NM; ++k)
-          d[k] = __builtin_amdgcn_mfma_f32_4x4x1f32(
-              e == 0 ? x[k].x : e == 1 ? x[k].y : e == 2 ? x[k].z : x[k].w, wt[4 * c + e], d[k], 0,
-              0, 0);
+        for (int t = 0; t < SS_K; ++t) a = fmaf(A.w[t], buf[k][i][lane + t], a);
+        d[k][i] = a;
       }
+  } else {
+#pragma unroll
+    for (int k = 0; k < NM; ++k) d[k] = ss_v4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      float4 x[NM];
+#pragma unroll
+      for (int k = 0; k < NM; ++k)
+        x[k] = *reinterpret_cast<const float4*>(&buf[k][lane & 3][(lane & ~3) + 4 * c]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (4 * c + e < SS_W) {
+#pragma unroll
+          for (int k = 0; k < NM; ++k)
+            d[k] = __builtin_amdgcn_mfma_f32_4x4x1f32(
+                e == 0 ? x[k].x : e == 1 ? x[k].y : e == 2 ? x[k].z : x[k].w, wt[4 * c + e], d[k],
+                0, 0, 0);
+        }
+    }
   }
   if (NW == 1) __builtin_amdgcn_wave_barrier();
 }
@@ -126,6 +165,7 @@ __global__ __launch_bounds__(64 * NW) void k_ssim(SsimArgs A, const float* color
   constexpr int OW = ss_out(NW), SW = ss_stats(NW);
   __shared__ __align__(16) float buf[4][4][ss_ld(NW)], buf2[3][4][ss_ld(NW)];
   __shared__ float red[3][NW];
+  __shared__ int flag[2];
   const int lane = threadIdx.x;  // the thread's column
   const int vc = blockIdx.y, v = vc / 3;
   const int sy = blockIdx.x / A.TX, sx = blockIdx.x - sy * A.TX;
@@ -171,6 +211,8 @@ __global__ __launch_bounds__(64 * NW) void k_ssim(SsimArgs A, const float* color
       y[i] = in ? b[i] : 0.f;
     }
   };
+  if (lane < 2) flag[lane] = 0;
+  if (NW > 1) __syncthreads();
   float nx[4], ny[4];
 #pragma unroll
   for (int g = 0; g < 3; ++g) {
@@ -198,14 +240,14 @@ __global__ __launch_bounds__(64 * NW) void k_ssim(SsimArgs A, const float* color
       }
       // moments of the statistics rows y0 - 5 + 4 st + i
       ss_v4 m[4];
-      ss_vert<4>(
-          wt,
+      bool alone = ss_vert<4>(
+          A, wt,
           [&](int k, int t) {
             const float x = rx[(u + (t >> 2)) & 3][t & 3], y = ry[(u + (t >> 2)) & 3][t & 3];
             return k == 0 ? x : k == 1 ? y : k == 2 ? x * x + y * y : x * y;
           },
           m);
-      ss_horiz<4, NW>(wt, buf, m);
+      ss_horiz<4, NW>(A, wt, buf, alone, st + 1, flag, m);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int r = y0 - SS_R + 4 * st + i;
@@ -233,8 +275,8 @@ __global__ __launch_bounds__(64 * NW) void k_ssim(SsimArgs A, const float* color
       }
       // blurred maps at the output rows y0 + 4 (st - 3) + i
       ss_v4 bl[3];
-      ss_vert<3>(wt, [&](int k, int t) { return f[k][(u + 1 + (t >> 2)) & 3][t & 3]; }, bl);
-      ss_horiz<3, NW>(wt, buf2, bl);
+      alone = ss_vert<3>(A, wt, [&](int k, int t) { return f[k][(u + 1 + (t >> 2)) & 3][t & 3]; }, bl);
+      ss_horiz<3, NW>(A, wt, buf2, alone, st + 1, flag + 1, bl);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int r = y0 + 4 * (st - 3) + i;

@@ -177,3 +177,30 @@ def test_ssim_grad_strip_edges(H, W):
     for k, key in ((0, "d_a"), (1, "d_b")):
         scale = np.abs(ref["d_color"]).sum(axis=(1, 2, 3)).max()
         assert np.abs(ge[:, k] - ref[key]).max() <= 1e-3 * scale, key
+
+
+@pytest.mark.parametrize("W", [38, 150])
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_ssim_grad_non_finite_stays_local(W, bad):
+    """A NaN or infinite pixel reaches the gradient within two windows of it
+    (10 pixels along each axis) and nowhere else; the rest is the gradient
+    without it, to the rounding of sums formed another way."""
+    announce(f"ssim non-finite {bad} W={W}")
+    import torch
+    from paper_2605_10760_amd import ssim_grad
+    H = 70
+    rng = np.random.default_rng(W)
+    c = rng.random((1, 3, H, W)).astype(np.float32)
+    tgt = rng.random(c.shape).astype(np.float32)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    grads = []
+    pj, pi = 33, min(W - 1, 101) if W > 100 else 17
+    for value in (c[0, 1, pj, pi], bad):
+        c[0, 1, pj, pi] = value
+        d = torch.zeros((1, 3, H, W), device="cuda")
+        ssim_grad(t(c), t(tgt), d, None, None, 1000.0)
+        grads.append(d.cpu().numpy()[0])
+    near = np.zeros((3, H, W), bool)
+    near[1, pj - 10:pj + 11, max(pi - 10, 0):pi + 11] = True
+    assert not np.isfinite(grads[1][near]).any()
+    np.testing.assert_allclose(grads[1][~near], grads[0][~near], rtol=1e-5, atol=1e-7)
