@@ -23,12 +23,12 @@ struct gsr_ctx {
   void* ws = nullptr;
   size_t ws_bytes = 0;
   uint32_t* blk_cnt = nullptr;   // visible pairs per projection block
-  uint32_t* blk_scan = nullptr;  // their exclusive prefix
   uint32_t *ka = nullptr, *va = nullptr, *kb = nullptr, *vb = nullptr;
   uint32_t* hist = nullptr;
   uint32_t* hoff = nullptr;
   BinWork bw{};
   float* grad2d = nullptr;
+  PoseAcc* pose = nullptr;
   unsigned int* sched = nullptr;  // tile cursors of the persistent compositing
   RenderCfg rc{1, 2, false};
   size_t max_blocks = 0, max_sblocks = 0, max_chunks = 0;
@@ -94,8 +94,10 @@ StateLayout state_layout(const gsr_plan_desc& p) {
   const size_t px = V * (size_t)p.width * (size_t)p.height;
   size_t o = 0;
   L.hdr = o; o = align256(o + STATE_HEADER_BYTES);
-  L.zkey = o; o = align256(o + P * 4);
-  L.vidx = o; o = align256(o + P * 4);
+  const size_t nblk = P / PROJ_BLOCK + V + 1;
+  L.vmask = o; o = align256(o + nblk * 32);
+  L.vbase = o; o = align256(o + nblk * 4);
+  L.vkey = o; o = align256(o + P * 4);
   L.rect = o; o = align256(o + P * 8);
   L.rec = o; o = align256(o + P * 48);
   L.order = o; o = align256(o + P * 4);
@@ -113,8 +115,9 @@ StateDev state_ptrs(void* base, const gsr_plan_desc& p) {
   char* b = (char*)base;
   StateDev s;
   s.hdr = (StateHeader*)(b + L.hdr);
-  s.zkey = (uint32_t*)(b + L.zkey);
-  s.vidx = (uint32_t*)(b + L.vidx);
+  s.vmask = (unsigned long long*)(b + L.vmask);
+  s.vbase = (uint32_t*)(b + L.vbase);
+  s.vkey = (uint32_t*)(b + L.vkey);
   s.rect = (uint2*)(b + L.rect);
   s.rec = (float4*)(b + L.rec);
   s.order = (uint32_t*)(b + L.order);
@@ -206,7 +209,8 @@ gsr_status build_tabs(gsr_ctx* c, const gsr_scene* sc, const gsr_views* vw, Call
   memset(&t.set, 0, sizeof t.set);
   long P = 0;
   t.pt.nv = nv;
-  t.pt.W = p.width; t.pt.H = p.height; t.pt.TW = p.tile_w; t.pt.TH = p.tile_h;
+  t.pt.W = p.width; t.pt.H = p.height;
+  t.pt.itw = 1.0f / (float)p.tile_w; t.pt.ith = 1.0f / (float)p.tile_h;
   t.pt.TX = c->TX; t.pt.TY = c->TY;
   t.stb.nv = nv;
   t.bt.nv = nv; t.bt.chunk = c->chunk; t.bt.TX = c->TX; t.bt.TY = c->TY; t.bt.T = c->T;
@@ -258,6 +262,7 @@ gsr_status build_tabs(gsr_ctx* c, const gsr_scene* sc, const gsr_views* vw, Call
   // sets, for the projection backward
   SetTab& st = t.set;
   st.ns = sc->n_sets;
+  st.nv = nv;
   st.W = p.width; st.H = p.height;
   int sb = 0, nvs = 0;
   for (int s = 0; s < sc->n_sets; ++s) {
@@ -271,7 +276,7 @@ gsr_status build_tabs(gsr_ctx* c, const gsr_scene* sc, const gsr_views* vw, Call
   st.set_goff[sc->n_sets] = (int)sc->set_offsets[sc->n_sets];
   st.set_blk[sc->n_sets] = sb;
   st.set_voff[sc->n_sets] = nvs;
-  for (int v = 0; v <= nv; ++v) st.pair_off[v] = t.pt.pair_off[v];
+  for (int v = 0; v <= nv; ++v) st.blk_off[v] = t.pt.blk_off[v];
   return GSR_OK;
 }
 
@@ -399,7 +404,6 @@ gsr_status gsr_plan(gsr_ctx* c, const gsr_plan_desc* p) {
   c->max_chunks = P / (size_t)c->chunk + V + 1;
   size_t o = 0;
   const size_t o_blk = o; o = align256(o + c->max_blocks * 4);
-  const size_t o_bsc = o; o = align256(o + c->max_blocks * 4);
   const size_t o_ka = o; o = align256(o + P * 4);
   const size_t o_va = o; o = align256(o + P * 4);
   const size_t o_kb = o; o = align256(o + P * 4);
@@ -410,6 +414,7 @@ gsr_status gsr_plan(gsr_ctx* c, const gsr_plan_desc* p) {
   const size_t o_rt = o; o = align256(o + V * (size_t)c->TY * 4);
   const size_t o_ap = o; o = align256(o + (c->max_chunks / RC_SUB + 1) * 4);
   const size_t o_g2 = o; o = align256(o + P * GRAD2D * 4);
+  const size_t o_pose = o; o = align256(o + sizeof(PoseAcc));
   const size_t o_sch = o; o = align256(o + SCHED_WORDS * 4);
   void* ws = nullptr;
   hipError_t e = hipMalloc(&ws, o);
@@ -421,7 +426,6 @@ gsr_status gsr_plan(gsr_ctx* c, const gsr_plan_desc* p) {
   c->ws = ws;
   c->ws_bytes = o;
   c->blk_cnt = (uint32_t*)(b + o_blk);
-  c->blk_scan = (uint32_t*)(b + o_bsc);
   c->ka = (uint32_t*)(b + o_ka);
   c->va = (uint32_t*)(b + o_va);
   c->kb = (uint32_t*)(b + o_kb);
@@ -432,15 +436,17 @@ gsr_status gsr_plan(gsr_ctx* c, const gsr_plan_desc* p) {
   c->bw.row_tot = (uint32_t*)(b + o_rt);
   c->bw.area_part = (uint32_t*)(b + o_ap);
   c->grad2d = (float*)(b + o_g2);
+  c->pose = (PoseAcc*)(b + o_pose);
   c->sched = (unsigned int*)(b + o_sch);
   c->rc.fwd_batch = p->fwd_batch == 2 ? 2 : 1;
   c->rc.bwd_batch = p->bwd_batch == 0 ? 1 : p->bwd_batch;
   c->rc.persistent = p->persistent == 1;
   c->rc.bwd_cols = p->bwd_cols == 2 ? 2 : 1;
-  // The per-pair screen-space gradient rows start at zero and every
-  // backward leaves them at zero (the projection backward clears what it
-  // reads), so no clearing pass is needed per call.
+  // The per-pair screen-space gradient rows and the pose sums start at zero and
+  // every backward leaves them at zero (the projection backward clears what
+  // it reads), so no clearing pass is needed per call.
   e = hipMemset(c->grad2d, 0, P * GRAD2D * 4);
+  if (e == hipSuccess) e = hipMemset(c->pose, 0, sizeof(PoseAcc));
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
     free_ws(c);
@@ -474,7 +480,7 @@ gsr_status gsr_forward(gsr_ctx* c, const gsr_scene* sc, const gsr_views* vw,
   }
   {
     StageMark m(c, GSR_STAGE_COMPACT, st);
-    if ((e = launch_compact(t.pt, sd, c->blk_cnt, c->blk_scan, c->ka, st)) != hipSuccess) return hip_fail(c, e, "compact");
+    if ((e = launch_compact(t.pt, sd, c->blk_cnt, st)) != hipSuccess) return hip_fail(c, e, "compact");
   }
   {
     StageMark m(c, GSR_STAGE_RECORD, st);
@@ -524,10 +530,13 @@ gsr_status gsr_backward(gsr_ctx* c, const gsr_scene* sc, const gsr_views* vw,
   const float* gd = gin ? gin->depth : nullptr;
   const float* ga = gin ? gin->alpha : nullptr;
   hipError_t e;
+  // the projection backward writes every pose gradient; without a Gaussian it
+  // is not launched, and the persistent queue's cursor starts every call at 0
   {
     StageMark m(c, GSR_STAGE_ZERO, st);
-    if ((e = launch_zero_pose(out->d_pose, vw->n_views, c->sched + 1, st)) != hipSuccess)
-      return hip_fail(c, e, "zero");
+    if (t.set.set_blk[t.set.ns] == 0 || c->rc.persistent)
+      if ((e = launch_zero_pose(out->d_pose, vw->n_views, c->sched + 1, st)) != hipSuccess)
+        return hip_fail(c, e, "zero");
   }
   {
     StageMark m(c, GSR_STAGE_RENDER_BWD, st);
@@ -538,7 +547,7 @@ gsr_status gsr_backward(gsr_ctx* c, const gsr_scene* sc, const gsr_views* vw,
   }
   {
     StageMark m(c, GSR_STAGE_PROJECT_BWD, st);
-    if ((e = launch_project_bwd(t.set, scd, cam, sd, c->grad2d, *out, t.P, st)) != hipSuccess)
+    if ((e = launch_project_bwd(t.set, scd, cam, sd, c->grad2d, c->pose, *out, st)) != hipSuccess)
       return hip_fail(c, e, "projection backward");
   }
   return GSR_OK;
@@ -579,7 +588,6 @@ gsr_status gsr_debug_export(gsr_ctx* c, const void* state, int32_t n_views, gsr_
   const size_t px = (size_t)n_views * c->plan.width * c->plan.height;
   struct Cp { void* dst; const void* src; size_t bytes; };
   std::vector<Cp> cps;
-  if (d->zkeys) cps.push_back({d->zkeys, sd.zkey, np * 4});
   if (d->order) cps.push_back({d->order, sd.order, std::min<size_t>(np, h.vis_total) * 4});
   // The tile lists are never stored by the forward: debug kernels filter
   // them from the row lists into temporary buffers (counts, host scan,
@@ -642,16 +650,41 @@ gsr_status gsr_debug_export(gsr_ctx* c, const void* state, int32_t n_views, gsr_
   for (auto& x : cps)
     if (x.bytes && (e = hipMemcpy(x.dst, x.src, x.bytes, hipMemcpyDeviceToHost)) != hipSuccess)
       return hip_fail(c, e, "debug copy");
-  // the sorted lists and the rects live at visible-list positions: report
-  // pair ids (the pair of each position, from the position of each pair)
-  // and per-pair rects
+  // keys, rects and the sorted lists live at visible-list positions: report
+  // pair ids (the pair of each position, from the blocks' visible bits), and
+  // per-pair keys and rects
   const size_t nvis = std::min<size_t>((size_t)h.vis_total, (size_t)c->plan.max_pairs);
   std::vector<uint32_t> vpair(nvis, 0xFFFFFFFFu);
-  std::vector<uint32_t> vi(np);
-  if (np && (e = hipMemcpy(vi.data(), sd.vidx, np * 4, hipMemcpyDeviceToHost)) != hipSuccess)
-    return hip_fail(c, e, "debug vidx");
-  for (size_t i = 0; i < np; ++i)
-    if (vi[i] < nvis) vpair[vi[i]] = (uint32_t)i;
+  std::vector<uint32_t> vi(np, 0xFFFFFFFFu);
+  {
+    size_t nblk = 0;
+    for (int v = 0; v < n_views; ++v)
+      nblk += (size_t)ceil_div((long)h.pair_off[v + 1] - (long)h.pair_off[v], PROJ_BLOCK);
+    nblk = std::min(nblk, c->max_blocks);
+    std::vector<unsigned long long> mask(4 * nblk);
+    std::vector<uint32_t> base(nblk);
+    if (nblk && (e = hipMemcpy(mask.data(), sd.vmask, nblk * 32, hipMemcpyDeviceToHost)) != hipSuccess)
+      return hip_fail(c, e, "debug visible bits");
+    if (nblk && (e = hipMemcpy(base.data(), sd.vbase, nblk * 4, hipMemcpyDeviceToHost)) != hipSuccess)
+      return hip_fail(c, e, "debug visible bases");
+    size_t b = 0;
+    for (int v = 0; v < n_views; ++v)
+      for (size_t p0 = h.pair_off[v]; p0 < h.pair_off[v + 1] && b < nblk; p0 += PROJ_BLOCK, ++b) {
+        uint32_t row = base[b];
+        for (int k = 0; k < PROJ_BLOCK; ++k)
+          if ((mask[4 * b + k / 64] >> (k % 64)) & 1ull) {
+            if (p0 + k < np) vi[p0 + k] = row;
+            if (row < nvis) vpair[row] = (uint32_t)(p0 + k);
+            ++row;
+          }
+      }
+  }
+  if (d->zkeys && np) {
+    std::vector<uint32_t> key(std::max<size_t>(nvis, 1));
+    if (nvis && (e = hipMemcpy(key.data(), sd.vkey, nvis * 4, hipMemcpyDeviceToHost)) != hipSuccess)
+      return hip_fail(c, e, "debug keys");
+    for (size_t i = 0; i < np; ++i) d->zkeys[i] = vi[i] < nvis ? key[vi[i]] : CULLED;
+  }
   auto to_pair = [&](uint32_t* a, size_t n) {
     for (size_t i = 0; i < n; ++i) a[i] = a[i] < nvis ? vpair[a[i]] : 0xFFFFFFFFu;
   };

@@ -35,6 +35,18 @@ __device__ __forceinline__ int xcd_remap_mixed(int b, int n) {
   return l < n ? l : -1;
 }
 
+// Visible position of the lane's pair in block b of a view (StateDev::vmask),
+// CULLED if it is culled; w: the wave of the block (uniform).
+__device__ __forceinline__ uint32_t visible_row(const StateDev& st, size_t b, int w) {
+  const unsigned long long* m = st.vmask + 4 * b;
+  uint32_t row = st.vbase[b];
+  for (int k = 0; k < w; ++k) row += (uint32_t)__popcll(m[k]);
+  const unsigned long long mk = m[w];
+  row += __builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32),
+                                   __builtin_amdgcn_mbcnt_lo((uint32_t)mk, 0u));
+  return ((mk >> (threadIdx.x & 63)) & 1ull) ? row : CULLED;
+}
+
 // Index s with off[s] <= b < off[s+1] for a non-decreasing off[0..n].
 __device__ __forceinline__ int find_seg(const int* off, int n, int b) {
   int lo = 0, hi = n;
@@ -154,19 +166,36 @@ __device__ __forceinline__ void cov3_fp64(const float* ls, const float* q, doubl
     }
 }
 
-// FP64 camera-space mean p, its guard-clamped-free ratios (p_x/p_z, p_y/p_z)
-// and the dilated 2D covariance [[a, b], [b, c]] = J (Rc Sigma Rc^T) J^T +
-// 0.3 I of a Gaussian in one view (J at the guard-clamped ratios).
+// Guard limits of the Jacobian's ratios x/z, y/z in a view (1.3 times the
+// half field of view), in the FP32 of the key path and in FP64: formed once
+// per workgroup and view instead of by two divisions per pair and precision.
+struct ViewLim {
+  float lx, ly;
+  double dx, dy;
+};
+__device__ __forceinline__ ViewLim view_lim(float fx, float fy, int W, int H) {
+#pragma clang fp contract(off)
+  return ViewLim{1.3f * ((0.5f * (float)W) / fx), 1.3f * ((0.5f * (float)H) / fy),
+                 1.3 * (0.5 * W) / (double)fx, 1.3 * (0.5 * H) / (double)fy};
+}
+
+// FP64 camera-space mean p, 1 / p_z, its guard-clamped-free ratios (p_x/p_z,
+// p_y/p_z), the camera-space covariance V = Rc Sigma Rc^T and the dilated 2D
+// covariance [[a, b], [b, c]] = J V J^T + 0.3 I of a Gaussian in one view (J at
+// the guard-clamped ratios).
 struct ScreenCov {
   double p[3];
+  double iz;
   double rx, ry;
+  double V[3][3];
   double a, b, c;
 };
 __device__ __forceinline__ ScreenCov screen_cov_fp64(const double Sd[3][3], const float* Rc,
                                                      const float* tc, const float* m, float fxf,
-                                                     float fyf, int W, int H) {
+                                                     float fyf, double limx, double limy) {
   ScreenCov o;
-  double Wd[3][3], V[3][3];
+  double Wd[3][3];
+  auto& V = o.V;
   for (int i = 0; i < 3; ++i)
     for (int k = 0; k < 3; ++k)
       Wd[i][k] = (double)Rc[3 * i] * Sd[0][k] + (double)Rc[3 * i + 1] * Sd[1][k] +
@@ -179,9 +208,9 @@ __device__ __forceinline__ ScreenCov screen_cov_fp64(const double Sd[3][3], cons
              (double)Rc[3 * i + 2] * m[2] + (double)tc[i];
   const double fx = fxf, fy = fyf;
   const double ip2 = 1.0 / o.p[2];
+  o.iz = ip2;
   o.rx = o.p[0] * ip2;
   o.ry = o.p[1] * ip2;
-  const double limx = 1.3 * (0.5 * W) / fx, limy = 1.3 * (0.5 * H) / fy;
   const double rxc = fmin(fmax(o.rx, -limx), limx), ryc = fmin(fmax(o.ry, -limy), limy);
   const double j00 = fx * ip2, j02 = -fx * rxc * ip2;
   const double j11 = fy * ip2, j12 = -fy * ryc * ip2;

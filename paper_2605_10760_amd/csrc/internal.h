@@ -34,7 +34,8 @@ constexpr long SEED_NOALLOC_MAX_POINTS = GSR_SEED_NOALLOC_MAX_POINTS;
 struct ProjTab {
   int nv;
   int P;                      // total pairs of the call
-  int W, H, TW, TH, TX, TY;
+  int W, H, TX, TY;
+  float itw, ith;             // 1 / tile width, height (exact: powers of two)
   int pair_off[MAXV + 1];
   int blk_off[MAXV + 1];      // PROJ_BLOCK-pair blocks per view, prefix
   int g_off[MAXV];            // first global Gaussian of the view's set
@@ -58,13 +59,24 @@ struct BinTab {
 };
 
 struct SetTab {
-  int ns;
+  int ns, nv;
   int set_goff[MAXS + 1];     // Gaussian offsets of the sets
   int set_blk[MAXS + 1];      // PROJ_BLOCK-Gaussian blocks per set, prefix
   int set_voff[MAXS + 1];     // views of each set in view_by_set
   int view_by_set[MAXV];      // view ids grouped by set (grad-needing only)
-  int pair_off[MAXV + 1];
+  int blk_off[MAXV + 1];      // PROJ_BLOCK-pair blocks per view, prefix (ProjTab's)
   int W, H;
+};
+
+// Pose sums of a backward call (context-owned, zero between calls): a share per
+// XCD, with the count of its workgroups that have added theirs, and the count
+// of shares that are complete.
+struct PoseAcc {
+  struct alignas(128) Share {
+    double sum[6 * MAXV];
+    unsigned int done;
+  } share[8];
+  unsigned int done;
 };
 
 struct SceneDev {
@@ -91,20 +103,26 @@ struct StateHeader {
   unsigned int vis_total;
   unsigned long long row_total;   // (pair, tile row) entries of the binning
   unsigned int vis_off[MAXV + 1]; // visible-pair offsets per view (compacted order)
+  unsigned int pair_off[MAXV + 1]; // pair offsets per view (for the debug export)
 };
-constexpr size_t STATE_HEADER_BYTES = 512;
+constexpr size_t STATE_HEADER_BYTES = 1024;
 static_assert(sizeof(StateHeader) <= STATE_HEADER_BYTES, "header");
 
 // Byte offsets of the arrays inside a saved-state buffer (all 256-aligned).
 struct StateLayout {
-  size_t hdr, zkey, vidx, rect, rec, order, row_rg, rows, torder, tfinal, last, total;
+  size_t hdr, vmask, vbase, vkey, rect, rec, order, row_rg, rows, torder, tfinal, last, total;
 };
 
 // Pointers into a saved-state buffer.
 struct StateDev {
   StateHeader* hdr;
-  uint32_t* zkey;     // [P]
-  uint32_t* vidx;     // [P] position in the compacted visible list, CULLED if culled
+  // A view's pairs are cut into blocks of PROJ_BLOCK (ProjTab::blk_off); pair
+  // 64 w + l of block b is visible iff bit l of vmask[4 b + w] is set, and
+  // its position in the compacted visible list (view-major, pair order) is
+  // vbase[b] plus the set bits before it in the block.
+  unsigned long long* vmask;  // [4 blocks]
+  uint32_t* vbase;    // [blocks]
+  uint32_t* vkey;     // [Pv] by visible position: FP32 bits of camera z
   uint2* rect;        // [Pv] by visible position: packed (x0 | y0 << 16, x1 | y1 << 16)
   float4* rec;        // [Pv][3] by visible position: (u, v, A', B'), (C', sigma, z, ex),
                       //   (r, g, b, ey)
@@ -143,8 +161,7 @@ hipError_t launch_project_keys(const ProjTab& t, const SceneDev& sc, const CamDe
                                StateDev st, uint32_t* blk_cnt, hipStream_t s);
 hipError_t launch_project_records(const ProjTab& t, const SceneDev& sc, const CamDev& cam,
                                   StateDev st, hipStream_t s);
-hipError_t launch_compact(const ProjTab& t, StateDev st, const uint32_t* blk_cnt,
-                          uint32_t* blk_scan, uint32_t* kout, hipStream_t s);
+hipError_t launch_compact(const ProjTab& t, StateDev st, const uint32_t* blk_cnt, hipStream_t s);
 hipError_t launch_depth_sort(const SortTab& t, StateDev st, uint32_t* ka, uint32_t* va,
                              uint32_t* kb, uint32_t* vb, uint32_t* hist, uint32_t* off,
                              hipStream_t s);
@@ -180,8 +197,8 @@ hipError_t launch_count_blend(int nv, int W, int H, int TW, int TH, int TX, int 
                               hipStream_t s);
 hipError_t launch_zero_pose(float* d_pose, int nv, unsigned int* bwd_next, hipStream_t s);
 hipError_t launch_project_bwd(const SetTab& t, const SceneDev& sc, const CamDev& cam,
-                              StateDev st, float* grad2d, const gsr_grads& g,
-                              int n_total, hipStream_t s);
+                              StateDev st, float* grad2d, PoseAcc* pa,
+                              const gsr_grads& g, hipStream_t s);
 hipError_t launch_pose_delta(const float* vin, const float* delta, float* vout, int nv,
                              hipStream_t s);
 hipError_t launch_sim3_gaussians(const SimSetTab& tab, const float* m_in, const float* ls_in,

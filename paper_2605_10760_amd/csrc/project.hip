@@ -4,12 +4,15 @@
 // Key pass: one thread per Gaussian, looping over the views of its set; each
 // pair evaluates the key path in FP32 with no fused multiply-add and a fixed
 // operation order (it decides culling, the tile rectangle and the depth key
-// and must match an FP32 re-evaluation bit for bit) and writes a 4-byte key,
-// with one visible count per 256-pair block for the ordered compaction that
-// follows.  Record pass: for visible pairs, the rect again and the
-// screen-space record in FP64 rounded once to FP32 (the 2D conic of an
-// elongated splat loses digits to cancellation in FP32), one pair per lane
-// from a per-wave queue of the wave's visible pairs.  The parameters are
+// and must match an FP32 re-evaluation bit for bit) and leaves one bit, with one
+// visible count per 256-pair block: a scan of the counts gives every visible
+// pair its position in the ordered compaction (no array per pair is written
+// or read: keys and positions of every pair, culled ones included, were
+// 16 B of traffic each, and a compaction kernel of 45 us on 13.4M pairs and
+// 461 us on 144M).  Record pass: for visible pairs, the depth key and the rect
+// again and the screen-space record in FP64 rounded once to FP32 (the 2D
+// conic of an elongated splat loses digits to cancellation in FP32), one pair
+// per lane from a per-wave queue of the wave's visible pairs.  The parameters are
 // read once per Gaussian in each pass (coalesced AoS rows); the record pass
 // writes one 48-byte record and one 8-byte rect per visible pair.
 #include <algorithm>
@@ -109,8 +112,8 @@ __device__ __forceinline__ KeyGauss key_gauss(const float* ls, const float* q, f
 // Returns false when the pair is culled.
 __device__ __forceinline__ bool key_view(const float* m, const KeyGauss& g, const float* Rc,
                                          const float* tc, float fx, float fy, float cx, float cy,
-                                         int W, int H, int TW, int TH, int TX, int TY,
-                                         float z_near, KeyResult& kr) {
+                                         float limx, float limy, float itw, float ith, int TX,
+                                         int TY, float z_near, KeyResult& kr) {
 #pragma clang fp contract(off)
   const float p0 = ((Rc[0] * m[0] + Rc[1] * m[1]) + Rc[2] * m[2]) + tc[0];
   const float p1 = ((Rc[3] * m[0] + Rc[4] * m[1]) + Rc[5] * m[2]) + tc[1];
@@ -132,8 +135,6 @@ __device__ __forceinline__ bool key_view(const float* m, const KeyGauss& g, cons
   const float rx = p0 / p2, ry = p1 / p2;
   const float u = fx * rx + cx;
   const float v = fy * ry + cy;
-  const float limx = 1.3f * ((0.5f * (float)W) / fx);
-  const float limy = 1.3f * ((0.5f * (float)H) / fy);
   const float rxc = rx < -limx ? -limx : (rx > limx ? limx : rx);
   const float ryc = ry < -limy ? -limy : (ry > limy ? limy : ry);
   const float j00 = fx / p2, j02 = -(fx * rxc) / p2;
@@ -151,7 +152,6 @@ __device__ __forceinline__ bool key_view(const float* m, const KeyGauss& g, cons
   const float ex = sqrtf(g.k2 * a);
   const float ey = sqrtf(g.k2 * c);
   if (!(isfinite(u) && isfinite(v) && isfinite(ex) && isfinite(ey))) return false;
-  const float itw = 1.0f / (float)TW, ith = 1.0f / (float)TH;
   const float fX = (float)TX, fY = (float)TY;
   float fx0 = floorf((u - ex) * itw);
   float fx1 = floorf((u + ex) * itw) + 1.f;
@@ -175,8 +175,8 @@ __device__ __forceinline__ bool key_view(const float* m, const KeyGauss& g, cons
 // opacity threshold) is done once, instead of once per view.  Pair p of view
 // v is Gaussian p - pair_off[v] of the set, so the workgroup's 256 Gaussians
 // are the 256-pair block (blk_off[v] + its block index in the set) of each
-// view.  Writes the depth key (or CULLED) of every pair and the visible
-// count of every 256-pair block, for the ordered compaction that follows.
+// view.  Writes the visible bits and the visible count of every 256-pair
+// block, for the ordered compaction that follows.
 __global__ __launch_bounds__(PROJ_BLOCK) void k_project(ProjTab t, SceneDev sc, CamDev cam,
                                                         StateDev st, uint32_t* blk_cnt) {
   const int b = xcd_remap(blockIdx.x, t.set_gblk[t.ns]);
@@ -195,21 +195,32 @@ __global__ __launch_bounds__(PROJ_BLOCK) void k_project(ProjTab t, SceneDev sc, 
     q[0] = q4.x; q[1] = q4.y; q[2] = q4.z; q[3] = q4.w;
     o = sc.opac[gi];
   }
+  // the views' guard limits, formed once per workgroup
+  __shared__ float lim[2][MAXV];
+  if ((int)threadIdx.x < t.set_voff[s + 1] - t.set_voff[s]) {
+    const float* f = cam.intrinsics + 4 * t.vset[t.set_voff[s] + (int)threadIdx.x];
+    const ViewLim l = view_lim(f[0], f[1], t.W, t.H);
+    lim[0][threadIdx.x] = l.lx;
+    lim[1][threadIdx.x] = l.ly;
+  }
   KeyGauss kg = key_gauss(ls, q, o);
   kg.ok = kg.ok && valid;
+  __syncthreads();
   for (int vi = t.set_voff[s]; vi < t.set_voff[s + 1]; ++vi) {
     const int v = t.vset[vi];
-    const int pair = t.pair_off[v] + local;
     const float* vm = cam.viewmats + 12 * v;
     const float Rc[9] = {vm[0], vm[1], vm[2], vm[4], vm[5], vm[6], vm[8], vm[9], vm[10]};
     const float tc[3] = {vm[3], vm[7], vm[11]};
     const float4 in = *reinterpret_cast<const float4*>(cam.intrinsics + 4 * v);
     KeyResult kr;
-    const bool vis = key_view(m, kg, Rc, tc, in.x, in.y, in.z, in.w, t.W, t.H, t.TW, t.TH, t.TX,
-                              t.TY, cam.z_near, kr);
-    if (valid) st.zkey[pair] = vis ? __float_as_uint(kr.p2) : CULLED;
+    const int k = vi - t.set_voff[s];
+    const bool vis = key_view(m, kg, Rc, tc, in.x, in.y, in.z, in.w, lim[0][k], lim[1][k], t.itw,
+                              t.ith, t.TX, t.TY, cam.z_near, kr);
+    const unsigned long long mk = __ballot(vis);
+    const size_t bi = (size_t)(t.blk_off[v] + lb);
+    if (lane_id() == 0) st.vmask[4 * bi + (threadIdx.x >> 6)] = mk;
     const int cnt = __syncthreads_count(vis);
-    if (threadIdx.x == 0) blk_cnt[t.blk_off[v] + lb] = (uint32_t)cnt;
+    if (threadIdx.x == 0) blk_cnt[bi] = (uint32_t)cnt;
   }
 }
 
@@ -234,15 +245,22 @@ struct RecSlot {
   double Sd[6][64];    // FP64 covariance (00, 01, 02, 11, 12, 22)
   float sig[64], k2f[64];
   float col[3][64];
-  uint32_t item[RQ], row[RQ];
+  uint32_t row[RQ];
+  uint16_t item[RQ];   // lane | view of the set << 6
+};
+// The views of the workgroup's set: ids and guard limits.
+struct RecViews {
+  double dx[MAXV], dy[MAXV];
+  float lx[MAXV], ly[MAXV];
+  uint16_t id[MAXV];
 };
 
 template <int SHD>
 __device__ __forceinline__ void record_one(const ProjTab& t, const SceneDev& sc,
                                            const CamDev& cam, const StateDev& st,
-                                           const RecSlot& L, long g0, uint32_t item,
-                                           uint32_t row) {
-  const int l = (int)(item & 63u), v = (int)(item >> 6);
+                                           const RecSlot& L, const RecViews& RV, long g0,
+                                           uint32_t item, uint32_t row) {
+  const int l = (int)(item & 63u), k = (int)(item >> 6), v = RV.id[k];
   const float m[3] = {L.m[0][l], L.m[1][l], L.m[2][l]};
   KeyGauss kg;
   kg.S00 = L.S[0][l]; kg.S01 = L.S[1][l]; kg.S02 = L.S[2][l];
@@ -256,14 +274,17 @@ __device__ __forceinline__ void record_one(const ProjTab& t, const SceneDev& sc,
   KeyResult kr;
   // visible in the key pass, so visible here (the same pure function of the
   // same inputs); an empty rect would only drop the pair
-  if (!key_view(m, kg, Rc, tc, in.x, in.y, in.z, in.w, t.W, t.H, t.TW, t.TH, t.TX, t.TY,
-                cam.z_near, kr))
+  if (!key_view(m, kg, Rc, tc, in.x, in.y, in.z, in.w, RV.lx[k], RV.ly[k], t.itw, t.ith, t.TX,
+                t.TY, cam.z_near, kr)) {
     kr.x0 = kr.x1 = kr.y0 = kr.y1 = 0u;
+    kr.p2 = cam_depth32(m, Rc, tc);
+  }
+  st.vkey[row] = __float_as_uint(kr.p2);  // the depth sort's input
   st.rect[row] = make_uint2(kr.x0 | (kr.y0 << 16), kr.x1 | (kr.y1 << 16));
   double Sd[3][3];
   Sd[0][0] = L.Sd[0][l]; Sd[0][1] = Sd[1][0] = L.Sd[1][l]; Sd[0][2] = Sd[2][0] = L.Sd[2][l];
   Sd[1][1] = L.Sd[3][l]; Sd[1][2] = Sd[2][1] = L.Sd[4][l]; Sd[2][2] = L.Sd[5][l];
-  ScreenCov sc2 = screen_cov_fp64(Sd, Rc, tc, m, in.x, in.y, t.W, t.H);
+  ScreenCov sc2 = screen_cov_fp64(Sd, Rc, tc, m, in.x, in.y, RV.dx[k], RV.dy[k]);
   const double fx = in.x, fy = in.y;
   const double* p = sc2.p;
   const double rx = sc2.rx, ry = sc2.ry;
@@ -282,11 +303,11 @@ __device__ __forceinline__ void record_one(const ProjTab& t, const SceneDev& sc,
     constexpr int NB = (SHD + 1) * (SHD + 1);
     float Y[16];
     sh_eval<SHD>(dx, dy, dz, Y);
-    const float* k = sc.colors + (long)3 * sc.sh_stride * (g0 + l);
+    const float* kc = sc.colors + (long)3 * sc.sh_stride * (g0 + l);
     float r = 0.5f, g = 0.5f, bl = 0.5f;
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
-      r += Y[i] * k[3 * i]; g += Y[i] * k[3 * i + 1]; bl += Y[i] * k[3 * i + 2];
+      r += Y[i] * kc[3 * i]; g += Y[i] * kc[3 * i + 1]; bl += Y[i] * kc[3 * i + 2];
     }
     cv[0] = fmaxf(r, 0.f); cv[1] = fmaxf(g, 0.f); cv[2] = fmaxf(bl, 0.f);
   }
@@ -308,6 +329,7 @@ template <int SHD>
 __global__ __launch_bounds__(PROJ_BLOCK) void k_records(ProjTab t, SceneDev sc, CamDev cam,
                                                         StateDev st) {
   __shared__ RecSlot slots[PROJ_BLOCK / 64];
+  __shared__ RecViews RV;
   const int b = xcd_remap(blockIdx.x, t.set_gblk[t.ns]);
   if (b < 0) return;
   const int s = find_seg(t.set_gblk, t.ns, b);
@@ -356,34 +378,45 @@ __global__ __launch_bounds__(PROJ_BLOCK) void k_records(ProjTab t, SceneDev sc, 
     }
     L.col[0][lane] = col[0]; L.col[1][lane] = col[1]; L.col[2][lane] = col[2];
   }
+  if ((int)threadIdx.x < t.set_voff[s + 1] - t.set_voff[s]) {
+    const int v = t.vset[t.set_voff[s] + (int)threadIdx.x];
+    const ViewLim lm = view_lim(cam.intrinsics[4 * v], cam.intrinsics[4 * v + 1], t.W, t.H);
+    RV.dx[threadIdx.x] = lm.dx;
+    RV.dy[threadIdx.x] = lm.dy;
+    RV.lx[threadIdx.x] = lm.lx;
+    RV.ly[threadIdx.x] = lm.ly;
+    RV.id[threadIdx.x] = (uint16_t)v;
+  }
+  __syncthreads();
   uint32_t head = 0u, tail = 0u;
   for (int vi = t.set_voff[s]; vi < t.set_voff[s + 1]; ++vi) {
     const int v = t.vset[vi];
-    const uint32_t row = valid ? st.vidx[t.pair_off[v] + local] : CULLED;
+    const uint32_t row = visible_row(st, (size_t)(t.blk_off[v] + lb), wv);
     const bool vis = row != CULLED;
     const unsigned long long mk = __ballot(vis);
     if (vis) {
       const uint32_t k = (tail + __builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32),
                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)mk, 0u))) &
                          (RQ - 1);
-      L.item[k] = (uint32_t)lane | ((uint32_t)v << 6);
+      L.item[k] = (uint16_t)(lane | ((vi - t.set_voff[s]) << 6));
       L.row[k] = row;
     }
     tail += (uint32_t)__popcll(mk);
     __builtin_amdgcn_wave_barrier();
     if (tail - head >= 64u) {
       const uint32_t k = (head + (uint32_t)lane) & (RQ - 1);
-      record_one<SHD>(t, sc, cam, st, L, g0, L.item[k], L.row[k]);
+      record_one<SHD>(t, sc, cam, st, L, RV, g0, L.item[k], L.row[k]);
       head += 64u;
       __builtin_amdgcn_wave_barrier();
     }
   }
   if ((uint32_t)lane < tail - head) {
     const uint32_t k = (head + (uint32_t)lane) & (RQ - 1);
-    record_one<SHD>(t, sc, cam, st, L, g0, L.item[k], L.row[k]);
+    record_one<SHD>(t, sc, cam, st, L, RV, g0, L.item[k], L.row[k]);
   }
 }
 
+// Ordered compaction: visible pairs keep their (view-major, id) order.
 // Exclusive scan of the per-block visible counts and the per-view offsets
 // of the compacted, view-major visible-pair list, over ceil(nb / 4096)
 // workgroups: workgroup b scans tile b after summing every count before it,
@@ -421,64 +454,12 @@ __global__ __launch_bounds__(1024) void k_scan_blocks(ProjTab t, const uint32_t*
   __syncthreads();
   // view offsets: the scanned value of the view's first block, or the total
   // for views whose blocks start at nb (empty views at the end)
+  if (last)
+    for (int v = threadIdx.x; v <= t.nv; v += 1024) hdr->pair_off[v] = (unsigned int)t.pair_off[v];
   for (int v = threadIdx.x; v < t.nv; v += 1024) {
     const int f = t.blk_off[v];
     if (f >= base && f < base + SB_TILE && f < nb) hdr->vis_off[v] = scan[f];
     else if (f >= nb && last) hdr->vis_off[v] = (uint32_t)all;
-  }
-}
-
-// Ordered compaction: visible pairs keep their (view-major, id) order.  A
-// workgroup takes CP_SUB consecutive 256-pair blocks (their keys loaded
-// together, then compacted block by block).
-constexpr int CP_SUB = 4;
-__global__ __launch_bounds__(PROJ_BLOCK) void k_compact(ProjTab t, StateDev st,
-                                                        const uint32_t* blk_scan,
-                                                        uint32_t* kout) {
-  const int nb = t.blk_off[t.nv];
-  const int g = xcd_remap(blockIdx.x, (nb + CP_SUB - 1) / CP_SUB);
-  if (g < 0) return;
-  __shared__ int wc[CP_SUB][PROJ_BLOCK / 64];
-  const int lane = lane_id(), w = threadIdx.x >> 6;
-  uint32_t key[CP_SUB];
-  int pair[CP_SUB];
-  bool in[CP_SUB];
-#pragma unroll
-  for (int k = 0; k < CP_SUB; ++k) {
-    const int b = g * CP_SUB + k;
-    in[k] = false;
-    key[k] = CULLED;
-    pair[k] = 0;
-    if (b < nb) {
-      const int v = find_seg(t.blk_off, t.nv, b);
-      const int local = (b - t.blk_off[v]) * PROJ_BLOCK + (int)threadIdx.x;
-      pair[k] = t.pair_off[v] + local;
-      in[k] = local < t.pair_off[v + 1] - t.pair_off[v];
-      if (in[k]) key[k] = st.zkey[pair[k]];
-    }
-  }
-  unsigned long long m[CP_SUB];
-#pragma unroll
-  for (int k = 0; k < CP_SUB; ++k) {
-    m[k] = __ballot(key[k] != CULLED);
-    if (lane == 0) wc[k][w] = __popcll(m[k]);
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < CP_SUB; ++k) {
-    const int b = g * CP_SUB + k;
-    if (b >= nb) break;
-    uint32_t pos = CULLED;
-    if (key[k] != CULLED) {
-      pos = blk_scan[b] + (uint32_t)__popcll(m[k] & ((1ull << lane) - 1ull));
-      for (int i = 0; i < w; ++i) pos += wc[k][i];
-      // the sort carries the visible position (its first pass takes each
-      // key's index as its value)
-      kout[pos] = key[k];
-    }
-    // position of the pair in the compacted visible list (the row of its
-    // screen-space gradient), CULLED for culled pairs
-    if (in[k]) st.vidx[pair[k]] = pos;
   }
 }
 
@@ -549,14 +530,9 @@ hipError_t launch_project_records(const ProjTab& t, const SceneDev& sc, const Ca
   return hipGetLastError();
 }
 
-hipError_t launch_compact(const ProjTab& t, StateDev st, const uint32_t* blk_cnt,
-                          uint32_t* blk_scan, uint32_t* kout, hipStream_t s) {
+hipError_t launch_compact(const ProjTab& t, StateDev st, const uint32_t* blk_cnt, hipStream_t s) {
   hipLaunchKernelGGL(k_scan_blocks, dim3(std::max(1, (t.blk_off[t.nv] + SB_TILE - 1) / SB_TILE)),
-                     dim3(1024), 0, s, t, blk_cnt, blk_scan, st.hdr);
-  const int nb = t.blk_off[t.nv];
-  if (nb > 0)
-    hipLaunchKernelGGL(k_compact, dim3(xcd_grid((nb + CP_SUB - 1) / CP_SUB)), dim3(PROJ_BLOCK), 0,
-                       s, t, st, blk_scan, kout);
+                     dim3(1024), 0, s, t, blk_cnt, st.vbase, st.hdr);
   return hipGetLastError();
 }
 

@@ -236,10 +236,10 @@ hipError_t launch_depth_sort(const SortTab& t, StateDev st, uint32_t* ka, uint32
   const int nb = t.sblk_off[t.nv];
   if (nb == 0) return hipSuccess;
   const dim3 g(xcd_grid(nb)), blk(SORT_THREADS), sg(t.nv), sb(RADIX * SCAN_Q);
-  // pass 0: A -> B
-  hipLaunchKernelGGL(k_radix_hist<0>, g, blk, 0, s, t, st.hdr, ka, hist);
+  // pass 0: state keys -> B
+  hipLaunchKernelGGL(k_radix_hist<0>, g, blk, 0, s, t, st.hdr, st.vkey, hist);
   hipLaunchKernelGGL(k_radix_scan, sg, sb, 0, s, t, st.hdr, hist, off);
-  hipLaunchKernelGGL((k_radix_scatter<0, true, true>), g, blk, 0, s, t, st.hdr, hist, off, ka,
+  hipLaunchKernelGGL((k_radix_scatter<0, true, true>), g, blk, 0, s, t, st.hdr, hist, off, st.vkey,
                      (const uint32_t*)nullptr, kb, vb);
   // pass 1: B -> A
   hipLaunchKernelGGL(k_radix_hist<8>, g, blk, 0, s, t, st.hdr, kb, hist);

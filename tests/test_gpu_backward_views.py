@@ -1,0 +1,54 @@
+"""The projection backward's two ways through a set's views against each other:
+one call with views in all directions, where a lane takes the views that see
+its own Gaussian, and one call per view, where a wave takes the views in
+turn.  Gradients agree to the rounding of their sums (RERUN_TOL of the
+tensor's largest value), and a second backward of the same call finds the
+per-pair rows and the pose sums cleared."""
+import numpy as np
+import pytest
+
+from gpu_harness import RERUN_TOL, announce
+from synth.scenes import ROOM_HI, ROOM_LO, Scene, Views, draw_gaussians, look_at, pinhole
+
+pytestmark = pytest.mark.gpu
+
+PARAMS = ("d_means", "d_log_scales", "d_quats", "d_opacity_logits", "d_colors")
+
+
+# one Gaussian, a partial and a full wave and workgroup, several workgroups of
+# two sets; up to the largest number of views
+@pytest.mark.parametrize("sizes,n_views,sh", [
+    ((1,), 3, 0), ((63, 64), 64, 3), ((257,), 33, 1), ((256, 1), 20, 2), ((700, 300), 64, 0)])
+def test_views_in_turn_and_own_views(sizes, n_views, sh):
+    import torch
+    from paper_2605_10760_amd import Rasterizer, SceneTensors, ViewTensors
+    announce(f"backward views {sizes} {n_views} sh {sh}")
+    rng = np.random.default_rng(sum(sizes) + n_views)
+    n, W, H = sum(sizes), 64, 48
+    scene = Scene(*draw_gaussians(rng, n, ROOM_LO, ROOM_HI, sh_degree=sh),
+                  set_offsets=np.cumsum((0,) + sizes).astype(np.int64), sh_degree=sh)
+    vm = [look_at(rng.uniform(-0.5, 0.5, 3), rng.uniform(-1, 1, 3) * [3.0, 1.5, 2.0], 0.2)
+          for _ in range(n_views)]
+    # the last set sees two views of three
+    vs = np.where(np.arange(n_views) % 3 == 0, 0, len(sizes) - 1).astype(np.int32)
+    views = Views(np.array(vm, np.float32),
+                  np.array([pinhole(W, H, W / 2.0)] * n_views, np.float32), vs, W, H)
+    st, vt = SceneTensors.from_numpy(scene), ViewTensors.from_numpy(views)
+    up = [torch.from_numpy(rng.choice([-1.0, 1.0], s).astype(np.float32)).cuda()
+          for s in ((n_views, 3, H, W), (n_views, H, W), (n_views, H, W))]
+    big = Rasterizer(W, H, n_views * n, n_views)
+    *_, state = big.forward(st, vt)
+    runs = [{k: v.clone() for k, v in big.backward(st, vt, state, *up).items()} for _ in range(2)]
+    one = Rasterizer(W, H, n, 1)
+    total = {k: torch.zeros_like(runs[0][k]) for k in PARAMS + ("d_pose",)}
+    for k in range(n_views):
+        vk = vt.select([k])
+        *_, sk = one.forward(st, vk)
+        gk = one.backward(st, vk, sk, *[x[k:k + 1].contiguous() for x in up])
+        for q in PARAMS:
+            total[q] += gk[q]
+        total["d_pose"][k] = gk["d_pose"][0]
+    for g in runs:
+        for q in PARAMS + ("d_pose",):
+            err = float((total[q] - g[q]).abs().max())
+            assert err <= RERUN_TOL * float(total[q].abs().max()), (q, err)
