@@ -5,14 +5,17 @@
 // sum_c |s_c - mean(s)| (s = exp(log-scale)) with respect to the log-scales,
 // added into the caller's gradient (HBM-bound: 12 B read, 12 B read-modify-
 // written per Gaussian).
-// k_normal_grad: one 16 x 16 output tile per workgroup.  The depth of the
-// tile plus a two-pixel halo goes to LDS; every pixel of the tile plus a
-// one-pixel halo computes its depth-induced normal (central differences of
-// back-projected points) and the gradients of its cosine loss with respect
-// to its two difference vectors, also to LDS; each output pixel then gathers
-// the four difference-vector gradients that involve it and projects them on
-// its ray.  The difference vectors are formed from depth differences and the
-// exact ray differences (2 / f), which keeps FP32 cancellation small.
+// k_normal_grad: a wave marches down a strip of 64 columns (60 written, two of
+// halo on either side) over NR rows.  Every pixel computes its depth-induced
+// normal (central differences of back-projected points) and the gradients of its
+// cosine loss with respect to its two difference vectors; each output pixel
+// gathers the four difference-vector gradients that involve it, the vertical ones
+// from the registers of the rows before and after, the horizontal ones from
+// the neighbouring lanes, and projects them on its ray.  The difference
+// vectors are formed from depth differences and the exact ray differences
+// (2 / f), which keeps FP32 cancellation small.  HBM-bound, 24 B per pixel:
+// 48 views of 640 x 480 in 78 us (157 by 16 x 16 tiles through LDS), 8 views in 19
+// (30; 23 with 16 rows to a wave).
 // k_seed_*: ordered compaction (per-block counts, summed by each later block,
 // wave-ballot ranks) of the pixels with positive depth on a stride grid,
 // each writing one isotropic Gaussian at its back-projected point.
@@ -48,9 +51,8 @@ hipError_t launch_iso_grad(long n, const float* ls, float w, float* g, hipStream
 }
 
 // ------------------------------------------------------------ normal loss
-constexpr int NT = 16;       // output tile edge
-constexpr int NG = NT + 2;   // pixels whose normals the tile needs
-constexpr int ND = NT + 4;   // depth samples those normals read
+constexpr int NR = 8;        // rows per wave
+constexpr int NC = 60;       // columns written per wave
 
 struct F3 {
   float x, y, z;
@@ -59,80 +61,95 @@ __device__ __forceinline__ F3 cross3(F3 a, F3 b) {
   return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
 }
 
-__global__ __launch_bounds__(256) void k_normal_grad(int W, int H, int tiles_x, int tiles_y,
+// The value of the lane before / after (0 past the wave's ends).
+__device__ __forceinline__ float lane_before(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+                                       0, __builtin_bit_cast(int, x), 0x138, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float lane_after(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+                                       0, __builtin_bit_cast(int, x), 0x130, 0xF, 0xF, true));
+}
+
+__global__ __launch_bounds__(256) void k_normal_grad(int W, int H, int tiles_x, int tiles_y, long n,
                                                      const float* depth, const float* prior,
                                                      const float* intr, float w, float* g_dep) {
-  __shared__ float sd[ND][ND];
-  __shared__ float sg[6][NG][NG];  // (ga, gb) of every pixel of the tile + halo
+  const long u = (long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  if (u >= n) return;
   const int tpv = tiles_x * tiles_y;
-  const int v = blockIdx.x / tpv;
-  const int t = blockIdx.x - v * tpv;
-  const int j0 = (t / tiles_x) * NT, i0 = (t % tiles_x) * NT;
+  const int v = (int)(u / tpv), t = (int)(u - (long)v * tpv);
+  const int r0 = (t / tiles_x) * NR, r1 = min(H, r0 + NR);
+  const int lane = lane_id(), i = (t % tiles_x) * NC - 2 + lane;
+  const bool in = i >= 0 && i < W;                        // a pixel of the image
+  const bool out = in && lane >= 2 && lane < 2 + NC;      // written
   const size_t HW = (size_t)H * W;
-  const float* dv = depth + v * HW;
-  for (int k = threadIdx.x; k < ND * ND; k += 256) {
-    const int j = j0 - 2 + k / ND, i = i0 - 2 + k % ND;
-    sd[k / ND][k % ND] = (j >= 0 && j < H && i >= 0 && i < W) ? dv[(size_t)j * W + i] : 0.f;
-  }
+  const float* dv = depth + v * HW + i;
+  const float* pv = prior + v * 3 * HW + i;
+  float* gv = g_dep + v * HW + i;
   const float fx = intr[4 * v], fy = intr[4 * v + 1], cx = intr[4 * v + 2], cy = intr[4 * v + 3];
   const float ifx = 1.f / fx, ify = 1.f / fy;
-  __syncthreads();
-  for (int k = threadIdx.x; k < NG * NG; k += 256) {
-    const int lj = k / NG, li = k % NG;
-    const int j = j0 - 1 + lj, i = i0 - 1 + li;
+  const float xi = ((float)i + 0.5f - cx) * ifx, xr = ((float)(i + 1) + 0.5f - cx) * ifx;
+  const auto load_d = [&](int j) { return in && j >= 0 && j < H ? dv[(size_t)j * W] : 0.f; };
+  const auto load_p = [&](int j) {
+    F3 p{0.f, 0.f, 0.f};
+    if (in && j >= 0 && j < H) {
+      const size_t q = (size_t)j * W;
+      p = F3{pv[q], pv[q + HW], pv[q + 2 * HW]};
+    }
+    return p;
+  };
+  const auto load_g = [&](int j) { return out && j >= r0 && j < r1 ? gv[(size_t)j * W] : 0.f; };
+  // depth of rows j - 1, j, j + 1; prior of row j, gradient of row j - 1: the
+  // loads of a step are issued one step ahead
+  float dd = load_d(r0 - 2), d0 = load_d(r0 - 1), du = load_d(r0), g = 0.f;
+  F3 p = load_p(r0 - 1);
+  F3 ga2{0.f, 0.f, 0.f}, ga1{0.f, 0.f, 0.f}, gb1{0.f, 0.f, 0.f};  // of rows j - 2, j - 1
+  for (int j = r0 - 1; j <= r1; ++j) {
+    const float dn = load_d(j + 2), gn = load_g(j);
+    const F3 pn = load_p(j + 1);
+    const float dr = lane_after(d0), dl = lane_before(d0);
     F3 ga{0.f, 0.f, 0.f}, gb{0.f, 0.f, 0.f};
-    if (j >= 1 && j < H - 1 && i >= 1 && i < W - 1) {
-      const float du = sd[lj + 2][li + 1], dd = sd[lj][li + 1];
-      const float dr = sd[lj + 1][li + 2], dl = sd[lj + 1][li];
-      if (du > 0.f && dd > 0.f && dr > 0.f && dl > 0.f) {
-        const float xi = ((float)i + 0.5f - cx) * ifx, yj = ((float)j + 0.5f - cy) * ify;
-        const float xr = ((float)(i + 1) + 0.5f - cx) * ifx;
-        const float yu = ((float)(j + 1) + 0.5f - cy) * ify;
-        // a = P(i, j+1) - P(i, j-1), b = P(i+1, j) - P(i-1, j)
-        const float ev = du - dd, eh = dr - dl;
-        const F3 a{ev * xi, ev * yu + dd * (2.f * ify), ev};
-        const F3 b{eh * xr + dl * (2.f * ifx), eh * yj, eh};
-        const F3 c = cross3(a, b);
-        const float n2 = c.x * c.x + c.y * c.y + c.z * c.z;
-        if (n2 > 0.f) {
-          const float inr = rsqrtf(n2);
-          const F3 n{c.x * inr, c.y * inr, c.z * inr};
-          const size_t q = v * 3 * HW + (size_t)j * W + i;
-          const F3 p{prior[q], prior[q + HW], prior[q + 2 * HW]};
-          const float dot = n.x * p.x + n.y * p.y + n.z * p.z;
-          const float sc = w * inr;
-          const F3 gc{sc * (dot * n.x - p.x), sc * (dot * n.y - p.y), sc * (dot * n.z - p.z)};
-          ga = cross3(b, gc);
-          gb = cross3(gc, a);
-        }
+    if (j >= 1 && j < H - 1 && i >= 1 && i < W - 1 && du > 0.f && dd > 0.f && dr > 0.f &&
+        dl > 0.f) {
+      const float yj = ((float)j + 0.5f - cy) * ify, yu = ((float)(j + 1) + 0.5f - cy) * ify;
+      // a = P(i, j+1) - P(i, j-1), b = P(i+1, j) - P(i-1, j)
+      const float ev = du - dd, eh = dr - dl;
+      const F3 a{ev * xi, ev * yu + dd * (2.f * ify), ev};
+      const F3 b{eh * xr + dl * (2.f * ifx), eh * yj, eh};
+      const F3 c = cross3(a, b);
+      const float n2 = c.x * c.x + c.y * c.y + c.z * c.z;
+      if (n2 > 0.f) {
+        const float inr = rsqrtf(n2);
+        const F3 n{c.x * inr, c.y * inr, c.z * inr};
+        const float dot = n.x * p.x + n.y * p.y + n.z * p.z;
+        const float sc = w * inr;
+        const F3 gc{sc * (dot * n.x - p.x), sc * (dot * n.y - p.y), sc * (dot * n.z - p.z)};
+        ga = cross3(b, gc);
+        gb = cross3(gc, a);
       }
     }
-    sg[0][lj][li] = ga.x;
-    sg[1][lj][li] = ga.y;
-    sg[2][lj][li] = ga.z;
-    sg[3][lj][li] = gb.x;
-    sg[4][lj][li] = gb.y;
-    sg[5][lj][li] = gb.z;
+    // the point P(i, j-1) is the "+" end of the vertical difference of
+    // (i, j-2), the "-" end of that of (i, j), and likewise horizontally
+    const float px = ga2.x - ga.x + lane_before(gb1.x) - lane_after(gb1.x);
+    const float py = ga2.y - ga.y + lane_before(gb1.y) - lane_after(gb1.y);
+    const float pz = ga2.z - ga.z + lane_before(gb1.z) - lane_after(gb1.z);
+    if (out && j > r0) {
+      const float ry = ((float)(j - 1) + 0.5f - cy) * ify;
+      gv[(size_t)(j - 1) * W] = g + (xi * px + ry * py + pz);
+    }
+    dd = d0; d0 = du; du = dn;
+    p = pn;
+    g = gn;
+    ga2 = ga1; ga1 = ga; gb1 = gb;
   }
-  __syncthreads();
-  const int lj = threadIdx.x / NT, li = threadIdx.x % NT;
-  const int j = j0 + lj, i = i0 + li;
-  if (j >= H || i >= W) return;
-  // the point P(i, j) is the "+" end of the vertical difference of (i, j-1),
-  // the "-" end of that of (i, j+1), and likewise horizontally
-  const int gj = lj + 1, gi = li + 1;
-  const float px = sg[0][gj - 1][gi] - sg[0][gj + 1][gi] + sg[3][gj][gi - 1] - sg[3][gj][gi + 1];
-  const float py = sg[1][gj - 1][gi] - sg[1][gj + 1][gi] + sg[4][gj][gi - 1] - sg[4][gj][gi + 1];
-  const float pz = sg[2][gj - 1][gi] - sg[2][gj + 1][gi] + sg[5][gj][gi - 1] - sg[5][gj][gi + 1];
-  const float rx = ((float)i + 0.5f - cx) * ifx, ry = ((float)j + 0.5f - cy) * ify;
-  g_dep[v * HW + (size_t)j * W + i] += rx * px + ry * py + pz;
 }
 
 hipError_t launch_normal_grad(int nv, int W, int H, const float* depth, const float* prior,
                               const float* intr, float w, float* g_dep, hipStream_t s) {
-  const int tx = (W + NT - 1) / NT, ty = (H + NT - 1) / NT;
-  hipLaunchKernelGGL(k_normal_grad, dim3((unsigned)(nv * tx * ty)), dim3(256), 0, s, W, H, tx,
-                     ty, depth, prior, intr, w, g_dep);
+  const int tx = (W + NC - 1) / NC, ty = (H + NR - 1) / NR;
+  const long n = (long)nv * tx * ty;  // waves
+  hipLaunchKernelGGL(k_normal_grad, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, W, H, tx, ty, n,
+                     depth, prior, intr, w, g_dep);
   return hipGetLastError();
 }
 

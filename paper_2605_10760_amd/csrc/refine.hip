@@ -21,20 +21,24 @@ __global__ __launch_bounds__(256) void k_zero_f32(float* p, int n) {
 }
 
 // A view's pixels are spread over blocks_per_view blocks that stride through
-// them, so the exposure sums take few atomics per view.  Pixels go four at a
+// them, so the exposure sums take few atomics per view: every atomic of a call
+// falls on a few lines of g_expo, about 10 ns each (8 views of
+// 640 x 480 with sums, 118 MB: 2048 workgroups of 256 threads 66 us, 1024 and 512
+// of 1024 threads 29 us, 256 of them 23 us).  Pixels go four at a
 // time (16-byte loads and stores) when the plane size and every pointer
 // allow it, one at a time otherwise.
 __device__ __forceinline__ float l1_sign(float e, float w) {
   return e > 0.f ? w : (e < 0.f ? -w : 0.f);
 }
 
+constexpr int L1_NT = 1024;
 template <bool VEC>
-__global__ __launch_bounds__(256) void k_l1_grad(int HW, int blocks_per_view, const float* color,
+__global__ __launch_bounds__(L1_NT) void k_l1_grad(int HW, int blocks_per_view, const float* color,
                                                  const float* depth, const float* tcol,
                                                  const float* tdep, const float* expo,
                                                  float w_col, float w_dep, float* g_col,
                                                  float* g_dep, float* g_expo) {
-  __shared__ float red[2][4];
+  __shared__ float red[2][L1_NT / 64];
   const int v = blockIdx.x / blocks_per_view;
   const int b0 = blockIdx.x - v * blocks_per_view;
   const float a = expo ? expo[2 * v] : 0.f, b = expo ? expo[2 * v + 1] : 0.f;
@@ -42,7 +46,7 @@ __global__ __launch_bounds__(256) void k_l1_grad(int HW, int blocks_per_view, co
   float sa = 0.f, sb = 0.f;
   if (VEC) {
     const int n4 = HW / 4;
-    for (int p = b0 * 256 + (int)threadIdx.x; p < n4; p += blocks_per_view * 256) {
+    for (int p = b0 * L1_NT + (int)threadIdx.x; p < n4; p += blocks_per_view * L1_NT) {
       const size_t base = (size_t)v * 3 * HW + 4 * (size_t)p;
 #pragma unroll
       for (int ch = 0; ch < 3; ++ch) {
@@ -67,7 +71,7 @@ __global__ __launch_bounds__(256) void k_l1_grad(int HW, int blocks_per_view, co
       }
     }
   } else {
-    for (int p = b0 * 256 + (int)threadIdx.x; p < HW; p += blocks_per_view * 256) {
+    for (int p = b0 * L1_NT + (int)threadIdx.x; p < HW; p += blocks_per_view * L1_NT) {
       const size_t base = (size_t)v * 3 * HW + p;
 #pragma unroll
       for (int ch = 0; ch < 3; ++ch) {
@@ -92,11 +96,14 @@ __global__ __launch_bounds__(256) void k_l1_grad(int HW, int blocks_per_view, co
     red[1][w] = sb;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    atomicAdd(&g_expo[2 * v], ea * (red[0][0] + red[0][1] + red[0][2] + red[0][3]));
-    atomicAdd(&g_expo[2 * v + 1], red[1][0] + red[1][1] + red[1][2] + red[1][3]);
-  }
+  if (w > 1) return;
+  // wave 0 adds up the first sum, wave 1 the second
+  const float tot = wave_total(lane_id() < L1_NT / 64 ? red[w][lane_id()] : 0.f);
+  if (lane_id() == 0) atomicAdd(&g_expo[2 * v + w], w == 0 ? ea * tot : tot);
 }
+
+// Workgroups of a call with exposure sums: one per compute unit
+constexpr int L1_EXPO_BLOCKS = 256;
 
 hipError_t launch_l1_grad(int nv, int HW, const float* color, const float* depth,
                           const float* tcol, const float* tdep, const float* expo, float w_col,
@@ -109,12 +116,13 @@ hipError_t launch_l1_grad(int nv, int HW, const float* color, const float* depth
   // kernel in flight at once); with exposure sums, fewer blocks per view
   // (each adds to the view's two sums with one atomic apiece)
   const int per = vec ? HW / 4 : HW;
-  const int bpv = std::min((per + 255) / 256, std::max(64, (g_expo ? 2048 : 16384) / nv));
+  const int bpv = std::min((per + L1_NT - 1) / L1_NT,
+                           g_expo ? std::max(1, L1_EXPO_BLOCKS / nv) : std::max(16, 4096 / nv));
   if (vec)
-    hipLaunchKernelGGL(k_l1_grad<true>, dim3(nv * bpv), dim3(256), 0, s, HW, bpv, color, depth,
+    hipLaunchKernelGGL(k_l1_grad<true>, dim3(nv * bpv), dim3(L1_NT), 0, s, HW, bpv, color, depth,
                        tcol, tdep, expo, w_col, w_dep, g_col, g_dep, g_expo);
   else
-    hipLaunchKernelGGL(k_l1_grad<false>, dim3(nv * bpv), dim3(256), 0, s, HW, bpv, color, depth,
+    hipLaunchKernelGGL(k_l1_grad<false>, dim3(nv * bpv), dim3(L1_NT), 0, s, HW, bpv, color, depth,
                        tcol, tdep, expo, w_col, w_dep, g_col, g_dep, g_expo);
   return hipGetLastError();
 }

@@ -61,6 +61,14 @@ def test_normal_loss_grad_matches_oracle(V, H, W):
     np.testing.assert_allclose(got, ref, rtol=1e-3, atol=1e-4 * scale)
 
 
+# a wave writes 60 columns and 8 rows: one less, one more, two strips and a bit,
+# and images narrower than a strip's halo
+@pytest.mark.parametrize("V,H,W", [(1, 7, 59), (2, 8, 60), (1, 9, 61), (1, 24, 64), (2, 17, 121),
+                                   (1, 3, 180), (1, 200, 4)])
+def test_normal_loss_grad_strip_edges(V, H, W):
+    test_normal_loss_grad_matches_oracle(V, H, W)
+
+
 def test_normal_loss_grad_full_size_sampled():
     """48 views at 640 x 480 in one launch; views 0, 17 and 47 against the
     oracle (views are independent; the oracle's mean runs over its own

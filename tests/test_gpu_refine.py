@@ -46,6 +46,13 @@ def test_l1_loss_grad_matches_oracle(H, W):
             assert amb.sum() < 20
 
 
+# several workgroups of 1024 per view, the last one partly filled, four pixels at
+# a time and one at a time
+@pytest.mark.parametrize("H,W", [(130, 64), (67, 129)])
+def test_l1_loss_grad_several_workgroups(H, W):
+    test_l1_loss_grad_matches_oracle(H, W)
+
+
 def test_prune_matches_oracle():
     announce("refine prune")
     import torch
