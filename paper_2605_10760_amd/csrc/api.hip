@@ -434,6 +434,8 @@ gsr_status gsr_plan(gsr_ctx* c, const gsr_plan_desc* p) {
   c->hoff = (uint32_t*)(b + o_hoff);
   c->bw.counts = (uint32_t*)(b + o_cnt);
   c->bw.row_tot = (uint32_t*)(b + o_rt);
+  c->bw.rect_lo = c->ka;  // the last sort pass reads kb, vb
+  c->bw.rect_hi = c->va;
   c->bw.area_part = (uint32_t*)(b + o_ap);
   c->grad2d = (float*)(b + o_g2);
   c->pose = (PoseAcc*)(b + o_pose);

@@ -140,6 +140,8 @@ struct StateDev {
 struct BinWork {
   uint32_t* counts;     // [chunks][TY] per-chunk row counts -> exclusive bases
   uint32_t* row_tot;    // [V*TY] entries per (view, row)
+  uint32_t* rect_lo;    // [P] the rects in depth order (rect.x and rect.y), in sort
+  uint32_t* rect_hi;    //   buffers that the depth sort has done with
   uint32_t* area_part;  // [chunks / RC_SUB + 1] (pair, tile) copies per counting workgroup
 };
 

@@ -13,7 +13,8 @@
 // do, else one per digit present in the wave for the top digit), one
 // workgroup per view turning the [block][digit] counts into
 // scatter bases in (digit, block) order (a separate array: the scatter also
-// reads its block's counts), and a scatter where each 256-key round is
+// reads its block's counts; with few blocks the scatter forms its bases from
+// the counts itself), and a scatter where each 256-key round is
 // ranked stably inside the block by wave64 ballots over the digit bits, the
 // block is reordered by digit in LDS and written out in runs.
 #include "common.h"
@@ -146,7 +147,8 @@ __global__ __launch_bounds__(RADIX* SCAN_Q) void k_radix_scan(SortTab t, const S
 // slot by slot: a digit's run of the block (about 8 keys) is stored by
 // consecutive lanes to consecutive addresses instead of one scattered store
 // per key.
-template <int SH, bool KEYS_OUT, bool VAL_INDEX = false>
+// FOLD: no scan kernel, every block walks the view's counts itself.
+template <bool FOLD, int SH, bool KEYS_OUT, bool VAL_INDEX = false>
 __global__ __launch_bounds__(SORT_THREADS) void k_radix_scatter(
     SortTab t, const StateHeader* hdr, const uint32_t* hist, const uint32_t* off,
     const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout) {
@@ -180,7 +182,34 @@ __global__ __launch_bounds__(SORT_THREADS) void k_radix_scatter(
     const uint32_t c = hist[(size_t)b * RADIX + tid];
     const uint32_t o = (uint32_t)wg_excl_scan<SORT_THREADS>(c, sh, &tot);
     loff[tid] = o;
-    goff[tid] = off[(size_t)b * RADIX + tid];
+    if (FOLD) {
+      // thread d: digit d's count over the view's blocks and over those before
+      // this one
+      const int seg = (int)hdr->vis_off[v], nb = ((int)hdr->vis_off[v + 1] - seg + SORT_TILE - 1) / SORT_TILE;
+      const int lb = (lo - seg) / SORT_TILE;
+      const uint32_t* h = hist + (size_t)t.sblk_off[v] * RADIX + tid;
+      uint32_t before = 0, all = 0;
+      int k = 0;
+      for (; k + 16 <= nb; k += 16) {
+        uint32_t x[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) x[j] = h[(size_t)(k + j) * RADIX];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+          all += x[j];
+          before += k + j < lb ? x[j] : 0u;
+        }
+      }
+      for (; k < nb; ++k) {
+        const uint32_t x = h[(size_t)k * RADIX];
+        all += x;
+        before += k < lb ? x : 0u;
+      }
+      __syncthreads();
+      goff[tid] = (uint32_t)seg + (uint32_t)wg_excl_scan<SORT_THREADS>(all, sh, &tot) + before;
+    } else {
+      goff[tid] = off[(size_t)b * RADIX + tid];
+    }
     cnt[tid] = 0;
   }
   __syncthreads();
@@ -230,32 +259,46 @@ __global__ __launch_bounds__(SORT_THREADS) void k_radix_scatter(
   }
 }
 
+// Pass 0: state keys -> B, pass 1: B -> A, pass 2: A -> B, pass 3: B -> state
+// order (values only).
+template <bool FOLD>
+static void sort_passes(const SortTab& t, const StateDev& st, uint32_t* ka, uint32_t* va,
+                        uint32_t* kb, uint32_t* vb, uint32_t* hist, uint32_t* off, hipStream_t s) {
+  const dim3 g(xcd_grid(t.sblk_off[t.nv])), blk(SORT_THREADS), sg(t.nv), sb(RADIX * SCAN_Q);
+  const uint32_t* none = nullptr;
+  const auto scan = [&] {
+    if (!FOLD) hipLaunchKernelGGL(k_radix_scan, sg, sb, 0, s, t, st.hdr, hist, off);
+  };
+  hipLaunchKernelGGL(k_radix_hist<0>, g, blk, 0, s, t, st.hdr, st.vkey, hist);
+  scan();
+  hipLaunchKernelGGL((k_radix_scatter<FOLD, 0, true, true>), g, blk, 0, s, t, st.hdr, hist, off,
+                     st.vkey, none, kb, vb);
+  hipLaunchKernelGGL(k_radix_hist<8>, g, blk, 0, s, t, st.hdr, kb, hist);
+  scan();
+  hipLaunchKernelGGL((k_radix_scatter<FOLD, 8, true>), g, blk, 0, s, t, st.hdr, hist, off, kb, vb,
+                     ka, va);
+  hipLaunchKernelGGL(k_radix_hist<16>, g, blk, 0, s, t, st.hdr, ka, hist);
+  scan();
+  hipLaunchKernelGGL((k_radix_scatter<FOLD, 16, true>), g, blk, 0, s, t, st.hdr, hist, off, ka, va,
+                     kb, vb);
+  hipLaunchKernelGGL(k_radix_hist<24>, g, blk, 0, s, t, st.hdr, kb, hist);
+  scan();
+  hipLaunchKernelGGL((k_radix_scatter<FOLD, 24, false>), g, blk, 0, s, t, st.hdr, hist, off, kb,
+                     vb, (uint32_t*)nullptr, st.order);
+}
+
+// Blocks of a call (upper bound) up to which each scatter block walks its view's
+// counts itself: four launches less.  One view of 1M pairs (489 blocks) 462 ->
+// 454 us a pass, 8 views of 400k (1563) 1054 -> 1043; 48 views of 278k (6542)
+// 2934 -> 2965, where the walks cost more than the launches.
+constexpr int FOLD_BLOCKS = 2048;
+
 hipError_t launch_depth_sort(const SortTab& t, StateDev st, uint32_t* ka, uint32_t* va,
                              uint32_t* kb, uint32_t* vb, uint32_t* hist, uint32_t* off,
                              hipStream_t s) {
-  const int nb = t.sblk_off[t.nv];
-  if (nb == 0) return hipSuccess;
-  const dim3 g(xcd_grid(nb)), blk(SORT_THREADS), sg(t.nv), sb(RADIX * SCAN_Q);
-  // pass 0: state keys -> B
-  hipLaunchKernelGGL(k_radix_hist<0>, g, blk, 0, s, t, st.hdr, st.vkey, hist);
-  hipLaunchKernelGGL(k_radix_scan, sg, sb, 0, s, t, st.hdr, hist, off);
-  hipLaunchKernelGGL((k_radix_scatter<0, true, true>), g, blk, 0, s, t, st.hdr, hist, off, st.vkey,
-                     (const uint32_t*)nullptr, kb, vb);
-  // pass 1: B -> A
-  hipLaunchKernelGGL(k_radix_hist<8>, g, blk, 0, s, t, st.hdr, kb, hist);
-  hipLaunchKernelGGL(k_radix_scan, sg, sb, 0, s, t, st.hdr, hist, off);
-  hipLaunchKernelGGL((k_radix_scatter<8, true>), g, blk, 0, s, t, st.hdr, hist, off, kb, vb, ka,
-                     va);
-  // pass 2: A -> B
-  hipLaunchKernelGGL(k_radix_hist<16>, g, blk, 0, s, t, st.hdr, ka, hist);
-  hipLaunchKernelGGL(k_radix_scan, sg, sb, 0, s, t, st.hdr, hist, off);
-  hipLaunchKernelGGL((k_radix_scatter<16, true>), g, blk, 0, s, t, st.hdr, hist, off, ka, va, kb,
-                     vb);
-  // pass 3: B -> state order (values only)
-  hipLaunchKernelGGL(k_radix_hist<24>, g, blk, 0, s, t, st.hdr, kb, hist);
-  hipLaunchKernelGGL(k_radix_scan, sg, sb, 0, s, t, st.hdr, hist, off);
-  hipLaunchKernelGGL((k_radix_scatter<24, false>), g, blk, 0, s, t, st.hdr, hist, off, kb, vb,
-                     (uint32_t*)nullptr, st.order);
+  if (t.sblk_off[t.nv] == 0) return hipSuccess;
+  (t.sblk_off[t.nv] <= FOLD_BLOCKS ? sort_passes<true> : sort_passes<false>)(t, st, ka, va, kb, vb, hist, off,
+                                                                  s);
   return hipGetLastError();
 }
 

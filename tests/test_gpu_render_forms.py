@@ -68,3 +68,27 @@ def test_wave_and_workgroup_forms(tile, cols, W, H, n_views):
     for q in PARAMS:
         err = float((total[q] - g[q]).abs().max())
         assert err <= RERUN_TOL * float(g[q].abs().max()), (q, err)
+
+
+# 64 views of 33 sort blocks each (2112: past the limit up to which a block walks
+# its view's digit counts itself), of 32 (2048: at it)
+@pytest.mark.parametrize("n", [65537, 65536])
+def test_sort_with_and_without_scan_kernel(n):
+    """The depth order of a call on either side of the limit equals that of one
+    call per view, bit for bit."""
+    from paper_2605_10760_amd import Rasterizer, SceneTensors, ViewTensors
+    announce(f"sort forms {n}")
+    W, H, n_views = 64, 48, 64
+    scene, views = _case(n, n_views, W, H)
+    st, vt = SceneTensors.from_numpy(scene), ViewTensors.from_numpy(views)
+    big = Rasterizer(W, H, n_views * n, n_views)
+    *_, state = big.forward(st, vt)
+    dbg = big.debug_export(state, n_views, n_views * n, 0)
+    one = Rasterizer(W, H, n, 1)
+    for k in (0, 1, 31, 63):
+        *_, sk = one.forward(st, vt.select([k]))
+        ek = one.debug_export(sk, 1, n, 0)
+        lo, hi = int(dbg["vis_off"][k]), int(dbg["vis_off"][k + 1])
+        assert hi - lo == int(ek["vis_off"][1]) > 4096
+        np.testing.assert_array_equal(dbg["order"][lo:hi].astype(np.int64) - k * n,
+                                      ek["order"].astype(np.int64))
