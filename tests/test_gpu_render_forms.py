@@ -92,3 +92,42 @@ def test_sort_with_and_without_scan_kernel(n):
         assert hi - lo == int(ek["vis_off"][1]) > 4096
         np.testing.assert_array_equal(dbg["order"][lo:hi].astype(np.int64) - k * n,
                                       ek["order"].astype(np.int64))
+
+
+# views of a set: below and from the number on which the key pass queues its pairs
+@pytest.mark.parametrize("n,n_views", [(64, 5), (700, 21), (1500, 64)])
+def test_key_pass_with_and_without_queue(n, n_views):
+    """Splats of all sizes and shapes, most of them across or beyond the image's
+    edges or the near plane, some without a finite rectangle; views of any
+    scale: the same pairs are visible, with the same depth keys and rectangles,
+    as in one call per view."""
+    from paper_2605_10760_amd import Rasterizer, SceneTensors, ViewTensors
+    announce(f"key pass forms {n} {n_views}")
+    W, H = 72, 40
+    scene, views = _case(n, n_views, W, H)
+    rng = np.random.default_rng(n)
+    scene.log_scales[:] = rng.normal(-2.5, 1.5, (n, 3))
+    scene.opacity_logits[:] = rng.normal(-3.0, 2.5, n)
+    bad = rng.permutation(n)[:4]
+    scene.means[bad[0]] = np.nan
+    scene.log_scales[bad[1], 1] = 60.0
+    scene.means[bad[2]] = 1e30
+    scene.quats[bad[3]] = 0.0
+    views.viewmats[1::3, :, :3] *= 1.7
+    views.viewmats[2::3, 0, :3] *= 0.4
+    views.intrinsics[::4, 0] *= 3.0
+    views.intrinsics[3::4, 3] += 25.0
+    views.intrinsics[2, 1] *= -1.0
+    st, vt = SceneTensors.from_numpy(scene), ViewTensors.from_numpy(views)
+    big = Rasterizer(W, H, n_views * n, n_views)
+    *_, state = big.forward(st, vt)
+    dbg = big.debug_export(state, n_views, n_views * n, 0)
+    one = Rasterizer(W, H, n, 1)
+    seen = 0
+    for k in range(n_views):
+        *_, sk = one.forward(st, vt.select([k]))
+        ek = one.debug_export(sk, 1, n, 0)
+        np.testing.assert_array_equal(dbg["zkeys"][k * n:(k + 1) * n], ek["zkeys"])
+        np.testing.assert_array_equal(dbg["rects"][k * n:(k + 1) * n], ek["rects"])
+        seen += int(ek["vis_off"][1])
+    assert 0.03 * n * n_views < seen < 0.9 * n * n_views
