@@ -412,7 +412,7 @@ gsr_status gsr_plan(gsr_ctx* c, const gsr_plan_desc* p) {
   const size_t o_hoff = o; o = align256(o + c->max_sblocks * RADIX * 4);
   const size_t o_cnt = o; o = align256(o + c->max_chunks * (size_t)c->TY * 4);
   const size_t o_rt = o; o = align256(o + V * (size_t)c->TY * 4);
-  const size_t o_ap = o; o = align256(o + (c->max_chunks / RC_SUB + 1) * 4);
+  const size_t o_ap = o; o = align256(o + (size_t)vis_grid(c->max_chunks) * 8);
   const size_t o_g2 = o; o = align256(o + P * GRAD2D * 4);
   const size_t o_pose = o; o = align256(o + sizeof(PoseAcc));
   const size_t o_sch = o; o = align256(o + SCHED_WORDS * 4);
@@ -436,7 +436,7 @@ gsr_status gsr_plan(gsr_ctx* c, const gsr_plan_desc* p) {
   c->bw.row_tot = (uint32_t*)(b + o_rt);
   c->bw.rect_lo = c->ka;  // the last sort pass reads kb, vb
   c->bw.rect_hi = c->va;
-  c->bw.area_part = (uint32_t*)(b + o_ap);
+  c->bw.area_part = (unsigned long long*)(b + o_ap);
   c->grad2d = (float*)(b + o_g2);
   c->pose = (PoseAcc*)(b + o_pose);
   c->sched = (unsigned int*)(b + o_sch);

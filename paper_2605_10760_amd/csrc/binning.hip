@@ -19,12 +19,14 @@
 
 namespace gsr {
 
-__device__ __forceinline__ void chunk_range(const BinTab& t, const StateHeader* hdr, int b,
-                                            int& v, int& lo, int& hi) {
-  v = find_seg(t.cblk_off, t.nv, b);
-  const int lc = b - t.cblk_off[v];
-  lo = (int)hdr->vis_off[v] + lc * t.chunk;
-  hi = min((int)hdr->vis_off[v + 1], lo + t.chunk);
+// View, number in the counts and pairs [lo, hi) of visible chunk i.
+__device__ __forceinline__ void chunk_range(const BinTab& t, const VisBlocks& vb, int i, int& v,
+                                            int& b, int& lo, int& hi) {
+  int lc, first, last;
+  vb.locate(i, v, lc, first, last);
+  b = t.cblk_off[v] + lc;
+  lo = first + lc * t.chunk;
+  hi = min(last, lo + t.chunk);
 }
 
 __device__ __forceinline__ void unpack_rect(uint2 r, int& x0, int& y0, int& x1, int& y1) {
@@ -43,62 +45,70 @@ __device__ __forceinline__ void unpack_rect(uint2 r, int& x0, int& y0, int& x1, 
 // keyframes) 60 -> 73 and 139 -> 105.
 __global__ __launch_bounds__(256) void k_row_count(BinTab t, StateDev st, BinWork w) {
   __shared__ int dif[RC_SUB][MAX_ROWS + 1];
-  __shared__ uint32_t wsum[4];
-  const int nc = t.cblk_off[t.nv];
-  const int g = xcd_remap(blockIdx.x, (nc + RC_SUB - 1) / RC_SUB);
-  if (g < 0) return;
+  __shared__ unsigned long long wsum[4];
   const int TY = t.TY;
-  int lo[RC_SUB], hi[RC_SUB];
-  uint2 rc[RC_SUB];
+  unsigned long long area = 0;
+  VisBlocks vb(st.hdr, t.nv, t.chunk, RC_SUB);
+  for (; vb.i < vb.end; vb.i += vb.step) {
+    int bk[RC_SUB], lo[RC_SUB], hi[RC_SUB];
+    uint2 rc[RC_SUB];
 #pragma unroll
-  for (int k = 0; k < RC_SUB; ++k) {
-    const int b = g * RC_SUB + k;
-    lo[k] = hi[k] = 0;
-    if (b < nc) {
-      int v;
-      chunk_range(t, st.hdr, b, v, lo[k], hi[k]);
+    for (int k = 0; k < RC_SUB; ++k) {
+      const int c = vb.i * RC_SUB + k;
+      bk[k] = lo[k] = hi[k] = 0;
+      if (c < vb.n) {
+        int v;
+        chunk_range(t, vb, c, v, bk[k], lo[k], hi[k]);
+      }
+      // a chunk holds at most 256 pairs: one per thread
+      const int i = lo[k] + (int)threadIdx.x;
+      rc[k] = i < hi[k] ? st.rect[st.order[i]] : make_uint2(0u, 0u);
+      if (i < hi[k]) {
+        w.rect_lo[i] = rc[k].x;
+        w.rect_hi[i] = rc[k].y;
+      }
     }
-    // a chunk holds at most 256 pairs: one per thread
-    const int i = lo[k] + (int)threadIdx.x;
-    rc[k] = i < hi[k] ? st.rect[st.order[i]] : make_uint2(0u, 0u);
-    if (i < hi[k]) {
-      w.rect_lo[i] = rc[k].x;
-      w.rect_hi[i] = rc[k].y;
+    for (int i = threadIdx.x; i < RC_SUB * (MAX_ROWS + 1); i += 256) (&dif[0][0])[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < RC_SUB; ++k) {
+      if (lo[k] + (int)threadIdx.x < hi[k]) {
+        int x0, y0, x1, y1;
+        unpack_rect(rc[k], x0, y0, x1, y1);
+        atomicAdd(&dif[k][y0], 1);
+        atomicSub(&dif[k][y1], 1);
+        area += (unsigned long long)((x1 - x0) * (y1 - y0));
+      }
     }
+    __syncthreads();
+    // wave k: inclusive scan of chunk k's difference array, 64 rows at a time
+    const int k = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    int b = bk[0], n = hi[0] - lo[0];
+#pragma unroll
+    for (int j = 1; j < RC_SUB; ++j)
+      if (k == j) {
+        b = bk[j];
+        n = hi[j] - lo[j];
+      }
+    if (n > 0) {
+      int carry = 0;
+      for (int base = 0; base < TY; base += 64) {
+        const int y = base + lane_id();
+        const int x = y < TY ? dif[k][y] : 0;
+        const int inc = (int)wave_incl_scan((uint32_t)x) + carry;
+        if (y < TY) w.counts[(size_t)b * TY + y] = (uint32_t)inc;
+        carry = __shfl(inc, 63, 64);
+      }
+    }
+    __syncthreads();  // the next chunks reuse the LDS
   }
-  for (int i = threadIdx.x; i < RC_SUB * (MAX_ROWS + 1); i += 256) (&dif[0][0])[i] = 0;
-  __syncthreads();
-  uint32_t area = 0;
+  // (pair, tile) copies of the workgroup's pairs, one partial per workgroup: the
+  // row range scan adds them up
 #pragma unroll
-  for (int k = 0; k < RC_SUB; ++k) {
-    if (lo[k] + (int)threadIdx.x < hi[k]) {
-      int x0, y0, x1, y1;
-      unpack_rect(rc[k], x0, y0, x1, y1);
-      atomicAdd(&dif[k][y0], 1);
-      atomicSub(&dif[k][y1], 1);
-      area += (uint32_t)((x1 - x0) * (y1 - y0));
-    }
-  }
-  // (pair, tile) copies of the workgroup's pairs (at most 1024 x 512 x 512),
-  // one partial per workgroup: the row range scan adds them up
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) area += (uint32_t)__shfl_xor((int)area, d, 64);
+  for (int d = 32; d >= 1; d >>= 1) area += __shfl_xor(area, d, 64);
   if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = area;
   __syncthreads();
-  if (threadIdx.x == 0) w.area_part[g] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-  // wave k: inclusive scan of chunk k's difference array, 64 rows at a time
-  const int k = threadIdx.x >> 6;
-  const int b = g * RC_SUB + k;
-  if (b < nc && lo[k] < hi[k]) {
-    int carry = 0;
-    for (int base = 0; base < TY; base += 64) {
-      const int y = base + lane_id();
-      const int x = y < TY ? dif[k][y] : 0;
-      const int inc = (int)wave_incl_scan((uint32_t)x) + carry;
-      if (y < TY) w.counts[(size_t)b * TY + y] = (uint32_t)inc;
-      carry = __shfl(inc, 63, 64);
-    }
-  }
+  if (threadIdx.x == 0) w.area_part[blockIdx.x] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
 }
 
 // Exclusive prefix of a [chunk][cols] count matrix down each column over the
@@ -167,7 +177,7 @@ __global__ __launch_bounds__(1024) void k_range_scan(int n, const uint32_t* cnt,
                                                     unsigned long long cap,
                                                     unsigned long long* total,
                                                     unsigned int* flag, int np,
-                                                    const uint32_t* part,
+                                                    const unsigned long long* part,
                                                     unsigned long long* part_total) {
   __shared__ unsigned long long sh[17];
   const int base = (int)blockIdx.x * RS_TILE;
@@ -226,74 +236,76 @@ __device__ __forceinline__ int wave_max_i(int x) {
 __global__ __launch_bounds__(256) void k_row_scatter(BinTab t, StateDev st, BinWork w) {
   constexpr int STEPS = MAX_CHUNK / 64;
   __shared__ uint32_t curs[4][MAX_ROWS];
-  const int nc = t.cblk_off[t.nv];
+  if (st.hdr->overflow) return;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int b = xcd_remap(blockIdx.x, (nc + 3) / 4) * 4 + wave;
-  if (b < 0 || b >= nc) return;
-  int v, lo, hi;
-  chunk_range(t, st.hdr, b, v, lo, hi);
-  if (lo >= hi || st.hdr->overflow) return;
-  const int lane = threadIdx.x & 63, TY = t.TY;
-  const int nsteps = (hi - lo + 63) / 64;
-  // the chunk's pairs and rects, every load issued before the first use
-  uint32_t pid[STEPS];
-  uint2 rc[STEPS];
-#pragma unroll
-  for (int k = 0; k < STEPS; ++k) {
-    const int i = min(lo + k * 64 + lane, hi - 1);
-    pid[k] = st.order[i];
-    rc[k] = make_uint2(w.rect_lo[i], w.rect_hi[i]);
-  }
-  int y0[STEPS], span[STEPS];
-  uint32_t xs[STEPS];
-  int ymin = TY, ymax = 0;
-#pragma unroll
-  for (int k = 0; k < STEPS; ++k) {
-    const bool valid = lo + k * 64 + lane < hi;
-    y0[k] = (int)(rc[k].x >> 16);
-    const int y1 = (int)(rc[k].y >> 16);
-    span[k] = valid ? y1 - y0[k] : 0;
-    xs[k] = (rc[k].x & 0xFFFF) | (rc[k].y << 16);
-    if (valid && y1 > y0[k]) {
-      ymin = min(ymin, y0[k]);
-      ymax = max(ymax, y1);
-    }
-  }
-  ymin = __builtin_amdgcn_readfirstlane(wave_min_i(ymin));
-  ymax = __builtin_amdgcn_readfirstlane(wave_max_i(ymax));
-  uint32_t* cw = curs[wave];
-  for (int y = ymin + lane; y < ymax; y += 64)
-    cw[y] = st.row_rg[(size_t)v * TY + y].x + w.counts[(size_t)b * TY + y];
-  __builtin_amdgcn_wave_barrier();
-  // row by row: a ballot per 64 pairs; the row's stores of the chunk are
-  // issued back to back onto consecutive entries.  They stay inside the row's
-  // range: the counts used the same y0 <= y < y1 rule, and an overflowing
-  // row level returned above.
-#pragma unroll 1
-  for (int y = ymin; y < ymax; ++y) {
-    uint32_t c = (uint32_t)__builtin_amdgcn_readfirstlane((int)cw[y]);
+  VisBlocks vb(st.hdr, t.nv, t.chunk, 4);
+  for (; vb.i < vb.end; vb.i += vb.step) {
+    if (vb.i * 4 + wave >= vb.n) break;  // no barriers: a wave ends by itself
+    int v, b, lo, hi;
+    chunk_range(t, vb, vb.i * 4 + wave, v, b, lo, hi);
+    const int lane = threadIdx.x & 63, TY = t.TY;
+    const int nsteps = (hi - lo + 63) / 64;
+    // the chunk's pairs and rects, every load issued before the first use
+    uint32_t pid[STEPS];
+    uint2 rc[STEPS];
 #pragma unroll
     for (int k = 0; k < STEPS; ++k) {
-      if (k < nsteps) {
-        const bool cov = (unsigned)(y - y0[k]) < (unsigned)span[k];
-        const unsigned long long m = __ballot(cov);
-        if (cov) {
-          const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
-              (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-          st.rows[c + rank] = make_uint2(pid[k], xs[k]);
-        }
-        c += (uint32_t)__popcll(m);
+      const int i = min(lo + k * 64 + lane, hi - 1);
+      pid[k] = st.order[i];
+      rc[k] = make_uint2(w.rect_lo[i], w.rect_hi[i]);
+    }
+    int y0[STEPS], span[STEPS];
+    uint32_t xs[STEPS];
+    int ymin = TY, ymax = 0;
+#pragma unroll
+    for (int k = 0; k < STEPS; ++k) {
+      const bool valid = lo + k * 64 + lane < hi;
+      y0[k] = (int)(rc[k].x >> 16);
+      const int y1 = (int)(rc[k].y >> 16);
+      span[k] = valid ? y1 - y0[k] : 0;
+      xs[k] = (rc[k].x & 0xFFFF) | (rc[k].y << 16);
+      if (valid && y1 > y0[k]) {
+        ymin = min(ymin, y0[k]);
+        ymax = max(ymax, y1);
       }
     }
+    ymin = __builtin_amdgcn_readfirstlane(wave_min_i(ymin));
+    ymax = __builtin_amdgcn_readfirstlane(wave_max_i(ymax));
+    uint32_t* cw = curs[wave];
+    for (int y = ymin + lane; y < ymax; y += 64)
+      cw[y] = st.row_rg[(size_t)v * TY + y].x + w.counts[(size_t)b * TY + y];
+    __builtin_amdgcn_wave_barrier();
+    // row by row: a ballot per 64 pairs; the row's stores of the chunk are
+    // issued back to back onto consecutive entries.  They stay inside the row's
+    // range: the counts used the same y0 <= y < y1 rule, and an overflowing
+    // row level returned above.
+#pragma unroll 1
+    for (int y = ymin; y < ymax; ++y) {
+      uint32_t c = (uint32_t)__builtin_amdgcn_readfirstlane((int)cw[y]);
+#pragma unroll
+      for (int k = 0; k < STEPS; ++k) {
+        if (k < nsteps) {
+          const bool cov = (unsigned)(y - y0[k]) < (unsigned)span[k];
+          const unsigned long long m = __ballot(cov);
+          if (cov) {
+            const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
+                (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            st.rows[c + rank] = make_uint2(pid[k], xs[k]);
+          }
+          c += (uint32_t)__popcll(m);
+        }
+      }
+    }
+    __builtin_amdgcn_wave_barrier();  // the next chunk reuses the cursors
   }
 }
 
 hipError_t launch_binning(const BinTab& t, StateDev st, const BinWork& w, hipStream_t s) {
   const int nc = t.cblk_off[t.nv];
   const int nrows = t.nv * t.TY;
-  const int nparts = (nc + RC_SUB - 1) / RC_SUB;
+  const int nparts = vis_grid((nc + RC_SUB - 1) / RC_SUB);  // counting workgroups
   if (nc > 0)
-    hipLaunchKernelGGL(k_row_count, dim3(xcd_grid(nparts)), dim3(256), 0, s, t, st, w);
+    hipLaunchKernelGGL(k_row_count, dim3(nparts), dim3(256), 0, s, t, st, w);
   hipLaunchKernelGGL(k_colscan, dim3((nrows + CS_COLS - 1) / CS_COLS), dim3(CS_COLS * CS_SEGS),
                      0, s, t, st.hdr, t.TY, w.counts, w.row_tot);
   const int nb = std::max(1, (nrows + RS_TILE - 1) / RS_TILE);
@@ -301,7 +313,7 @@ hipError_t launch_binning(const BinTab& t, StateDev st, const BinWork& w, hipStr
                      st.cap, &st.hdr->row_total, &st.hdr->overflow, nparts, w.area_part,
                      &st.hdr->inst_total);
   if (nc > 0)
-    hipLaunchKernelGGL(k_row_scatter, dim3(xcd_grid((nc + 3) / 4)), dim3(256), 0, s, t, st, w);
+    hipLaunchKernelGGL(k_row_scatter, dim3(vis_grid((nc + 3) / 4)), dim3(256), 0, s, t, st, w);
   return hipGetLastError();
 }
 

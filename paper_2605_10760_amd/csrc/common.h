@@ -57,13 +57,20 @@ __device__ __forceinline__ int find_seg(const int* off, int n, int b) {
   return lo;
 }
 
+// Inclusive prefix sum over the wave (every lane active): row shifts by 1, 2, 4
+// and 8, then the last lane of each row to the next row and of each half to
+// the next half; a lane without a source adds 0.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint32_t dpp_add_u(uint32_t x) {
+  return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROW_MASK, 0xF, false);
+}
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    uint32_t y = __shfl_up(x, d, 64);
-    if (lane_id() >= d) x += y;
-  }
-  return x;
+  x = dpp_add_u<0x111, 0xF>(x);
+  x = dpp_add_u<0x112, 0xF>(x);
+  x = dpp_add_u<0x114, 0xF>(x);
+  x = dpp_add_u<0x118, 0xF>(x);
+  x = dpp_add_u<0x142, 0xA>(x);
+  return dpp_add_u<0x143, 0xC>(x);
 }
 
 __device__ __forceinline__ float wave_sum(float x) {
@@ -240,4 +247,42 @@ __device__ __forceinline__ unsigned long long wg_sum_before(const uint32_t* x, i
   return tot;
 }
 
+// The blocks of `tile` visible pairs that the views have, view-major.  How many
+// there are is known to the device alone, so a kernel over them has a grid of at
+// most VIS_GRID workgroups (the host's bound on their number, if smaller) that
+// walk them: a workgroup per block of the bound, most of them without a pair,
+// cost 80 us a kernel where 48 views saw 28M of 144M pairs (12.0 -> 11.15 ms a
+// pass in the four binning and eight sort kernels; 400k in 8 views 978 -> 930 us, one
+// view of 300k 372 -> 360).  An XCD takes a
+// contiguous eighth of the blocks.  Every lane of the wave must be active.
+struct VisBlocks {
+  int lo, hi;   // lane v: the view's visible pairs
+  int incl;     //   blocks of views 0..v
+  int n, step;  // blocks; a workgroup's stride
+  int i, end;   // the workgroup's next item, its XCD's end
+  // items of `per_wg` blocks; an XCD takes at least `least` of them
+  __device__ __forceinline__ VisBlocks(const StateHeader* hdr, int nv, int tile, int per_wg,
+                                       int least = 1) {
+    const int l = lane_id();
+    lo = hi = 0;
+    if (l < nv) {
+      lo = (int)hdr->vis_off[l];
+      hi = (int)hdr->vis_off[l + 1];
+    }
+    incl = (int)wave_incl_scan((uint32_t)(hi - lo + tile - 1) / (uint32_t)tile);
+    n = __builtin_amdgcn_readlane(incl, 63);
+    const int items = (n + per_wg - 1) / per_wg, x = (int)blockIdx.x & 7;
+    step = (int)gridDim.x / 8;
+    const int per = max((items + 7) / 8, min(least, step));
+    i = x * per + ((int)blockIdx.x >> 3);
+    end = min(items, (x + 1) * per);
+  }
+  // block b < n (uniform): its view, its number in the view, the view's pairs
+  __device__ __forceinline__ void locate(int b, int& v, int& lb, int& first, int& last) const {
+    v = (int)__builtin_ctzll(__ballot(incl > b));
+    lb = b - (v ? __builtin_amdgcn_readlane(incl, v - 1) : 0);
+    first = __builtin_amdgcn_readlane(lo, v);
+    last = __builtin_amdgcn_readlane(hi, v);
+  }
+};
 }  // namespace gsr

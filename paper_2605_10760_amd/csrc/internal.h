@@ -24,6 +24,11 @@ constexpr int GRAD2D = 10;        // u, v, A, B, C, sigma, r, g, b, z
 constexpr uint32_t CULLED = 0xFFFFFFFFu;
 constexpr int MAX_ROWS = 512;     // tile rows per view (binning LDS arrays)
 constexpr int MAX_COLS = 512;     // tile columns per view
+constexpr int VIS_GRID = 8192;   // most workgroups of a kernel over visible pairs
+// The grid of such a kernel whose items are at most `bound`: a multiple of 8.
+inline int vis_grid(size_t bound) {
+  return (int)((bound < (size_t)VIS_GRID ? bound : (size_t)VIS_GRID) + 7) / 8 * 8;
+}
 constexpr int MAX_CHUNK = 256;   // depth-sorted pairs per row-binning chunk
 constexpr int RC_SUB = 4;        // row-binning chunks per counting workgroup
 constexpr int SCHED_WORDS = 2 + 2 * 33;  // tile cursors + length-bucket counts (render.hip)
@@ -142,7 +147,7 @@ struct BinWork {
   uint32_t* row_tot;    // [V*TY] entries per (view, row)
   uint32_t* rect_lo;    // [P] the rects in depth order (rect.x and rect.y), in sort
   uint32_t* rect_hi;    //   buffers that the depth sort has done with
-  uint32_t* area_part;  // [chunks / RC_SUB + 1] (pair, tile) copies per counting workgroup
+  unsigned long long* area_part;  // [<= VIS_GRID] (pair, tile) copies per counting workgroup
 };
 
 // Sim(3) corrections: Gaussian set offsets, and the set of every view.

@@ -21,61 +21,71 @@
 
 namespace gsr {
 
-__device__ __forceinline__ void sort_block_range(const SortTab& t, const StateHeader* hdr,
-                                                 int b, int& v, int& lo, int& hi) {
-  v = find_seg(t.sblk_off, t.nv, b);
-  const int lb = b - t.sblk_off[v];
-  const int seg_lo = (int)hdr->vis_off[v], seg_hi = (int)hdr->vis_off[v + 1];
-  lo = seg_lo + lb * SORT_TILE;
-  hi = min(seg_hi, lo + SORT_TILE);
-}
+// Blocks that an XCD takes at least: a small view's passes are faster on a few
+// XCDs, whose L2s hold what the pass before wrote, than spread over all (one view
+// of 1M pairs, about 70 blocks visible: 220 us a pass spread, 210 so).
+constexpr int XCD_BLOCKS = 16;
+
+// View, its keys [seg, end), number in the counts and keys [lo, hi) of visible
+// block i.
+struct SortBlock {
+  int v, seg, end, lb, b, lo, hi;
+  __device__ __forceinline__ SortBlock(const SortTab& t, const VisBlocks& blocks) {
+    blocks.locate(blocks.i, v, lb, seg, end);
+    b = t.sblk_off[v] + lb;
+    lo = seg + lb * SORT_TILE;
+    hi = min(end, lo + SORT_TILE);
+  }
+};
 
 template <int SH>
 __global__ __launch_bounds__(SORT_THREADS) void k_radix_hist(SortTab t, const StateHeader* hdr,
                                                              const uint32_t* keys,
                                                              uint32_t* hist) {
   __shared__ uint32_t cnt[RADIX];
-  const int b = xcd_remap(blockIdx.x, t.sblk_off[t.nv]);
-  if (b < 0) return;
-  int v, lo, hi;
-  sort_block_range(t, hdr, b, v, lo, hi);
-  cnt[threadIdx.x] = 0;
-  __syncthreads();
-  uint32_t d[SORT_ITEMS];
+  VisBlocks blocks(hdr, t.nv, SORT_TILE, 1, XCD_BLOCKS);
+  for (; blocks.i < blocks.end; blocks.i += blocks.step) {
+    const SortBlock sb(t, blocks);
+    const int b = sb.b, lo = sb.lo, hi = sb.hi;
+    cnt[threadIdx.x] = 0;
+    __syncthreads();
+    uint32_t d[SORT_ITEMS];
 #pragma unroll
-  for (int r = 0; r < SORT_ITEMS; ++r) {
-    const int i = lo + r * SORT_THREADS + (int)threadIdx.x;
-    d[r] = i < hi ? (keys[i] >> SH) & (RADIX - 1) : RADIX;
-  }
-#pragma unroll
-  for (int r = 0; r < SORT_ITEMS; ++r) {
-    const bool valid = d[r] < (uint32_t)RADIX;
-    const unsigned long long act = __ballot(valid);
-    if (act == 0ull) continue;  // uniform
-    // the first valid lane's digit; a wave whose keys all share it adds them
-    // with one atomic
-    const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d[r], (int)__builtin_ctzll(act));
-    if (__ballot(valid && d[r] == d0) == act) {
-      if (lane_id() == (int)__builtin_ctzll(act)) atomicAdd(&cnt[d0], (uint32_t)__popcll(act));
-    } else if (SH >= 24) {
-      // the top digit takes few values: the lanes sharing a digit (found by
-      // a ballot per digit bit) add their count with one atomic from the
-      // lowest of them
-      unsigned long long peers = act;
-#pragma unroll
-      for (int bit = 0; bit < RADIX_BITS; ++bit) {
-        const bool on = (d[r] >> bit) & 1u;
-        const unsigned long long bb = __ballot(on);
-        peers &= on ? bb : ~bb;
-      }
-      const unsigned long long lt = (1ull << lane_id()) - 1ull;
-      if (valid && (peers & lt) == 0ull) atomicAdd(&cnt[d[r]], (uint32_t)__popcll(peers));
-    } else if (valid) {
-      atomicAdd(&cnt[d[r]], 1u);
+    for (int r = 0; r < SORT_ITEMS; ++r) {
+      const int i = lo + r * SORT_THREADS + (int)threadIdx.x;
+      d[r] = i < hi ? (keys[i] >> SH) & (RADIX - 1) : RADIX;
     }
+#pragma unroll
+    for (int r = 0; r < SORT_ITEMS; ++r) {
+      const bool valid = d[r] < (uint32_t)RADIX;
+      const unsigned long long act = __ballot(valid);
+      if (act == 0ull) continue;  // uniform
+      // the first valid lane's digit; a wave whose keys all share it adds them
+      // with one atomic
+      const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d[r], (int)__builtin_ctzll(act));
+      if (__ballot(valid && d[r] == d0) == act) {
+        if (lane_id() == (int)__builtin_ctzll(act)) atomicAdd(&cnt[d0], (uint32_t)__popcll(act));
+      } else if (SH >= 24) {
+        // the top digit takes few values: the lanes sharing a digit (found by
+        // a ballot per digit bit) add their count with one atomic from the
+        // lowest of them
+        unsigned long long peers = act;
+#pragma unroll
+        for (int bit = 0; bit < RADIX_BITS; ++bit) {
+          const bool on = (d[r] >> bit) & 1u;
+          const unsigned long long bb = __ballot(on);
+          peers &= on ? bb : ~bb;
+        }
+        const unsigned long long lt = (1ull << lane_id()) - 1ull;
+        if (valid && (peers & lt) == 0ull) atomicAdd(&cnt[d[r]], (uint32_t)__popcll(peers));
+      } else if (valid) {
+        atomicAdd(&cnt[d[r]], 1u);
+      }
+    }
+    __syncthreads();
+    hist[(size_t)b * RADIX + threadIdx.x] = cnt[threadIdx.x];  // the next block clears what the
+                                                               // thread has read
   }
-  __syncthreads();
-  hist[(size_t)b * RADIX + threadIdx.x] = cnt[threadIdx.x];
 }
 
 // One workgroup per view; thread (q, d) owns digit d over the q-th quarter
@@ -159,103 +169,104 @@ __global__ __launch_bounds__(SORT_THREADS) void k_radix_scatter(
   __shared__ uint32_t goff[RADIX];   // output position of the block's first key of each digit
   __shared__ uint32_t lk[SORT_TILE], lv[SORT_TILE];
   __shared__ unsigned long long sh[NW + 1];
-  const int b = xcd_remap(blockIdx.x, t.sblk_off[t.nv]);
-  if (b < 0) return;
-  int v, lo, hi;
-  sort_block_range(t, hdr, b, v, lo, hi);
-  if (lo >= hi) return;
-  const int tid = threadIdx.x, w = tid >> 6, lane = lane_id();
-  const int n = hi - lo;
-  // the block's digit counts (from the histogram pass) and global bases
+  VisBlocks blocks(hdr, t.nv, SORT_TILE, 1, XCD_BLOCKS);
+  for (; blocks.i < blocks.end; blocks.i += blocks.step) {
+    const SortBlock sb(t, blocks);
+    const int v = sb.v, b = sb.b, lo = sb.lo, hi = sb.hi;
+    const int tid = threadIdx.x, w = tid >> 6, lane = lane_id();
+    const int n = hi - lo;
+    // the block's digit counts (from the histogram pass) and global bases
 #pragma unroll
-  for (int i = 0; i < NW; ++i) whist[i][tid] = 0;
-  uint32_t key[SORT_ITEMS], val[SORT_ITEMS];
+    for (int i = 0; i < NW; ++i) whist[i][tid] = 0;
+    uint32_t key[SORT_ITEMS], val[SORT_ITEMS];
 #pragma unroll
-  for (int r = 0; r < SORT_ITEMS; ++r) {
-    const int i = r * SORT_THREADS + tid;
-    key[r] = i < n ? kin[lo + i] : 0u;
-    // the first pass's values are the keys' own positions
-    val[r] = i < n ? (VAL_INDEX ? (uint32_t)(lo + i) : vin[lo + i]) : 0u;
-  }
-  {
-    unsigned long long tot;
-    const uint32_t c = hist[(size_t)b * RADIX + tid];
-    const uint32_t o = (uint32_t)wg_excl_scan<SORT_THREADS>(c, sh, &tot);
-    loff[tid] = o;
-    if (FOLD) {
-      // thread d: digit d's count over the view's blocks and over those before
-      // this one
-      const int seg = (int)hdr->vis_off[v], nb = ((int)hdr->vis_off[v + 1] - seg + SORT_TILE - 1) / SORT_TILE;
-      const int lb = (lo - seg) / SORT_TILE;
-      const uint32_t* h = hist + (size_t)t.sblk_off[v] * RADIX + tid;
-      uint32_t before = 0, all = 0;
-      int k = 0;
-      for (; k + 16 <= nb; k += 16) {
-        uint32_t x[16];
+    for (int r = 0; r < SORT_ITEMS; ++r) {
+      const int i = r * SORT_THREADS + tid;
+      key[r] = i < n ? kin[lo + i] : 0u;
+      // the first pass's values are the keys' own positions
+      val[r] = i < n ? (VAL_INDEX ? (uint32_t)(lo + i) : vin[lo + i]) : 0u;
+    }
+    {
+      unsigned long long tot;
+      const uint32_t c = hist[(size_t)b * RADIX + tid];
+      const uint32_t o = (uint32_t)wg_excl_scan<SORT_THREADS>(c, sh, &tot);
+      loff[tid] = o;
+      if (FOLD) {
+        // thread d: digit d's count over the view's blocks and over those before
+        // this one
+        const int seg = sb.seg, nb = (sb.end - seg + SORT_TILE - 1) / SORT_TILE;
+        const int lb = sb.lb;
+        const uint32_t* h = hist + (size_t)t.sblk_off[v] * RADIX + tid;
+        uint32_t before = 0, all = 0;
+        int k = 0;
+        for (; k + 16 <= nb; k += 16) {
+          uint32_t x[16];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) x[j] = h[(size_t)(k + j) * RADIX];
+          for (int j = 0; j < 16; ++j) x[j] = h[(size_t)(k + j) * RADIX];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          all += x[j];
-          before += k + j < lb ? x[j] : 0u;
+          for (int j = 0; j < 16; ++j) {
+            all += x[j];
+            before += k + j < lb ? x[j] : 0u;
+          }
         }
+        for (; k < nb; ++k) {
+          const uint32_t x = h[(size_t)k * RADIX];
+          all += x;
+          before += k < lb ? x : 0u;
+        }
+        __syncthreads();
+        goff[tid] = (uint32_t)seg + (uint32_t)wg_excl_scan<SORT_THREADS>(all, sh, &tot) + before;
+      } else {
+        goff[tid] = off[(size_t)b * RADIX + tid];
       }
-      for (; k < nb; ++k) {
-        const uint32_t x = h[(size_t)k * RADIX];
-        all += x;
-        before += k < lb ? x : 0u;
+      cnt[tid] = 0;
+    }
+    __syncthreads();
+    const unsigned long long lt = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int r = 0; r < SORT_ITEMS; ++r) {
+      if (r * SORT_THREADS >= n) break;  // uniform
+      const bool valid = r * SORT_THREADS + tid < n;
+      const uint32_t d = (key[r] >> SH) & (RADIX - 1);
+      unsigned long long peers = __ballot(valid);
+#pragma unroll
+      for (int bit = 0; bit < RADIX_BITS; ++bit) {
+        const bool on = (d >> bit) & 1u;
+        const unsigned long long bb = __ballot(on);
+        peers &= on ? bb : ~bb;
+      }
+      const int rank = __popcll(peers & lt);
+      if (valid && rank == 0) whist[w][d] = (uint32_t)__popcll(peers);
+      __syncthreads();
+      if (valid) {
+        uint32_t slot = loff[d] + cnt[d] + (uint32_t)rank;
+        for (int j = 0; j < w; ++j) slot += whist[j][d];
+        lk[slot] = key[r];
+        lv[slot] = val[r];
       }
       __syncthreads();
-      goff[tid] = (uint32_t)seg + (uint32_t)wg_excl_scan<SORT_THREADS>(all, sh, &tot) + before;
-    } else {
-      goff[tid] = off[(size_t)b * RADIX + tid];
-    }
-    cnt[tid] = 0;
-  }
-  __syncthreads();
-  const unsigned long long lt = (1ull << lane) - 1ull;
+      uint32_t add = 0;
 #pragma unroll
-  for (int r = 0; r < SORT_ITEMS; ++r) {
-    if (r * SORT_THREADS >= n) break;  // uniform
-    const bool valid = r * SORT_THREADS + tid < n;
-    const uint32_t d = (key[r] >> SH) & (RADIX - 1);
-    unsigned long long peers = __ballot(valid);
+      for (int j = 0; j < NW; ++j) {
+        add += whist[j][tid];
+        whist[j][tid] = 0;
+      }
+      cnt[tid] += add;
+      __syncthreads();
+    }
+    // slot e holds a key of digit d: its output position is goff[d] + e - loff[d]
 #pragma unroll
-    for (int bit = 0; bit < RADIX_BITS; ++bit) {
-      const bool on = (d >> bit) & 1u;
-      const unsigned long long bb = __ballot(on);
-      peers &= on ? bb : ~bb;
+    for (int r = 0; r < SORT_ITEMS; ++r) {
+      const int e = r * SORT_THREADS + tid;
+      if (e < n) {
+        const uint32_t k = lk[e];
+        const uint32_t d = (k >> SH) & (RADIX - 1);
+        const uint32_t pos = goff[d] + (uint32_t)e - loff[d];
+        if (KEYS_OUT) kout[pos] = k;
+        vout[pos] = lv[e];
+      }
     }
-    const int rank = __popcll(peers & lt);
-    if (valid && rank == 0) whist[w][d] = (uint32_t)__popcll(peers);
-    __syncthreads();
-    if (valid) {
-      uint32_t slot = loff[d] + cnt[d] + (uint32_t)rank;
-      for (int j = 0; j < w; ++j) slot += whist[j][d];
-      lk[slot] = key[r];
-      lv[slot] = val[r];
-    }
-    __syncthreads();
-    uint32_t add = 0;
-#pragma unroll
-    for (int j = 0; j < NW; ++j) {
-      add += whist[j][tid];
-      whist[j][tid] = 0;
-    }
-    cnt[tid] += add;
-    __syncthreads();
-  }
-  // slot e holds a key of digit d: its output position is goff[d] + e - loff[d]
-#pragma unroll
-  for (int r = 0; r < SORT_ITEMS; ++r) {
-    const int e = r * SORT_THREADS + tid;
-    if (e < n) {
-      const uint32_t k = lk[e];
-      const uint32_t d = (k >> SH) & (RADIX - 1);
-      const uint32_t pos = goff[d] + (uint32_t)e - loff[d];
-      if (KEYS_OUT) kout[pos] = k;
-      vout[pos] = lv[e];
-    }
+    __syncthreads();  // the next block reuses the LDS
   }
 }
 
@@ -264,7 +275,7 @@ __global__ __launch_bounds__(SORT_THREADS) void k_radix_scatter(
 template <bool FOLD>
 static void sort_passes(const SortTab& t, const StateDev& st, uint32_t* ka, uint32_t* va,
                         uint32_t* kb, uint32_t* vb, uint32_t* hist, uint32_t* off, hipStream_t s) {
-  const dim3 g(xcd_grid(t.sblk_off[t.nv])), blk(SORT_THREADS), sg(t.nv), sb(RADIX * SCAN_Q);
+  const dim3 g(vis_grid(t.sblk_off[t.nv])), blk(SORT_THREADS), sg(t.nv), sb(RADIX * SCAN_Q);
   const uint32_t* none = nullptr;
   const auto scan = [&] {
     if (!FOLD) hipLaunchKernelGGL(k_radix_scan, sg, sb, 0, s, t, st.hdr, hist, off);

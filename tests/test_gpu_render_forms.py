@@ -131,3 +131,36 @@ def test_key_pass_with_and_without_queue(n, n_views):
         np.testing.assert_array_equal(dbg["rects"][k * n:(k + 1) * n], ek["rects"])
         seen += int(ek["vis_off"][1])
     assert 0.03 * n * n_views < seen < 0.9 * n * n_views
+
+
+# views that see none, one or thousands of the pairs, blocks that end on a view's
+# last pair, more blocks than the kernels over visible pairs have workgroups
+@pytest.mark.parametrize("n,n_views,chunk", [(2048, 9, 64), (2049, 64, 0), (65537, 33, 64)])
+def test_blocks_of_visible_pairs(n, n_views, chunk):
+    """Views that see everything, some or nothing, in one call and one call each:
+    the same depth order and per-tile lists."""
+    from paper_2605_10760_amd import Rasterizer, SceneTensors, ViewTensors
+    announce(f"visible blocks {n} {n_views}")
+    W, H = 64, 48
+    scene, views = _case(n, n_views, W, H)
+    # in front of every third view lies the whole scene, behind every other third
+    # nothing: the camera is moved out of the room, looking in or away
+    for k in range(n_views):
+        if k % 3 != 1:
+            views.viewmats[k, :, :3] = np.diag([1.0, 1.0, 1.0 if k % 3 == 0 else -1.0])
+            views.viewmats[k, :, 3] = (0.0, 0.0, 12.0 if k % 3 == 0 else -12.0)
+    scene.opacity_logits[:] = np.maximum(scene.opacity_logits, -1.0)
+    st, vt = SceneTensors.from_numpy(scene), ViewTensors.from_numpy(views)
+    big = Rasterizer(W, H, n_views * n, n_views, chunk=chunk)
+    c, *_, state = big.forward(st, vt)
+    dbg = big.debug_export(state, n_views, n_views * n, 0)
+    one = Rasterizer(W, H, n, 1, chunk=chunk)
+    for k in (0, 1, 2, 4, 5, n_views - 1):
+        ck, *_, sk = one.forward(st, vt.select([k]))
+        ek = one.debug_export(sk, 1, n, 0)
+        lo, hi = int(dbg["vis_off"][k]), int(dbg["vis_off"][k + 1])
+        assert hi - lo == int(ek["vis_off"][1])
+        assert hi - lo == (n if k % 3 == 0 else hi - lo if k % 3 == 1 else 0)
+        np.testing.assert_array_equal(dbg["order"][lo:hi].astype(np.int64) - k * n,
+                                      ek["order"].astype(np.int64))
+        np.testing.assert_array_equal(c[k].cpu().numpy(), ck[0].cpu().numpy())
