@@ -35,18 +35,6 @@ __device__ __forceinline__ int xcd_remap_mixed(int b, int n) {
   return l < n ? l : -1;
 }
 
-// Visible position of the lane's pair in block b of a view (StateDev::vmask),
-// CULLED if it is culled; w: the wave of the block (uniform).
-__device__ __forceinline__ uint32_t visible_row(const StateDev& st, size_t b, int w) {
-  const unsigned long long* m = st.vmask + 4 * b;
-  uint32_t row = st.vbase[b];
-  for (int k = 0; k < w; ++k) row += (uint32_t)__popcll(m[k]);
-  const unsigned long long mk = m[w];
-  row += __builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32),
-                                   __builtin_amdgcn_mbcnt_lo((uint32_t)mk, 0u));
-  return ((mk >> (threadIdx.x & 63)) & 1ull) ? row : CULLED;
-}
-
 // Index s with off[s] <= b < off[s+1] for a non-decreasing off[0..n].
 __device__ __forceinline__ int find_seg(const int* off, int n, int b) {
   int lo = 0, hi = n;

@@ -12,7 +12,7 @@
 // 461 us on 144M).  Record pass: for visible pairs, the depth key and the rect
 // again and the screen-space record in FP64 rounded once to FP32 (the 2D
 // conic of an elongated splat loses digits to cancellation in FP32), one pair
-// per lane from a per-wave queue of the wave's visible pairs.  The parameters are
+// per lane from the workgroup's visible pairs.  The parameters are
 // read once per Gaussian in each pass (coalesced AoS rows); the record pass
 // writes one 48-byte record and one 8-byte rect per visible pair.
 #include <algorithm>
@@ -342,37 +342,57 @@ __global__ __launch_bounds__(PROJ_BLOCK) void k_project(ProjTab t, SceneDev sc, 
 // visible list, so that a view's records are consecutive lines (written in
 // full, read densely by the binning and compositing).
 //
-// One wave per 64 Gaussians of a set.  Each lane loads its Gaussian once and
-// puts the view-independent quantities (mean, FP32 key covariance and
+// One workgroup per 256 Gaussians of a set.  Each thread loads its Gaussian once
+// and puts the view-independent quantities (mean, FP32 key covariance and
 // threshold, FP64 covariance, opacity, threshold of the record extents,
-// degree-0 colour) in the wave's LDS slot.  The wave then walks the set's
-// views, appending its visible pairs (lane, view) to a queue in LDS, and
-// computes records 64 at a time from the queue, one pair per lane, so that
-// no lane idles on a culled pair.
-constexpr int RQ = 128;  // queue slots per wave (at most 63 + 64 held)
-struct RecSlot {
-  float m[3][64];
-  float S[6][64];      // FP32 key-path covariance
-  float k2[64];        // key-path 2 ln(255 sigma), negative: not renderable
-  double Sd[6][64];    // FP64 covariance (00, 01, 02, 11, 12, 22)
-  float sig[64], k2f[64];
-  float col[3][64];
-  uint32_t row[RQ];
-  uint16_t item[RQ];   // lane | view of the set << 6
+// degree-0 colour) in LDS.  The workgroup's visible pairs, view by view, are
+// then taken 256 at a time, one per thread, so that no lane idles on a culled
+// pair: pair i's view is found in the prefix of the views' counts, its Gaussian
+// is the (i - prefix)-th visible one of the block.  Consecutive threads write
+// consecutive rows of a view, all that the workgroup has: a queue per wave
+// wrote the lines that waves share in parts, at different times (48 views of
+// keyframes 212 -> 180 us, one view of 1M Gaussians of degree 3 39 -> 29, 8 views of
+// 400k 57 -> 47, 48 views of 3M 1715 -> 1646: there the coefficients, 192 bytes a
+// pair out of line, take as long as the records; 64 KB of them in LDS left two waves
+// a SIMD and took longer).
+struct RecBlock {
+  float m[3][PROJ_BLOCK];
+  float S[6][PROJ_BLOCK];   // FP32 key-path covariance
+  float k2[PROJ_BLOCK];     // key-path 2 ln(255 sigma), negative: not renderable
+  double Sd[6][PROJ_BLOCK]; // FP64 covariance (00, 01, 02, 11, 12, 22)
+  float sig[PROJ_BLOCK], k2f[PROJ_BLOCK];
+  float col[3][PROJ_BLOCK];
 };
-// The views of the workgroup's set: ids and guard limits.
+// The views of the workgroup's set: ids, guard limits, visible bits, the pairs
+// before them and the position of the first.
 struct RecViews {
   double dx[MAXV], dy[MAXV];
   float lx[MAXV], ly[MAXV];
+  unsigned long long mask[MAXV][4];
+  uint32_t base[MAXV];
+  uint16_t first[MAXV + 1];
   uint16_t id[MAXV];
 };
+
+// The position of set bit n of m (n below their number).
+__device__ __forceinline__ int nth_bit(unsigned long long m, int n) {
+  int pos = 0;
+#pragma unroll
+  for (int w = 32; w >= 1; w >>= 1) {
+    const int c = __popc((uint32_t)(m >> pos) & (w == 32 ? 0xFFFFFFFFu : (1u << w) - 1u));
+    const bool up = n >= c;
+    n -= up ? c : 0;
+    pos += up ? w : 0;
+  }
+  return pos;
+}
 
 template <int SHD>
 __device__ __forceinline__ void record_one(const ProjTab& t, const SceneDev& sc,
                                            const CamDev& cam, const StateDev& st,
-                                           const RecSlot& L, const RecViews& RV, long g0,
-                                           uint32_t item, uint32_t row) {
-  const int l = (int)(item & 63u), k = (int)(item >> 6), v = RV.id[k];
+                                           const RecBlock& L, const RecViews& RV, long g0,
+                                           int l, int k, uint32_t row) {
+  const int v = RV.id[k];
   const float m[3] = {L.m[0][l], L.m[1][l], L.m[2][l]};
   KeyGauss kg;
   kg.S00 = L.S[0][l]; kg.S01 = L.S[1][l]; kg.S02 = L.S[2][l];
@@ -440,19 +460,18 @@ __device__ __forceinline__ void record_one(const ProjTab& t, const SceneDev& sc,
 template <int SHD>
 __global__ __launch_bounds__(PROJ_BLOCK) void k_records(ProjTab t, SceneDev sc, CamDev cam,
                                                         StateDev st) {
-  __shared__ RecSlot slots[PROJ_BLOCK / 64];
+  __shared__ RecBlock L;
   __shared__ RecViews RV;
   const int b = xcd_remap(blockIdx.x, t.set_gblk[t.ns]);
   if (b < 0) return;
   const int s = find_seg(t.set_gblk, t.ns, b);
   const int lb = b - t.set_gblk[s];
-  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int lane = threadIdx.x & 63;
-  RecSlot& L = slots[wv];
+  const int lane = threadIdx.x;
+  const int v0 = t.set_voff[s], nv = t.set_voff[s + 1] - v0;
   const int local = lb * PROJ_BLOCK + (int)threadIdx.x;
   const bool valid = local < t.set_goff[s + 1] - t.set_goff[s];
   const long gi = (long)t.set_goff[s] + (valid ? local : 0);
-  const long g0 = (long)t.set_goff[s] + lb * PROJ_BLOCK + 64 * wv;  // the wave's lane-0 Gaussian
+  const long g0 = (long)t.set_goff[s] + lb * PROJ_BLOCK;  // the first Gaussian
   {
     float m[3] = {0.f, 0.f, 0.f}, ls[3] = {0.f, 0.f, 0.f}, q[4] = {1.f, 0.f, 0.f, 0.f}, o = 0.f;
     if (valid) {
@@ -490,41 +509,49 @@ __global__ __launch_bounds__(PROJ_BLOCK) void k_records(ProjTab t, SceneDev sc, 
     }
     L.col[0][lane] = col[0]; L.col[1][lane] = col[1]; L.col[2][lane] = col[2];
   }
-  if ((int)threadIdx.x < t.set_voff[s + 1] - t.set_voff[s]) {
-    const int v = t.vset[t.set_voff[s] + (int)threadIdx.x];
-    const ViewLim lm = view_lim(cam.intrinsics[4 * v], cam.intrinsics[4 * v + 1], t.W, t.H);
-    RV.dx[threadIdx.x] = lm.dx;
-    RV.dy[threadIdx.x] = lm.dy;
-    RV.lx[threadIdx.x] = lm.lx;
-    RV.ly[threadIdx.x] = lm.ly;
-    RV.id[threadIdx.x] = (uint16_t)v;
+  if (threadIdx.x < 64) {  // MAXV views, one per lane of the first wave
+    uint32_t c = 0;
+    if (lane < nv) {
+      const int v = t.vset[v0 + lane];
+      const ViewLim lm = view_lim(cam.intrinsics[4 * v], cam.intrinsics[4 * v + 1], t.W, t.H);
+      RV.dx[lane] = lm.dx;
+      RV.dy[lane] = lm.dy;
+      RV.lx[lane] = lm.lx;
+      RV.ly[lane] = lm.ly;
+      RV.id[lane] = (uint16_t)v;
+      const size_t bi = (size_t)(t.blk_off[v] + lb);
+      RV.base[lane] = st.vbase[bi];
+      for (int w = 0; w < 4; ++w) {
+        const unsigned long long mk = st.vmask[4 * bi + w];
+        RV.mask[lane][w] = mk;
+        c += (uint32_t)__popcll(mk);
+      }
+    }
+    const uint32_t incl = wave_incl_scan(c);
+    RV.first[lane + 1] = (uint16_t)incl;  // at most 64 x 256
+    if (lane == 0) RV.first[0] = 0;
   }
   __syncthreads();
-  uint32_t head = 0u, tail = 0u;
-  for (int vi = t.set_voff[s]; vi < t.set_voff[s + 1]; ++vi) {
-    const int v = t.vset[vi];
-    const uint32_t row = visible_row(st, (size_t)(t.blk_off[v] + lb), wv);
-    const bool vis = row != CULLED;
-    const unsigned long long mk = __ballot(vis);
-    if (vis) {
-      const uint32_t k = (tail + __builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32),
-                                                           __builtin_amdgcn_mbcnt_lo((uint32_t)mk, 0u))) &
-                         (RQ - 1);
-      L.item[k] = (uint16_t)(lane | ((vi - t.set_voff[s]) << 6));
-      L.row[k] = row;
+  const int n = RV.first[MAXV];
+  for (int i = threadIdx.x; i < n; i += PROJ_BLOCK) {
+    // the last view k with first[k] <= i: one that has the pair, since the
+    // views without one share their successor's
+    int k = 0;
+#pragma unroll
+    for (int d = MAXV / 2; d >= 1; d >>= 1) k += (int)RV.first[k + d] <= i ? d : 0;
+    int j = i - RV.first[k], w = 0;
+    unsigned long long mk = RV.mask[k][0];
+#pragma unroll
+    for (int q = 1; q < 4; ++q) {
+      const int c = __popcll(mk);
+      if (w == q - 1 && j >= c) {
+        j -= c;
+        w = q;
+        mk = RV.mask[k][q];
+      }
     }
-    tail += (uint32_t)__popcll(mk);
-    __builtin_amdgcn_wave_barrier();
-    if (tail - head >= 64u) {
-      const uint32_t k = (head + (uint32_t)lane) & (RQ - 1);
-      record_one<SHD>(t, sc, cam, st, L, RV, g0, L.item[k], L.row[k]);
-      head += 64u;
-      __builtin_amdgcn_wave_barrier();
-    }
-  }
-  if ((uint32_t)lane < tail - head) {
-    const uint32_t k = (head + (uint32_t)lane) & (RQ - 1);
-    record_one<SHD>(t, sc, cam, st, L, RV, g0, L.item[k], L.row[k]);
+    record_one<SHD>(t, sc, cam, st, L, RV, g0, 64 * w + nth_bit(mk, j), k,
+                    RV.base[k] + (uint32_t)(i - RV.first[k]));
   }
 }
 
