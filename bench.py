@@ -373,27 +373,27 @@ def algorithmic(cnt, sc_np, V, H, W, sh_stride, fwd_only_views=0):
     npx = V * H * W
     byt = {
         # key pass: the key path's parameters (means, log-scales, quaternion,
-        # opacity: 44 B) once per Gaussian, a depth key per pair
-        "project": 44 * sc_np.n + 4 * P,
-        # read the keys, write each pair's visible position and each visible
-        # pair's key
-        "compact": 4 * P + 4 * P + 4 * Pv,
-        # record pass: every parameter once per Gaussian, the visible position
-        # per pair, rect + record per visible pair
-        "record": par * sc_np.n + 4 * P + (48 + 8) * Pv,
+        # opacity: 44 B) once per Gaussian, a visible bit per pair
+        "project": 44 * sc_np.n + P // 8,
+        # a count read and a position written per 256 pairs
+        "compact": 8 * (P // 256),
+        # record pass: every parameter once per Gaussian, the visible bit per
+        # pair, depth key + rect + record per visible pair
+        "record": par * sc_np.n + P // 8 + (48 + 8 + 4) * Pv,
         # four 8-bit passes over the visible keys: the histogram reads the
         # keys, the scatter reads keys (and values, from the second pass on)
         # and writes values (and keys, except in the last pass)
         "depth_sort": (4 + 4 + 8) * Pv + 2 * (4 + 8 + 8) * Pv + (4 + 8 + 4) * Pv,
-        # rects and depth order read by the counting and scatter passes, the
+        # depth order and rects read by the counting pass, which leaves the
+        # rects in depth order, both read by the scatter pass, the
         # (pair, tile row) entries written; the tile lists are filtered from
         # them by the compositing kernels
-        "binning": 2 * 12 * Pv + 8 * cnt["row_entries"],
+        "binning": (12 + 8 + 12) * Pv + 8 * cnt["row_entries"],
         "render_fwd": 52 * cnt["E_fwd"] + 28 * npx,
         "render_bwd": 52 * cnt["E_bwd"] + 80 * cnt["E_bwd"] + 28 * npx,
         # parameters read and gradients written once per Gaussian, the visible
-        # position per pair, each visible pair's gradient row read and cleared
-        "project_bwd": 2 * par * sc_np.n + 4 * P + 80 * Pv,
+        # bit per pair, each visible pair's gradient row read and cleared
+        "project_bwd": 2 * par * sc_np.n + P // 8 + 80 * Pv,
     }
     ops = {
         "render_fwd": OPS_FWD_EXAMINED * cnt["examined"] + OPS_FWD_BLENDED * cnt["blended"],

@@ -23,7 +23,7 @@ struct gsr_ctx {
   void* ws = nullptr;
   size_t ws_bytes = 0;
   uint32_t* blk_cnt = nullptr;   // visible pairs per projection block
-  uint32_t *ka = nullptr, *va = nullptr, *kb = nullptr, *vb = nullptr;
+  uint32_t *ka = nullptr, *va = nullptr, *vb = nullptr;
   uint32_t* hist = nullptr;
   uint32_t* hoff = nullptr;
   BinWork bw{};
@@ -100,6 +100,7 @@ StateLayout state_layout(const gsr_plan_desc& p) {
   L.vmask = o; o = align256(o + nblk * 32);
   L.vbase = o; o = align256(o + nblk * 4);
   L.vkey = o; o = align256(o + P * 4);
+  L.skey = o; o = align256(o + P * 4);
   L.rect = o; o = align256(o + P * 8);
   L.rec = o; o = align256(o + P * 48);
   L.order = o; o = align256(o + P * 4);
@@ -120,6 +121,7 @@ StateDev state_ptrs(void* base, const gsr_plan_desc& p) {
   s.vmask = (unsigned long long*)(b + L.vmask);
   s.vbase = (uint32_t*)(b + L.vbase);
   s.vkey = (uint32_t*)(b + L.vkey);
+  s.skey = (uint32_t*)(b + L.skey);
   s.rect = (uint2*)(b + L.rect);
   s.rec = (float4*)(b + L.rec);
   s.order = (uint32_t*)(b + L.order);
@@ -408,7 +410,6 @@ gsr_status gsr_plan(gsr_ctx* c, const gsr_plan_desc* p) {
   const size_t o_blk = o; o = align256(o + c->max_blocks * 4);
   const size_t o_ka = o; o = align256(o + P * 4);
   const size_t o_va = o; o = align256(o + P * 4);
-  const size_t o_kb = o; o = align256(o + P * 4);
   const size_t o_vb = o; o = align256(o + P * 4);
   const size_t o_hist = o; o = align256(o + c->max_sblocks * RADIX * 4);
   const size_t o_hoff = o; o = align256(o + c->max_sblocks * RADIX * 4);
@@ -430,13 +431,12 @@ gsr_status gsr_plan(gsr_ctx* c, const gsr_plan_desc* p) {
   c->blk_cnt = (uint32_t*)(b + o_blk);
   c->ka = (uint32_t*)(b + o_ka);
   c->va = (uint32_t*)(b + o_va);
-  c->kb = (uint32_t*)(b + o_kb);
   c->vb = (uint32_t*)(b + o_vb);
   c->hist = (uint32_t*)(b + o_hist);
   c->hoff = (uint32_t*)(b + o_hoff);
   c->bw.counts = (uint32_t*)(b + o_cnt);
   c->bw.row_tot = (uint32_t*)(b + o_rt);
-  c->bw.rect_lo = c->ka;  // the last sort pass reads kb, vb
+  c->bw.rect_lo = c->ka;  // the last sort pass reads the others
   c->bw.rect_hi = c->va;
   c->bw.area_part = (unsigned long long*)(b + o_ap);
   c->grad2d = (float*)(b + o_g2);
@@ -493,7 +493,7 @@ gsr_status gsr_forward(gsr_ctx* c, const gsr_scene* sc, const gsr_views* vw,
   }
   {
     StageMark m(c, GSR_STAGE_DEPTH_SORT, st);
-    if ((e = launch_depth_sort(t.stb, sd, c->ka, c->va, c->kb, c->vb, c->hist, c->hoff, st)) != hipSuccess)
+    if ((e = launch_depth_sort(t.stb, sd, c->ka, c->va, sd.skey, c->vb, c->hist, c->hoff, st)) != hipSuccess)
       return hip_fail(c, e, "depth sort");
   }
   {

@@ -115,7 +115,7 @@ static_assert(sizeof(StateHeader) <= STATE_HEADER_BYTES, "header");
 
 // Byte offsets of the arrays inside a saved-state buffer (all 256-aligned).
 struct StateLayout {
-  size_t hdr, vmask, vbase, vkey, rect, rec, order, row_rg, rows, torder, tfinal, last, total;
+  size_t hdr, vmask, vbase, vkey, skey, rect, rec, order, row_rg, rows, torder, tfinal, last, total;
 };
 
 // Pointers into a saved-state buffer.
@@ -128,6 +128,7 @@ struct StateDev {
   unsigned long long* vmask;  // [4 blocks]
   uint32_t* vbase;    // [blocks]
   uint32_t* vkey;     // [Pv] by visible position: FP32 bits of camera z
+  uint32_t* skey;     // [Pv] scratch of the forward: keys of the depth sort's odd passes
   uint2* rect;        // [Pv] by visible position: packed (x0 | y0 << 16, x1 | y1 << 16)
   float4* rec;        // [Pv][3] by visible position: (u, v, A', B'), (C', sigma, z, ex),
                       //   (r, g, b, ey)

@@ -110,11 +110,10 @@ __device__ __forceinline__ void pair_bwd(const BwdView& w, const float* m, const
   const float gs = g10[5], gz = g10[9];
   float gc[3] = {g10[6], g10[7], g10[8]};
   // the forward's FP64 projection again (no read of the record): the conic (A,
-  // B, C) = (c, -b, a) / det, and the mean and covariance in the camera,
-  // rounded once
+  // B, C) = (c, -b, a) / det, and, rounded once, the mean and covariance in the
+  // camera
   const ScreenCov s2 = screen_cov_fp64(Sd, &w.Rc[0][0], w.tc, m, fx, fy, w.dx, w.dy);
   const double idet = 1.0 / (s2.a * s2.c - s2.b * s2.b);
-  const float A = (float)(s2.c * idet), B = (float)(-s2.b * idet), C = (float)(s2.a * idet);
   const float p[3] = {(float)s2.p[0], (float)s2.p[1], (float)s2.p[2]};
   float V[3][3];
   for (int i = 0; i < 3; ++i)
@@ -126,13 +125,18 @@ __device__ __forceinline__ void pair_bwd(const BwdView& w, const float* m, const
   const float ryc = iny ? ry : (ry < 0.f ? -w.ly : w.ly);
   const float j00 = fx * iz, j02 = -fx * rxc * iz, j11 = fy * iz, j12 = -fy * ryc * iz;
 
-  // conic -> 2D covariance:  G_S2 = -Q G_Q Q
-  const float hB = 0.5f * gB;
-  const float X00 = gA * A + hB * B, X01 = gA * B + hB * C;
-  const float X10 = hB * A + gC * B, X11 = hB * B + gC * C;
-  const float s00 = -(A * X00 + B * X10);
-  const float s01 = -0.5f * ((A * X01 + B * X11) + (B * X00 + C * X10));
-  const float s11 = -(B * X01 + C * X11);
+  // conic -> 2D covariance:  G_S2 = -Q G_Q Q, in FP64: the products of an
+  // elongated splat's conic cancel
+  float s00, s01, s11;
+  {
+    const double A = s2.c * idet, B = -s2.b * idet, C = s2.a * idet;
+    const double hB = 0.5 * gB;
+    const double X00 = gA * A + hB * B, X01 = gA * B + hB * C;
+    const double X10 = hB * A + gC * B, X11 = hB * B + gC * C;
+    s00 = (float)-(A * X00 + B * X10);
+    s01 = (float)(-0.5 * ((A * X01 + B * X11) + (B * X00 + C * X10)));
+    s11 = (float)-(B * X01 + C * X11);
+  }
   // 2D -> camera covariance (J^T G J) and Jacobian (2 G J V)
   float GV[3][3];
   GV[0][0] = j00 * j00 * s00;

@@ -723,7 +723,7 @@ __device__ __forceinline__ float wave_sum10(const float (&v)[10], int lane) {
 
 // An entry's ten sums over a region's pixels (t, at pitch RED) turned in place
 // into its screen-space gradients; (a, b) is its record, (x0, y0) the region's
-// first pixel centre.  With (DX, DY) the entry's offset from (x0, y0) and T0,
+// centre.  With (DX, DY) the entry's offset from (x0, y0) and T0,
 // TU, TV, TUU, TUV, TVV the sums of gp, gp u, gp v, gp u^2, gp u v, gp v^2:
 // sum gp dx = DX T0 - TU, sum gp dx^2 = DX (DX T0 - 2 TU) + TUU, sum gp dx dy =
 // DX (DY T0 - TV) - DY TU + TUV, and likewise for dy; d(power)/du = -(A dx + B
@@ -820,10 +820,12 @@ __device__ __forceinline__ void bwd_tile(int g, int W, int H, int TX, int TY,
     blast[k] = (uint32_t)__builtin_amdgcn_readfirstlane((int)m);
   }
   const int sidx = sum10_index(lane);  // the sum the lane ends with
-  // the lane's pixel offset within an 8x8 block
-  const float lxf = (float)(lane & 7), lyf = (float)(lane >> 3);
-  // the region's first pixel centre
-  const float x0r = (float)(tx0 * TW) + 0.5f, y0r = (float)(ty * TH) + 0.5f;
+  // the region's centre, and the offset from it of the lane's pixel in the
+  // region's first 8x8 block: moments about the centre lose less to
+  // cancellation when they are moved to the entry's mean than moments about
+  // a corner
+  const float x0r = (float)(tx0 * TW) + 0.5f * RW, y0r = (float)(ty * TH) + 0.5f * TH;
+  const float lxf = (float)(lane & 7) + 0.5f - 0.5f * RW, lyf = (float)(lane >> 3) + 0.5f - 0.5f * TH;
   uint32_t nwalk[CP], top[CP];
   bool any = false;
 #pragma unroll
@@ -972,7 +974,7 @@ __device__ __forceinline__ void bwd_tile(int g, int W, int H, int TX, int TY,
           Tc[k] = Tb;
         }
         // moments of gp over the pixels' offsets (u, v) from the region's
-        // first pixel centre: pixel k of the lane sits at u = lx + 8 ix, v =
+        // centre: pixel k of the lane sits at u = lx + 8 ix, v =
         // ly + 8 iy.  Values 0..4 carry sum gp u, sum gp v, sum gp u^2, sum gp
         // u v, sum gp v^2 and value 5 sum gp; the output pass turns them into
         // moments over (dx, dy) = (DX - u, DY - v) with the entry's offset
@@ -1164,7 +1166,9 @@ __global__ __launch_bounds__(TW* TH) void k_render_bwd_coop(int ntiles, int W, i
   }
   const float x0c = (float)(tx * TW) + 0.5f, y0c = (float)(ty * TH) + 0.5f;
   // the lane's pixel offset within the tile, and the sum it ends with
-  const float lxf = (float)(8 * (w % BX) + (lane & 7)), lyf = (float)(8 * (w / BX) + (lane >> 3));
+  // from the tile's centre
+  const float lxf = (float)(8 * (w % BX) + (lane & 7)) + 0.5f - 0.5f * TW;
+  const float lyf = (float)(8 * (w / BX) + (lane >> 3)) + 0.5f - 0.5f * TH;
   const int sidx = sum10_index(lane);
   uint32_t head = 0u, tail = 0u, top = nwalk;
   // back to front: entry k of thread t is number k NT + t of the step,
@@ -1257,7 +1261,7 @@ __global__ __launch_bounds__(TW* TH) void k_render_bwd_coop(int ntiles, int W, i
         for (int u = 1; u < NB; ++u) x += red[u][RED * tid + k];
         t[k] = x;
       }
-      grads_in_place(t, s0[tid], s1[tid], x0c, y0c);
+      grads_in_place(t, s0[tid], s1[tid], (float)(tx * TW) + 0.5f * TW, (float)(ty * TH) + 0.5f * TH);
     }
     __syncthreads();
     for (uint32_t i = (uint32_t)tid; i < n * GRAD2D; i += (uint32_t)NT) {
