@@ -40,8 +40,8 @@ __device__ __forceinline__ void unpack_rect(uint2 r, int& x0, int& y0, int& x1, 
 // takes RC_SUB chunks: their rects are loaded together, counted into one 1D
 // difference array per chunk in LDS, and wave k scans chunk k's array.  The
 // rects, read here in depth order (8 random bytes of a line each), are left
-// in that order for the scatter, which reads them in sequence: 28M pairs (48
-// views of 3M Gaussians) count 646 -> 729 us, scatter 1331 -> 1012; 3.4M pairs (48
+// in that order for the scatter, which reads them in sequence: 31M pairs (48
+// views of 3M Gaussians) count 646 -> 729 us, scatter 1331 -> 1012; 7.0M pairs (48
 // keyframes) 60 -> 73 and 139 -> 105.
 __global__ __launch_bounds__(256) void k_row_count(BinTab t, StateDev st, BinWork w) {
   __shared__ int dif[RC_SUB][MAX_ROWS + 1];

@@ -239,7 +239,7 @@ __device__ __forceinline__ unsigned long long wg_sum_before(const uint32_t* x, i
 // there are is known to the device alone, so a kernel over them has a grid of at
 // most VIS_GRID workgroups (the host's bound on their number, if smaller) that
 // walk them: a workgroup per block of the bound, most of them without a pair,
-// cost 80 us a kernel where 48 views saw 28M of 144M pairs (12.0 -> 11.15 ms a
+// cost 80 us a kernel where 48 views saw 31M of 144M pairs (12.0 -> 11.15 ms a
 // pass in the four binning and eight sort kernels; 400k in 8 views 978 -> 930 us, one
 // view of 300k 372 -> 360).  An XCD takes a
 // contiguous eighth of the blocks.  Every lane of the wave must be active.
