@@ -31,8 +31,7 @@ __device__ __forceinline__ float l1_sign(float e, float w) {
   return e > 0.f ? w : (e < 0.f ? -w : 0.f);
 }
 
-constexpr int L1_NT = 1024;
-template <bool VEC>
+template <bool VEC, int L1_NT>
 __global__ __launch_bounds__(L1_NT) void k_l1_grad(int HW, int blocks_per_view, const float* color,
                                                  const float* depth, const float* tcol,
                                                  const float* tdep, const float* expo,
@@ -102,8 +101,8 @@ __global__ __launch_bounds__(L1_NT) void k_l1_grad(int HW, int blocks_per_view, 
   if (lane_id() == 0) atomicAdd(&g_expo[2 * v + w], w == 0 ? ea * tot : tot);
 }
 
-// Workgroups of a call: one per compute unit
-constexpr int L1_BLOCKS = 256;
+// Workgroups of a call with exposure sums: one per compute unit
+constexpr int L1_EXPO_BLOCKS = 256;
 
 hipError_t launch_l1_grad(int nv, int HW, const float* color, const float* depth,
                           const float* tcol, const float* tdep, const float* expo, float w_col,
@@ -112,18 +111,21 @@ hipError_t launch_l1_grad(int nv, int HW, const float* color, const float* depth
   const uintptr_t al = (uintptr_t)color | (uintptr_t)tcol | (uintptr_t)g_col |
                        (g_dep ? ((uintptr_t)depth | (uintptr_t)tdep | (uintptr_t)g_dep) : 0);
   const bool vec = HW % 4 == 0 && (al & 15) == 0;
-  // few workgroups that stride: few atomics with exposure sums, and without them
-  // the same rate as a workgroup per 256 groups (48 views of 640 x 480 without
-  // sums 137 us; 153 with a thread per group in workgroups of 1024)
+  // without exposure sums about one pixel group per thread (every load of the kernel
+  // in flight at once): 48 views of 640 x 480 137 us, 153 with workgroups of 1024,
+  // 162 with few of them that stride
   const int per = vec ? HW / 4 : HW;
-  const int bpv = std::min((per + L1_NT - 1) / L1_NT,
-                           std::max(1, L1_BLOCKS / nv));
-  if (vec)
-    hipLaunchKernelGGL(k_l1_grad<true>, dim3(nv * bpv), dim3(L1_NT), 0, s, HW, bpv, color, depth,
-                       tcol, tdep, expo, w_col, w_dep, g_col, g_dep, g_expo);
-  else
-    hipLaunchKernelGGL(k_l1_grad<false>, dim3(nv * bpv), dim3(L1_NT), 0, s, HW, bpv, color, depth,
-                       tcol, tdep, expo, w_col, w_dep, g_col, g_dep, g_expo);
+  if (g_expo) {
+    const int bpv = std::min((per + 1023) / 1024, std::max(1, L1_EXPO_BLOCKS / nv));
+    hipLaunchKernelGGL((vec ? k_l1_grad<true, 1024> : k_l1_grad<false, 1024>), dim3(nv * bpv),
+                       dim3(1024), 0, s, HW, bpv, color, depth, tcol, tdep, expo, w_col, w_dep,
+                       g_col, g_dep, g_expo);
+  } else {
+    const int bpv = std::min((per + 255) / 256, std::max(64, 16384 / nv));
+    hipLaunchKernelGGL((vec ? k_l1_grad<true, 256> : k_l1_grad<false, 256>), dim3(nv * bpv),
+                       dim3(256), 0, s, HW, bpv, color, depth, tcol, tdep, expo, w_col, w_dep, g_col,
+                       g_dep, g_expo);
+  }
   return hipGetLastError();
 }
 
