@@ -57,10 +57,11 @@ __device__ __forceinline__ void sh_eval(float x, float y, float z, float* Y) {
   }
 }
 
-// Camera-space depth of a mean, in the key path's FP32 order.
-__device__ __forceinline__ float cam_depth32(const float* m, const float* Rc, const float* tc) {
+// Camera-space coordinate of a mean along one row (R, t) of a view, in the key
+// path's FP32 order.
+__device__ __forceinline__ float cam_row32(const float* m, const float* R, float t) {
 #pragma clang fp contract(off)
-  return ((Rc[6] * m[0] + Rc[7] * m[1]) + Rc[8] * m[2]) + tc[2];
+  return ((R[0] * m[0] + R[1] * m[1]) + R[2] * m[2]) + t;
 }
 
 struct KeyResult {
@@ -115,9 +116,9 @@ __device__ __forceinline__ bool key_view(const float* m, const KeyGauss& g, cons
                                          float limx, float limy, float itw, float ith, int TX,
                                          int TY, float z_near, KeyResult& kr) {
 #pragma clang fp contract(off)
-  const float p0 = ((Rc[0] * m[0] + Rc[1] * m[1]) + Rc[2] * m[2]) + tc[0];
-  const float p1 = ((Rc[3] * m[0] + Rc[4] * m[1]) + Rc[5] * m[2]) + tc[1];
-  const float p2 = cam_depth32(m, Rc, tc);
+  const float p0 = cam_row32(m, Rc, tc[0]);
+  const float p1 = cam_row32(m, Rc + 3, tc[1]);
+  const float p2 = cam_row32(m, Rc + 6, tc[2]);
   if (!(p2 > z_near) || !g.ok) return false;
   const float S[3][3] = {{g.S00, g.S01, g.S02}, {g.S01, g.S11, g.S12}, {g.S02, g.S12, g.S22}};
   float Wm[3][3];
@@ -204,9 +205,11 @@ struct KeyViews {
 // so the half-extent times z is at most
 //   sqrt(k2 tr S) fx (|R0| + lim |R2|) + sqrt(0.3 k2) z = r ex + sk z,
 // and the splat misses the image's tiles if u z lies further than that outside
-// [0, wt z].  The factors carry 1% and the products 1e-4 of room for the
-// rounding of either side (1e-5 at most); a NaN or infinity anywhere decides
-// nothing.
+// [0, wt z].  p and z are the key path's own values, bit for bit: R m + t
+// cancels where coordinates are large, and another rounding of it moves a splat
+// by pixels there.  From them on nothing cancels, each side rounds by 1e-5 of
+// its terms at most, and the factors carry 1% and the products 1e-4 of room for
+// that; a NaN or infinity anywhere decides nothing.
 __device__ __forceinline__ bool outside(float f, float p, float c, float z, float e, float wt) {
   const float fp = f * p, cz = c * z;
   const float room = e + 1e-4f * (fabsf(fp) + fabsf(cz));
@@ -306,9 +309,8 @@ __global__ __launch_bounds__(PROJ_BLOCK) void k_project(ProjTab t, SceneDev sc, 
       mk = __ballot(key_view(m, kg, Rc, tc, in.x, in.y, in.z, in.w, KV.lx[k], KV.ly[k], t.itw,
                              t.ith, t.TX, t.TY, cam.z_near, kr));
     } else {
-      const float p2 = cam_depth32(m, Rc, tc);
-      const float p0 = Rc[0] * m[0] + Rc[1] * m[1] + Rc[2] * m[2] + tc[0];
-      const float p1 = Rc[3] * m[0] + Rc[4] * m[1] + Rc[5] * m[2] + tc[1];
+      const float p0 = cam_row32(m, Rc, tc[0]), p1 = cam_row32(m, Rc + 3, tc[1]);
+      const float p2 = cam_row32(m, Rc + 6, tc[2]);
       const float e = sk * p2;
       const bool left = kg.ok && p2 > cam.z_near &&
                         !outside(in.x, p0, in.z, p2, r * KV.ex[k] + e, wt) &&
@@ -409,7 +411,7 @@ __device__ __forceinline__ void record_one(const ProjTab& t, const SceneDev& sc,
   if (!key_view(m, kg, Rc, tc, in.x, in.y, in.z, in.w, RV.lx[k], RV.ly[k], t.itw, t.ith, t.TX,
                 t.TY, cam.z_near, kr)) {
     kr.x0 = kr.x1 = kr.y0 = kr.y1 = 0u;
-    kr.p2 = cam_depth32(m, Rc, tc);
+    kr.p2 = cam_row32(m, Rc + 6, tc[2]);
   }
   st.vkey[row] = __float_as_uint(kr.p2);  // the depth sort's input
   st.rect[row] = make_uint2(kr.x0 | (kr.y0 << 16), kr.x1 | (kr.y1 << 16));

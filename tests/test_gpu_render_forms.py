@@ -164,3 +164,50 @@ def test_blocks_of_visible_pairs(n, n_views, chunk):
         np.testing.assert_array_equal(dbg["order"][lo:hi].astype(np.int64) - k * n,
                                       ek["order"].astype(np.int64))
         np.testing.assert_array_equal(c[k].cpu().numpy(), ck[0].cpu().numpy())
+
+
+# metres from the origin: a centimetre is 2 (at 50 km), 10 and 80 FP32 steps
+@pytest.mark.parametrize("far", [5e4, 1e4, 1e3])
+def test_key_pass_far_from_the_origin(far):
+    """Small splats across the edges of views far from the origin, where the
+    rotation and the translation of a mean cancel: the queued key pass (five views
+    or more of a set) sees the same pairs as one call per view, bit for bit."""
+    from paper_2605_10760_amd import Rasterizer, SceneTensors, ViewTensors
+    announce(f"key pass far {far}")
+    W, H, n_views, n, f = 72, 40, 6, 60000, 600.0
+    rng = np.random.default_rng(int(far))
+    intr = np.array([f, f, W / 2.0, H / 2.0])
+    vm, means = [], []
+    for k in range(n_views):
+        c = far * rng.uniform(0.3, 1.0, 3) * rng.choice([-1.0, 1.0], 3)
+        T = look_at(c, c + rng.normal(size=3), 0.3, 0.4)
+        vm.append(T)
+        # this view's share of the splats, on its image's edges
+        m = n // n_views
+        z = rng.uniform(0.25, 1.0, m)
+        u, v = rng.uniform(0, W, m), rng.uniform(0, H, m)
+        e = rng.integers(0, 4, m)
+        near = rng.uniform(-2.5, 2.5, m)
+        u = np.where(e == 0, near, np.where(e == 1, W + 8 + near, u))  # 72 = 4.5 tiles
+        v = np.where(e == 2, near, np.where(e == 3, H + 8 + near, v))
+        p = np.stack([(u - intr[2]) / f * z, (v - intr[3]) / f * z, z], 1)
+        means.append((p - T[:, 3]) @ T[:, :3])
+    scene = Scene(*draw_gaussians(rng, n, ROOM_LO, ROOM_HI), set_offsets=np.array([0, n], np.int64))
+    scene.means[:] = np.concatenate(means)
+    scene.log_scales[:] = rng.normal(-8.5, 0.3, (n, 3))
+    scene.opacity_logits[:] = 1.0
+    views = Views(np.array(vm, np.float32), np.array([intr] * n_views, np.float32),
+                  np.zeros(n_views, np.int32), W, H)
+    st, vt = SceneTensors.from_numpy(scene), ViewTensors.from_numpy(views)
+    big = Rasterizer(W, H, n_views * n, n_views)
+    *_, state = big.forward(st, vt)
+    dbg = big.debug_export(state, n_views, n_views * n, 0)
+    one = Rasterizer(W, H, n, 1)
+    seen = 0
+    for k in range(n_views):
+        *_, sk = one.forward(st, vt.select([k]))
+        ek = one.debug_export(sk, 1, n, 0)
+        np.testing.assert_array_equal(dbg["zkeys"][k * n:(k + 1) * n], ek["zkeys"])
+        np.testing.assert_array_equal(dbg["rects"][k * n:(k + 1) * n], ek["rects"])
+        seen += int(ek["vis_off"][1])
+    assert 0.2 * n < seen < 0.95 * n
