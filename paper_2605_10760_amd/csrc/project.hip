@@ -209,7 +209,10 @@ struct KeyViews {
 // cancels where coordinates are large, and another rounding of it moves a splat
 // by pixels there.  From them on nothing cancels, each side rounds by 1e-5 of
 // its terms at most, and the factors carry 1% and the products 1e-4 of room for
-// that; a NaN or infinity anywhere decides nothing.
+// that; a NaN or infinity anywhere decides nothing.  The bound is one for z > 0:
+// a near plane behind the camera lets others through, and they, like depths whose
+// products leave the normal range, are left to the key path (OUTSIDE_Z).
+constexpr float OUTSIDE_Z = 1e-30f;
 __device__ __forceinline__ bool outside(float f, float p, float c, float z, float e, float wt) {
   const float fp = f * p, cz = c * z;
   const float room = e + 1e-4f * (fabsf(fp) + fabsf(cz));
@@ -313,8 +316,9 @@ __global__ __launch_bounds__(PROJ_BLOCK) void k_project(ProjTab t, SceneDev sc, 
       const float p2 = cam_row32(m, Rc + 6, tc[2]);
       const float e = sk * p2;
       const bool left = kg.ok && p2 > cam.z_near &&
-                        !outside(in.x, p0, in.z, p2, r * KV.ex[k] + e, wt) &&
-                        !outside(in.y, p1, in.w, p2, r * KV.ey[k] + e, ht);
+                        (p2 < OUTSIDE_Z ||
+                         (!outside(in.x, p0, in.z, p2, r * KV.ex[k] + e, wt) &&
+                          !outside(in.y, p1, in.w, p2, r * KV.ey[k] + e, ht)));
       mk = __ballot(left);
       if (left)
         L.item[(tail + __builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32),

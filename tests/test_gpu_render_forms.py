@@ -211,3 +211,27 @@ def test_key_pass_far_from_the_origin(far):
         np.testing.assert_array_equal(dbg["rects"][k * n:(k + 1) * n], ek["rects"])
         seen += int(ek["vis_off"][1])
     assert 0.2 * n < seen < 0.95 * n
+
+
+@pytest.mark.parametrize("z_near", [-8.0, 0.0])
+def test_key_pass_with_any_near_plane(z_near):
+    """A near plane at or behind the camera: the queued key pass keeps the pairs
+    that one call per view keeps, those of negative depth among them."""
+    from paper_2605_10760_amd import Rasterizer, SceneTensors, ViewTensors
+    announce(f"key pass near plane {z_near}")
+    W, H, n_views, n = 72, 40, 6, 3000
+    scene, views = _case(n, n_views, W, H)
+    st, vt = SceneTensors.from_numpy(scene), ViewTensors.from_numpy(views)
+    big = Rasterizer(W, H, n_views * n, n_views)
+    *_, state = big.forward(st, vt, z_near=z_near)
+    dbg = big.debug_export(state, n_views, n_views * n, 0)
+    one = Rasterizer(W, H, n, 1)
+    behind = 0
+    for k in range(n_views):
+        *_, sk = one.forward(st, vt.select([k]), z_near=z_near)
+        ek = one.debug_export(sk, 1, n, 0)
+        np.testing.assert_array_equal(dbg["zkeys"][k * n:(k + 1) * n], ek["zkeys"])
+        np.testing.assert_array_equal(dbg["rects"][k * n:(k + 1) * n], ek["rects"])
+        vis = ek["zkeys"] != 0xFFFFFFFF
+        behind += int((ek["zkeys"][vis].view(np.float32) < 0).sum())
+    assert (behind > 0) == (z_near < 0)
