@@ -354,8 +354,8 @@ gsr_status gsr_dedup_workspace_bytes(int64_t table_slots, size_t* out_bytes);
  * depth per pixel), viewmats [K,3,4] world->camera, intrinsics [K,4] for the
  * target's keyframes; src_means [n_src,3]; keep uint8 [n_src] (out);
  * workspace 256-byte aligned, >= gsr_dedup_workspace_bytes(table_slots),
- * overwritten.  Synchronises `stream`; n_voxels (HOST, may be NULL) gets the
- * number of distinct voxels inserted.  GSR_E_OVERFLOW (keep not valid) when
+ * overwritten.  Synchronises `stream` (GSR_E_DEVICE on one under capture);
+ * n_voxels (HOST, may be NULL) gets the number of distinct voxels inserted.  GSR_E_OVERFLOW (keep not valid) when
  * the hash set ran out of slots; GSR_E_INVALID_ARG for bad parameters, or
  * (found on the device; keep not valid) a voxel index outside +-2^20 per
  * axis, a non-finite input, or one box or segment of more than 2^22 voxels. */
@@ -374,7 +374,7 @@ gsr_status gsr_dedup(const gsr_dedup_params* params, const float* tgt_means,
  * log_scales, quats, opacity logits and colours; set_offsets_out is a HOST
  * array [n_sets+1] of the pruned set offsets (its last entry = rows kept).
  * Allocates a small temporary device buffer and synchronises `stream` (set-up
- * work, not capturable).  GSR_E_INVALID_ARG for null pointers, bad offsets or
+ * work; GSR_E_DEVICE on a stream under capture).  GSR_E_INVALID_ARG for null pointers, bad offsets or
  * min_opacity outside (0, 1). */
 gsr_status gsr_prune(const gsr_scene* scene, float min_opacity, float* means_out,
                      float* log_scales_out, float* quats_out, float* opacity_out,
@@ -418,7 +418,8 @@ gsr_status gsr_normal_loss_grad(const float* depth, const float* normal_prior,
  * [4]: device arrays.  Outputs (device, capacity max_out rows): means_out,
  * log_scales_out, colors_out [max_out,3], quats_out [max_out,4],
  * opacity_out [max_out].  Allocates a small temporary and synchronises
- * `stream`; *n_out (HOST) gets the number of seeded Gaussians.
+ * `stream` (GSR_E_DEVICE on one under capture: gsr_seed_noalloc is for that);
+ * *n_out (HOST) gets the number of seeded Gaussians.
  * GSR_E_OVERFLOW when that exceeds max_out (the first max_out rows are
  * written); GSR_E_INVALID_ARG for null pointers or bad sizes. */
 gsr_status gsr_seed(const float* depth, const float* color, const float* viewmat,

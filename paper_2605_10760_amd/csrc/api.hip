@@ -325,6 +325,20 @@ struct StageMark {
   }
 };
 
+// Whether work on the stream is being captured (also implicitly: the default
+// stream while a capture that it would join is open).  A call that returns
+// results to the host refuses it before anything is enqueued: captured work has
+// not run when the call returns, and a replay would write through its scratch
+// and into its caller's memory.
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return cs != hipStreamCaptureStatusNone;
+}
+
 void free_ws(gsr_ctx* c) {
   if (c->ws) (void)hipFree(c->ws);
   c->ws = nullptr;
@@ -843,6 +857,7 @@ gsr_status gsr_dedup(const gsr_dedup_params* p, const float* tgt_means,
     return GSR_E_INVALID_ARG;
   if (((uintptr_t)workspace & 255) != 0) return GSR_E_INVALID_ARG;
   hipStream_t st = (hipStream_t)stream;
+  if (capturing(st)) return GSR_E_DEVICE;
   unsigned int* dc = nullptr;
   hipError_t e = launch_dedup(p->table_slots, workspace, p->voxel, p->k_env, tgt_means,
                               tgt_log_scales, n_tgt, depth, viewmats, intrinsics, n_keyframes,
@@ -885,6 +900,7 @@ gsr_status gsr_prune(const gsr_scene* sc, float min_opacity, float* means_out,
   if ((double)thr < lg) thr = nextafterf(thr, INFINITY);
   SceneDev in = scene_dev(sc);
   hipStream_t st = (hipStream_t)stream;
+  if (capturing(st)) return GSR_E_DEVICE;
   const size_t nb = (size_t)((n + 255) / 256);
   CallScratch tmp;
   if (tmp.get(4 * (nb + 1) + 8 * (GSR_MAX_SETS + 1) + 256) != hipSuccess) {
@@ -941,13 +957,14 @@ gsr_status gsr_seed(const float* depth, const float* color, const float* viewmat
     return GSR_E_INVALID_ARG;
   const long gm = (long)((width + stride - 1) / stride) * ((height + stride - 1) / stride);
   if ((double)width * height * 3 > 2147483647.0 || gm > 0x7FFFFFFFL) return GSR_E_INVALID_ARG;
+  hipStream_t st = (hipStream_t)stream;
+  if (capturing(st)) return GSR_E_DEVICE;
   const size_t nb = (size_t)((gm + 255) / 256);
   CallScratch tmp;
   if (tmp.get(4 * (nb + 1)) != hipSuccess) {
     (void)hipGetLastError();
     return GSR_E_OOM;
   }
-  hipStream_t st = (hipStream_t)stream;
   uint32_t* blk = (uint32_t*)tmp.ptr;
   uint32_t total = 0;
   hipError_t e = launch_seed(width, height, stride, depth, color, viewmat, intrinsics,

@@ -112,3 +112,43 @@ def test_seed_counts_around_the_scan_size(shape):
     assert int(n_dev.item()) == want.shape[0]
     for key in rows:
         assert torch.equal(rows[key][:want.shape[0]], got[key]), key
+
+
+def test_calls_that_wait_are_refused_under_capture():
+    """seed, prune and dedup return results to the host: on a stream under capture
+    they are refused before anything is enqueued, so the capture goes on without
+    them and later eager calls are whole."""
+    announce("refused under capture")
+    import torch
+    from paper_2605_10760_amd import GsrError, SceneTensors, dedup, prune, seed
+    rng = np.random.default_rng(8)
+    n, H, W = 700, 37, 53
+    depth, _, intr = slanted_depth(rng, 1, W, H, f=0.5 * W, hole_frac=0.03)
+    col = rng.random((3, H, W)).astype(np.float32)
+    vm = look_at(np.array([0.4, -0.1, -1.5]), (0.0, 0.0, 1.0), 0.1).astype(np.float32)
+    dt, ct, vt, it = _t(depth[0]), _t(col), _t(vm), _t(intr[0])
+    f = lambda *s: _t(rng.normal(-1.0, 1.0, s).astype(np.float32))
+    scene = SceneTensors(f(n, 3), f(n, 3) - 3.0, f(n, 4), f(n) * 4.0, f(n, 3),
+                         np.array([0, 300, n], np.int64))
+    calls = [lambda: seed(dt, ct, vt, it, stride=2),
+             lambda: prune(scene, 0.3),
+             lambda: dedup(scene.means, scene.means, scene.log_scales, None, None, None, 0.05, 1.0,
+                           table_slots=1 << 16)]
+    want = [c() for c in calls]
+    x = torch.zeros(64, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for c in calls:
+            with pytest.raises(GsrError) as e:
+                c()
+            assert "GSR_E_DEVICE" in str(e.value)
+        x.add_(1.0)
+    for k in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert bool((x == k + 1).all())
+        got = [c() for c in calls]
+        assert all(torch.equal(got[0][q], want[0][q]) for q in want[0])
+        np.testing.assert_array_equal(got[1].set_offsets, want[1].set_offsets)
+        assert torch.equal(got[1].means, want[1].means) and 0 < got[1].n < n
+        assert torch.equal(got[2][0], want[2][0]) and got[2][1] == want[2][1] > 0
