@@ -62,12 +62,24 @@ struct DedupTable {
   __device__ unsigned int* bits() const { return reinterpret_cast<unsigned int*>(keys); }
 };
 
-// Sets bits of a word of the bitmap.  A plain read first: a word that
+// Reads and writes of memory that other threads write meanwhile: relaxed
+// atomics of the narrowest scope, which are the plain instructions but neither
+// torn nor repeated by the compiler.  Their readers bear a stale value (cells only
+// gain bits or go from empty to final), not half of one and half of another.
+template <class T>
+__device__ __forceinline__ T dd_peek(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+template <class T>
+__device__ __forceinline__ void dd_poke(T* p, T x) {
+  __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Sets bits of a word of the bitmap.  A look first: a word that
 // already holds them (the rays of one keyframe share most of their voxels)
 // needs no atomic, and a stale one falls through to it.
 __device__ __forceinline__ void dd_or(unsigned int* w, unsigned int bits) {
-  const unsigned int cur = *w;
-  if ((cur & bits) != bits) atomicOr(w, bits);
+  if ((dd_peek(w) & bits) != bits) atomicOr(w, bits);
 }
 __device__ __forceinline__ unsigned int* dd_word(const DedupTable& T, const DedupGrid& G, int x,
                                                  int y, int z) {
@@ -91,7 +103,7 @@ __device__ __forceinline__ unsigned long long dd_mix(unsigned long long k) {
   return k;
 }
 
-// A slot's key only ever goes from empty to its final value, so a plain
+// A slot's key only ever goes from empty to its final value, so a
 // read that already shows the key (or the flag) settles the insert without
 // an atomic: many rays of one keyframe share the voxels near its camera, and
 // their CASes would otherwise queue on the same slot.  A stale read of an
@@ -99,7 +111,7 @@ __device__ __forceinline__ unsigned long long dd_mix(unsigned long long k) {
 __device__ void dd_insert(const DedupTable& T, unsigned long long key, unsigned int flag) {
   unsigned long long h = dd_mix(key) & T.mask;
   for (int probe = 0; probe < DD_MAX_PROBE && probe <= (long long)T.mask; ++probe) {
-    unsigned long long cur = T.keys[h];
+    unsigned long long cur = dd_peek(&T.keys[h]);
     if (cur == DD_EMPTY) {
       cur = atomicCAS(&T.keys[h], DD_EMPTY, key);
       if (cur == DD_EMPTY) {
@@ -109,7 +121,7 @@ __device__ void dd_insert(const DedupTable& T, unsigned long long key, unsigned 
       }
     }
     if (cur == key) {
-      if ((T.flags[h] & flag) == 0u) atomicOr(&T.flags[h], flag);
+      if ((dd_peek(&T.flags[h]) & flag) == 0u) atomicOr(&T.flags[h], flag);
       return;
     }
     h = (h + 1) & T.mask;
@@ -129,7 +141,7 @@ __device__ void dd_insert_local(const DedupTable& T, unsigned long long* lk,
                                 unsigned long long key, unsigned int flag) {
   unsigned int h = (unsigned int)(dd_mix(key) >> 40) & (DD_LSLOTS - 1);
   for (int probe = 0; probe < DD_LPROBE; ++probe) {
-    unsigned long long cur = lk[h];
+    unsigned long long cur = dd_peek(&lk[h]);
     if (cur == DD_EMPTY) {
       cur = atomicCAS(&lk[h], DD_EMPTY, key);
       if (cur == DD_EMPTY) {
@@ -314,16 +326,16 @@ __global__ __launch_bounds__(256) void k_dd_occ(DedupTable T, const float* means
 
 // Sets one bit of the bitmap through a workgroup-local cache of words
 // (direct-mapped, (word + 1, bits known set) in one 64-bit slot).  Slots are
-// read and written without atomics: a lost update only costs another look at
-// the bitmap itself.
+// read and written whole, but not both at once: a lost update only costs another
+// look at the bitmap itself.
 __device__ __forceinline__ void dd_set_local(const DedupTable& T, unsigned long long* lk,
                                              unsigned int word, unsigned int bit) {
   unsigned long long* slot = lk + (word & (DD_LSLOTS - 1));
-  const unsigned long long e = *slot;
+  const unsigned long long e = dd_peek(slot);
   const bool same = (unsigned int)(e >> 32) == word + 1u;
   if (same && ((unsigned int)e & bit)) return;
   dd_or(T.bits() + word, bit);
-  *slot = ((unsigned long long)(word + 1u) << 32) | (same ? (unsigned int)e | bit : bit);
+  dd_poke(slot, ((unsigned long long)(word + 1u) << 32) | (same ? (unsigned int)e | bit : bit));
 }
 
 // Walks a segment's voxels in increasing t: step(axis, +-1) at every plane
@@ -454,7 +466,7 @@ __global__ __launch_bounds__(DD_FT) void k_dd_free(DedupTable T, const float* de
         const auto set = [&]() {
           unsigned int* w = lw + (at >> 5);
           const unsigned int bit = 1u << (at & 31);
-          if (!(*w & bit)) atomicOr(w, bit);
+          if (!(dd_peek(w) & bit)) atomicOr(w, bit);
         };
         set();
         dd_walk(c, d, cur, end, v, [&](int axis, int sg) {

@@ -173,3 +173,33 @@ def test_dedup_bitmap_and_hash_set(far):
     ref = np.array([tuple(q) not in occ and tuple(q) not in fr for q in voxel_of(sm, v)])
     np.testing.assert_array_equal(keep.cpu().numpy().astype(bool), ref)
     assert nvox == len(occ | fr) + more
+
+
+# boxes of a 64 x 16 pixel tile's rays: up to about 100 voxels an axis (they fit
+# the workgroup's bitmap), and up to 250 (the workgroup's cache of words)
+@pytest.mark.parametrize("v", [0.05, 0.02])
+def test_dedup_forms_full_size(v):
+    """Keyframes whose rays all cross the voxels near their camera at once: the
+    bitmap, through a workgroup's own bitmap or its cache of words, and the hash
+    set hold the same voxels."""
+    announce(f"dedup forms full size {v}")
+    import torch
+    from paper_2605_10760_amd import dedup as gpu_dedup
+    rng = np.random.default_rng(31)
+    K, H, W = 3, 203, 330
+    vms = [look_at(rng.uniform(-1.0, 1.0, 3), rng.uniform(-1.0, 1.0, 3), 0.3, 0.2)
+           for _ in range(K)]
+    intr = np.array([pinhole(W, H, W / 2.0)] * K, np.float32)
+    depth = (0.4 + 2.2 * rng.random((K, H, W))).astype(np.float32)
+    tm = rng.uniform(-2.0, 2.0, (4000, 3)).astype(np.float32)
+    tls = rng.normal(-3.2, 0.5, (4000, 3)).astype(np.float32)
+    sm = rng.uniform(-3.0, 3.0, (60000, 3)).astype(np.float32)
+    far = np.full((1, 3), 900.01, np.float32)  # no bitmap of the workspace reaches it
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    arg = (t(depth), t(np.array(vms, np.float32)), t(intr), v, 1.0)
+    keep, nvox = gpu_dedup(t(sm), t(tm), t(tls), *arg, table_slots=1 << 23)
+    keep2, nvox2 = gpu_dedup(t(sm), t(np.concatenate([tm, far])),
+                             t(np.concatenate([tls, np.full((1, 3), -20.0, np.float32)])), *arg,
+                             table_slots=1 << 23)
+    assert nvox2 == nvox + 1 > 10000
+    assert torch.equal(keep, keep2) and 0 < int(keep.sum()) < keep.numel()
