@@ -42,7 +42,9 @@ __global__ __launch_bounds__(L1_NT) void k_l1_grad(int HW, int blocks_per_view, 
   const int b0 = blockIdx.x - v * blocks_per_view;
   const float a = expo ? expo[2 * v] : 0.f, b = expo ? expo[2 * v + 1] : 0.f;
   const float ea = expf(a);
-  float sa = 0.f, sb = 0.f;
+  // the exposure sums: a thread's pixel groups in FP64, of which it takes as many
+  // as the call is large (FP32 over 60 groups: 2e-6 of the sum, now 1e-7)
+  double sad = 0.0, sbd = 0.0;
   if (VEC) {
     const int n4 = HW / 4;
     for (int p = b0 * L1_NT + (int)threadIdx.x; p < n4; p += blocks_per_view * L1_NT) {
@@ -57,8 +59,8 @@ __global__ __launch_bounds__(L1_NT) void k_l1_grad(int HW, int blocks_per_view, 
                                      l1_sign(ea * c.w + b - t.w, w_col));
         *reinterpret_cast<float4*>(g_col + base + (size_t)ch * HW) =
             make_float4(ea * g.x, ea * g.y, ea * g.z, ea * g.w);
-        sa += c.x * g.x + c.y * g.y + c.z * g.z + c.w * g.w;
-        sb += g.x + g.y + g.z + g.w;
+        sad += (double)(c.x * g.x + c.y * g.y + c.z * g.z + c.w * g.w);
+        sbd += (double)(g.x + g.y + g.z + g.w);
       }
       if (g_dep) {
         const size_t q = (size_t)v * HW + 4 * (size_t)p;
@@ -77,8 +79,8 @@ __global__ __launch_bounds__(L1_NT) void k_l1_grad(int HW, int blocks_per_view, 
         const float c = color[base + (size_t)ch * HW];
         const float g = l1_sign(ea * c + b - tcol[base + (size_t)ch * HW], w_col);
         g_col[base + (size_t)ch * HW] = ea * g;
-        sa += c * g;
-        sb += g;
+        sad += (double)(c * g);
+        sbd += (double)g;
       }
       if (g_dep) {
         const size_t q = (size_t)v * HW + p;
@@ -87,8 +89,7 @@ __global__ __launch_bounds__(L1_NT) void k_l1_grad(int HW, int blocks_per_view, 
     }
   }
   if (!g_expo) return;  // uniform
-  sa = wave_total(sa);
-  sb = wave_total(sb);
+  const float sa = wave_total((float)sad), sb = wave_total((float)sbd);
   const int w = threadIdx.x >> 6;
   if (lane_id() == 0) {
     red[0][w] = sa;

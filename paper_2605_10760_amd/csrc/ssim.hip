@@ -159,7 +159,7 @@ __device__ __forceinline__ void ss_horiz(const SsimArgs& A, const float (&wt)[SS
 }
 
 template <int NW>
-__global__ __launch_bounds__(64 * NW) void k_ssim(SsimArgs A, const float* color, const float* target,
+__global__ __launch_bounds__(64 * NW, 2) void k_ssim(SsimArgs A, const float* color, const float* target,
                                              const float* expo, float* d_color, float* ssim_part,
                                              float* e_part) {
   constexpr int OW = ss_out(NW), SW = ss_stats(NW);
@@ -220,7 +220,10 @@ __global__ __launch_bounds__(64 * NW) void k_ssim(SsimArgs A, const float* color
     place(g, nx, ny, rx[g], ry[g]);
   }
   fetch(3, nx, ny);
-  float s = 0.f, sa = 0.f, sb = 0.f;
+  // a lane sums four rows in FP32 and the steps, as many as the march is long,
+  // in FP64: a chain of hundreds of FP32 additions would lose digits that the
+  // tree over lanes and workgroups does not (240 rows: 3e-6 of the sum, now 2e-7).
+  double sd = 0.0, sad = 0.0, sbd = 0.0;
   const int steps = (y1 - y0 + 3) / 4 + 3;
   for (int s0 = 0; s0 < steps; s0 += 4) {
 #pragma unroll
@@ -248,6 +251,7 @@ __global__ __launch_bounds__(64 * NW) void k_ssim(SsimArgs A, const float* color
           },
           m);
       ss_horiz<4, NW>(A, wt, buf, alone, st + 1, flag, m);
+      float s4 = 0.f;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int r = y0 - SS_R + 4 * st + i;
@@ -267,8 +271,9 @@ __global__ __launch_bounds__(64 * NW) void k_ssim(SsimArgs A, const float* color
         f[1][u][i] = in ? d_sxx : 0.f;
         f[2][u][i] = in ? d_sxy : 0.f;
         // the workgroup's own pixels carry S
-        if (r >= y0 && r < y1) s += own_col ? so : 0.f;
+        if (r >= y0 && r < y1) s4 += own_col ? so : 0.f;
       }
+      sd += (double)s4;
       if (st < 3) {  // uniform: the first output rows need four groups
         if (NW > 1) __syncthreads();
         continue;
@@ -277,6 +282,7 @@ __global__ __launch_bounds__(64 * NW) void k_ssim(SsimArgs A, const float* color
       ss_v4 bl[3];
       alone = ss_vert<3>(A, wt, [&](int k, int t) { return f[k][(u + 1 + (t >> 2)) & 3][t & 3]; }, bl);
       ss_horiz<3, NW>(A, wt, buf2, alone, st + 1, flag + 1, bl);
+      float sa4 = 0.f, sb4 = 0.f;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int r = y0 + 4 * (st - 3) + i;
@@ -285,15 +291,16 @@ __global__ __launch_bounds__(64 * NW) void k_ssim(SsimArgs A, const float* color
         float g = -A.weight_over_n * (bl[0][i] + 2.f * x * bl[1][i] + oy[i] * bl[2][i]);
         g = r < y1 && xo_in ? g : 0.f;
         if (r < y1 && xo_in) (di + (size_t)r * A.W)[oxc] = od[i] + ea * g;
-        sa += g * oc[i];
-        sb += g;
+        sa4 += g * oc[i];
+        sb4 += g;
       }
+      sad += (double)sa4;
+      sbd += (double)sb4;
     }
   }
   const size_t bb = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
-  s = wave_total(s);
-  sa = wave_total(sa);
-  sb = wave_total(sb);
+  float s = wave_total((float)sd);
+  float sa = wave_total((float)sad), sb = wave_total((float)sbd);
   const int w = lane >> 6;
   if (lane_id() == 0) {
     red[0][w] = s;

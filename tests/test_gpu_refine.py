@@ -211,3 +211,55 @@ def test_ssim_grad_non_finite_stays_local(W, bad):
     near[1, pj - 10:pj + 11, max(pi - 10, 0):pi + 11] = True
     assert not np.isfinite(grads[1][near]).any()
     np.testing.assert_allclose(grads[1][~near], grads[0][~near], rtol=1e-5, atol=1e-7)
+
+
+# FP32 roundings between a term and its sum: the product, the sums over a thread's
+# pixel group (L1) or four rows (SSIM), the conversion of the thread's FP64 sum, the
+# tree over lanes and waves, the workgroups' sums and the exposure factor (1 here)
+L1_ROUNDINGS, SSIM_ROUNDINGS = 19, 23
+
+
+def _sum_err(got, terms):
+    """Largest error of the sums got [V] of terms [V, ...] (FP64), relative to the
+    sums of their absolute values."""
+    want = terms.flatten(1).sum(1)
+    return float(((got.double() - want).abs() / terms.flatten(1).abs().sum(1)).max())
+
+
+def test_l1_exposure_sums_of_a_large_batch():
+    """Constant images, whose equal terms let the roundings of a long chain of FP32
+    additions add up, in a call that gives a thread 180 of them: the exposure
+    gradients against FP64 sums over the gradient images."""
+    announce("l1 exposure sums of a large batch")
+    import torch
+    from paper_2605_10760_amd import l1_loss_grad as gpu_grad
+    V, H, W = 256, 384, 640
+    c = torch.full((V, 3, H, W), 0.37, device="cuda")
+    tc = torch.zeros_like(c)
+    ex = torch.zeros((V, 2), device="cuda")
+    out = dict(d_color=torch.empty_like(c), d_depth=None, d_exposure=torch.empty_like(ex))
+    for k in range(24):
+        gpu_grad(c, tc, None, None, ex, 1.0 + k / 17.0, 0.0, out=out)
+        g = out["d_color"][:1, :, :1, :1].double().expand(1, 3, H, W)  # every pixel's
+        assert bool((out["d_color"] == out["d_color"][0, 0, 0, 0]).all())
+        for i, t in enumerate((g * float(c[0, 0, 0, 0]), g)):
+            assert _sum_err(out["d_exposure"][:1, i], t) <= L1_ROUNDINGS * 2.0 ** -24, (k, i)
+
+
+def test_ssim_exposure_sums_of_a_large_batch():
+    """The same for SSIM, in a call whose lanes march down 240 rows."""
+    announce("ssim exposure sums of a large batch")
+    import torch
+    from paper_2605_10760_amd import ssim_grad
+    V, H, W = 2800, 240, 40
+    x = torch.full((V, 3, H, W), 0.71, device="cuda")
+    y = torch.full((V, 3, H, W), 0.35, device="cuda")
+    ex = torch.zeros((V, 2), device="cuda")
+    ws = None
+    for k in range(24):
+        d = torch.zeros_like(x)
+        de = torch.zeros_like(ex)
+        ws = ssim_grad(x, y, d, exposure=ex, d_exposure=de, weight=1.0 + k / 17.0, workspace=ws)
+        part = d[:4].double()
+        for i, t in enumerate((part * float(x[0, 0, 0, 0]), part)):
+            assert _sum_err(de[:4, i], t) <= SSIM_ROUNDINGS * 2.0 ** -24, (k, i)
