@@ -249,8 +249,10 @@ __device__ __forceinline__ void pair_bwd(const BwdView& w, const float* m, const
 // from 4 steps for 3 on (3M Gaussians of degree 3 in 32 views: 1500 us, in
 // turn 2670; 400k in 8 views 105 and 152; 1.6M of degree 0 in 8 views of each
 // submap, where most waves save nothing: 223 in turn, all `own` 348).
-// The workgroup adds its pose sums to the call's in FP64, and the last
-// workgroup to finish writes d_pose and clears them for the next call (no
+// Pose sums are FP64 from the workgroup's LDS on (a chain of up to 256 FP32
+// additions in `own`, no tree, lost 4 times the rounding of the result; the FP64
+// LDS atomics are the faster ones too: 3M Gaussians of degree 3 in 32 views 1401 ->
+// 1196 us), and the last workgroup to finish writes d_pose and clears them for the next call (no
 // clearing kernel, and the rounding of thousands of FP32 additions per
 // component does not reach the result).
 template <int SHD>
@@ -276,7 +278,7 @@ __global__ __launch_bounds__(256) void k_project_bwd(SetTab t, SceneDev sc, CamD
   __shared__ double vlim[MAXV][2];
   __shared__ unsigned long long vmask[MAXV][4];
   __shared__ uint32_t vrow[MAXV][4];
-  __shared__ float psum[MAXV][6];
+  __shared__ double psum[MAXV][6];
   if ((int)threadIdx.x < nv) {
     const int v = t.view_by_set[v0 + (int)threadIdx.x];
     const float* vm = cam.viewmats + 12 * v;
@@ -295,7 +297,7 @@ __global__ __launch_bounds__(256) void k_project_bwd(SetTab t, SceneDev sc, CamD
       vrow[threadIdx.x][w] = row;
       row += (uint32_t)__popcll(mk);
     }
-    for (int k = 0; k < 6; ++k) psum[threadIdx.x][k] = 0.f;
+    for (int k = 0; k < 6; ++k) psum[threadIdx.x][k] = 0.0;
   }
 
   // The mean and the forward's FP64 covariance (the conic is recomputed per view
@@ -378,7 +380,7 @@ __global__ __launch_bounds__(256) void k_project_bwd(SetTab t, SceneDev sc, CamD
       read_row(k, g10);
       pair_bwd<SHD>(load_view(k), m, Sd, g10, kk, G, gk, 256, pose);
 #pragma unroll
-      for (int i = 0; i < 6; ++i) unsafeAtomicAdd(&psum[k][i], pose[i]);
+      for (int i = 0; i < 6; ++i) unsafeAtomicAdd(&psum[k][i], (double)pose[i]);
     }
   } else {
     while (any) {
@@ -392,7 +394,7 @@ __global__ __launch_bounds__(256) void k_project_bwd(SetTab t, SceneDev sc, CamD
       }
       for (int i = 0; i < 6; ++i) pose[i] = wave_total(pose[i]);
       if (lane_id() == 0)
-        for (int i = 0; i < 6; ++i) unsafeAtomicAdd(&psum[k][i], pose[i]);
+        for (int i = 0; i < 6; ++i) unsafeAtomicAdd(&psum[k][i], (double)pose[i]);
     }
   }
   __syncthreads();
@@ -408,9 +410,9 @@ __global__ __launch_bounds__(256) void k_project_bwd(SetTab t, SceneDev sc, CamD
   }
   for (int i = threadIdx.x; i < 6 * nv; i += 256) {
     const int k = i / 6;
-    const float tot = psum[k][i - 6 * k];
-    if (tot != 0.f)
-      unsafeAtomicAdd(&pa->share[share].sum[6 * t.view_by_set[v0 + k] + (i - 6 * k)], (double)tot);
+    const double tot = psum[k][i - 6 * k];
+    if (tot != 0.0)
+      unsafeAtomicAdd(&pa->share[share].sum[6 * t.view_by_set[v0 + k] + (i - 6 * k)], tot);
   }
   // The last workgroup writes the call's sums and clears them: the last of each
   // XCD's share finds itself by the share's count, the last of these by the

@@ -52,3 +52,36 @@ def test_views_in_turn_and_own_views(sizes, n_views, sh):
         for q in PARAMS + ("d_pose",):
             err = float((total[q] - g[q]).abs().max())
             assert err <= RERUN_TOL * float(total[q].abs().max()), (q, err)
+
+
+def test_pose_sums_of_own_views():
+    """Two views side by side, each seeing every other Gaussian of one workgroup: a
+    lane takes its own view, and the views' translation gradients are the sums of
+    their Gaussians' mean gradients (unit rotations: the very same numbers) to the
+    one rounding of the result."""
+    import torch
+    from paper_2605_10760_amd import Rasterizer, SceneTensors, ViewTensors
+    announce("backward pose sums of own views")
+    rng = np.random.default_rng(77)
+    n, W, H = 256, 64, 48
+    scene = Scene(*draw_gaussians(rng, n, (-0.9, -0.6, 2.0), (0.9, 0.6, 3.0)),
+                  set_offsets=np.array([0, n], np.int64))
+    scene.log_scales[:] = rng.normal(-3.5, 0.2, (n, 3))
+    scene.opacity_logits[:] = 1.0
+    scene.means[1::2, 0] += 50.0
+    vm = np.zeros((2, 3, 4), np.float32)
+    vm[:, [0, 1, 2], [0, 1, 2]] = 1.0
+    vm[1, 0, 3] = -50.0
+    views = Views(vm, np.array([pinhole(W, H, W / 2.0)] * 2, np.float32), np.zeros(2, np.int32),
+                  W, H)
+    st, vt = SceneTensors.from_numpy(scene), ViewTensors.from_numpy(views)
+    gc = torch.linspace(-1.0, 1.0, W, device="cuda").expand(2, 3, H, W).contiguous()
+    gd = torch.full((2, H, W), 3.0, device="cuda")
+    r = Rasterizer(W, H, 2 * n, 2)
+    *_, state = r.forward(st, vt)
+    assert r.poll(state)["visible_pairs"] == n
+    g = r.backward(st, vt, state, gc, gd)
+    for v in range(2):
+        want = g["d_means"][v::2].double().sum(0)
+        err = (g["d_pose"][v, :3].double() - want).abs() / want.abs()
+        assert float(err.max()) <= 1.001 * 2.0 ** -24, (v, err.tolist())
