@@ -56,6 +56,30 @@ struct SortTab {
   int sblk_off[MAXV + 1];     // SORT_TILE blocks per view, prefix (upper bound)
 };
 
+// Whether the sort goes without scan kernels: each scatter block then walks its
+// view's digit counts itself (1 KB a block of the view), which saves four launches
+// and, in each pass, one workgroup's walk down the largest view.  A pass reads the
+// sum over the views of blocks^2 KB that way, so that sum decides, against the
+// launches and the largest view; the blocks are the host's bound on the visible
+// ones.  Sort of one view that sees all (without | with scan kernels, us): 1.0M
+// pairs 125 | 137, 1.5M 165 | 179, 2M 227 | 214, 3M 420 | 281, 4M 665 | 350; 8 views
+// of 200k 92 | 98, of 400k 156 | 146, of 800k 334 | 234; 48 of 85k 143 | 148, of 170k
+// 253 | 240.  Where a quarter of the pairs is visible, as in most calls, going
+// without is 8 to 17 us faster in all of them, so the line lies where the loss of a
+// call that sees all stays below that.  Calls of more than 2048 blocks have more
+// to sort than launches to save.
+constexpr int FOLD_BLOCKS = 2048;
+constexpr long FOLD_SQUARES = 250000, FOLD_PER_BLOCK = 400;
+inline bool sort_folds(const SortTab& t) {
+  long squares = 0, most = 0;
+  for (int v = 0; v < t.nv; ++v) {
+    const long b = t.sblk_off[v + 1] - t.sblk_off[v];
+    squares += b * b;
+    most = b > most ? b : most;
+  }
+  return t.sblk_off[t.nv] <= FOLD_BLOCKS && squares <= FOLD_SQUARES + FOLD_PER_BLOCK * most;
+}
+
 struct BinTab {
   int nv;
   int chunk;                  // pairs per chunk

@@ -22,9 +22,11 @@
 namespace gsr {
 
 // Blocks that an XCD takes at least: a small view's passes are faster on a few
-// XCDs, whose L2s hold what the pass before wrote, than spread over all (one view
-// of 1M pairs, about 70 blocks visible: 220 us a pass spread, 210 so).
-constexpr int XCD_BLOCKS = 16;
+// XCDs, whose L2s hold what the pass before wrote, than spread over all (two blocks
+// visible: 55.6 us for the sort spread, 50.9 so; ten blocks 63.9 and 60.8), but 16
+// at least leave XCDs idle that a call of 80 blocks fills (65.6, 59.8 with 8 or 1).
+// From 150 blocks on every value from 1 to 32 takes the same time.
+constexpr int XCD_BLOCKS = 8;
 
 // View, its keys [seg, end), number in the counts and keys [lo, hi) of visible
 // block i.
@@ -298,18 +300,11 @@ static void sort_passes(const SortTab& t, const StateDev& st, uint32_t* ka, uint
                      vb, (uint32_t*)nullptr, st.order);
 }
 
-// Blocks of a call (upper bound) up to which each scatter block walks its view's
-// counts itself: four launches less.  One view of 1M pairs (489 blocks) 462 ->
-// 454 us a pass, 8 views of 400k (1563) 1054 -> 1043; 48 views of 278k (6542)
-// 2934 -> 2965, where the walks cost more than the launches.
-constexpr int FOLD_BLOCKS = 2048;
-
 hipError_t launch_depth_sort(const SortTab& t, StateDev st, uint32_t* ka, uint32_t* va,
                              uint32_t* kb, uint32_t* vb, uint32_t* hist, uint32_t* off,
                              hipStream_t s) {
   if (t.sblk_off[t.nv] == 0) return hipSuccess;
-  (t.sblk_off[t.nv] <= FOLD_BLOCKS ? sort_passes<true> : sort_passes<false>)(t, st, ka, va, kb, vb, hist, off,
-                                                                  s);
+  (sort_folds(t) ? sort_passes<true> : sort_passes<false>)(t, st, ka, va, kb, vb, hist, off, s);
   return hipGetLastError();
 }
 

@@ -235,3 +235,26 @@ def test_key_pass_with_any_near_plane(z_near):
         vis = ek["zkeys"] != 0xFFFFFFFF
         behind += int((ek["zkeys"][vis].view(np.float32) < 0).sum())
     assert (behind > 0) == (z_near < 0)
+
+
+# one view of the most blocks whose sort goes without scan kernels, and of one more
+@pytest.mark.parametrize("n", [738 * 2048, 738 * 2048 + 1])
+def test_sort_of_one_large_view(n):
+    """A large view that sees everything: its depth order is the stable order of its
+    depth keys, with and without scan kernels."""
+    from paper_2605_10760_amd import Rasterizer, SceneTensors, ViewTensors
+    announce(f"sort one view {n}")
+    W, H = 64, 48
+    rng = np.random.default_rng(n)
+    means = np.stack([rng.uniform(-1, 1, n), rng.uniform(-1, 1, n), rng.uniform(3, 9, n)], 1)
+    scene = Scene(means, np.full((n, 3), -6.0), np.tile([1.0, 0.0, 0.0, 0.0], (n, 1)),
+                  np.ones(n), rng.random((n, 3)), set_offsets=np.array([0, n], np.int64))
+    vm = np.concatenate([np.eye(3), np.zeros((3, 1))], 1)[None]
+    views = Views(vm.astype(np.float32), np.array([pinhole(W, H, W / 2.0)], np.float32),
+                  np.zeros(1, np.int32), W, H)
+    st, vt = SceneTensors.from_numpy(scene), ViewTensors.from_numpy(views)
+    r = Rasterizer(W, H, n, 1, max_instances=3 * n)
+    *_, state = r.forward(st, vt)
+    e = r.debug_export(state, 1, n, 0)
+    assert int(e["vis_off"][1]) == n
+    np.testing.assert_array_equal(e["order"], np.argsort(e["zkeys"], kind="stable"))
