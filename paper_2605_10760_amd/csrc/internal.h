@@ -175,6 +175,60 @@ struct BinWork {
   unsigned long long* area_part;  // [<= VIS_GRID] (pair, tile) copies per counting workgroup
 };
 
+// SSIM: window, and the strips and rows of a call's workgroups.
+constexpr int SS_R = 5;                // window radius
+constexpr int SS_K = 2 * SS_R + 1;     // taps
+constexpr int SS_W = SS_K + 3;         // inputs of four neighbouring outputs
+constexpr int SS_MAXW = 4;             // waves per workgroup at most
+// statistics and output columns of a workgroup of nw waves
+constexpr int ss_stats(int nw) { return 4 * ((64 * nw - SS_W) / 4 + 1); }
+constexpr int ss_out(int nw) { return 4 * ((ss_stats(nw) - SS_W) / 4 + 1); }
+constexpr int SS_T = 32;               // tile edge the workspace is sized for
+constexpr int SS_SIMDS = 1024;         // of the device
+struct SsimShape {
+  int nw, strips, rows;  // waves per workgroup, workgroups across, output rows of one
+};
+inline SsimShape ssim_shape(int nv, int W, int H) {
+  SsimShape s{1, 0, SS_T};
+  const auto strips_of = [&](int k) { return (W + ss_out(k) - 1) / ss_out(k); };
+  // A call of few waves: a march's steps (four rows each, and three before the
+  // first) follow one another, about 2 us each, so the rows are as few as fill the
+  // SIMDs with one wave each, or with two where that, at 1.45 times the time a
+  // step, takes less: one view of 64 x 64 9.7 us, of 320 x 240 13.0, of 640 x 480
+  // 23.2.  Marches of 32 rows at least took 26, 28 and 30, and workgroups of 32 x
+  // 32 pixels with all blurs through LDS 11.7, 12.6 and 31.
+  const long waves32 = 3L * nv * strips_of(1) * ((H + SS_T - 1) / SS_T);
+  if (waves32 <= SS_SIMDS) {
+    s.strips = strips_of(1);
+    double best = 0.0;
+    for (int rows = 4; rows <= SS_T; rows += 4) {
+      const long waves = 3L * nv * s.strips * ((H + rows - 1) / rows);
+      if (waves > 2 * SS_SIMDS) continue;
+      const double cost = (rows / 4 + 3) * (waves <= SS_SIMDS ? 1.0 : 1.45);
+      if (best == 0.0 || cost < best) {
+        best = cost;
+        s.rows = rows;
+      }
+    }
+    return s;
+  }
+  // waves per workgroup: the fewest waves over the strips of a row (each strip
+  // recomputes two windows of columns), the larger workgroup on a tie (640
+  // columns: 3 x 4 waves 463 us, 4 x 3 572, 7 x 2 534, 16 x 1 585)
+  for (int k = 2; k <= SS_MAXW; ++k)
+    if (k * strips_of(k) <= s.nw * strips_of(s.nw)) s.nw = k;
+  s.strips = strips_of(s.nw);
+  // rows per workgroup: it recomputes the statistics of 12 rows, so long marches
+  // are cheaper, but about 8192 waves fill the chip (8 per SIMD); never below
+  // SS_T rows (the partials then fit the workspace)
+  const int waves = 3 * nv * s.strips * s.nw, most = (H + SS_T - 1) / SS_T;
+  int segs = (8192 + waves - 1) / waves;
+  segs = segs < 1 ? 1 : segs > most ? most : segs;
+  const int rows = ((H + segs - 1) / segs + 3) / 4 * 4;
+  s.rows = rows > SS_T ? rows : SS_T;
+  return s;
+}
+
 // Sim(3) corrections: Gaussian set offsets, and the set of every view.
 struct SimSetTab {
   int ns;

@@ -37,14 +37,6 @@
 
 namespace gsr {
 
-constexpr int SS_R = 5;                // window radius
-constexpr int SS_K = 2 * SS_R + 1;     // taps
-constexpr int SS_W = SS_K + 3;         // inputs of four neighbouring outputs
-constexpr int SS_MAXW = 4;             // waves per workgroup at most
-// statistics and output columns of a workgroup of nw waves
-constexpr int ss_stats(int nw) { return 4 * ((64 * nw - SS_W) / 4 + 1); }
-constexpr int ss_out(int nw) { return 4 * ((ss_stats(nw) - SS_W) / 4 + 1); }
-constexpr int SS_T = 32;               // tile edge the workspace is sized for
 constexpr float SS_C1 = 0.01f * 0.01f, SS_C2 = 0.03f * 0.03f;
 
 struct SsimArgs {
@@ -364,7 +356,9 @@ __global__ __launch_bounds__(64) void k_ssim_mean(int nv, const float* s_view, f
 static size_t align_up(size_t x) { return (x + 255) / 256 * 256; }
 
 size_t ssim_workspace_bytes(int nv, int W, int H) {
-  const size_t nb = (size_t)((W + SS_T - 1) / SS_T) * ((H + SS_T - 1) / SS_T) * 3 * nv;
+  // partials of a call: at most its 32 x 32 tiles, or a small call's waves
+  const size_t tiles = (size_t)((W + SS_T - 1) / SS_T) * ((H + SS_T - 1) / SS_T) * 3 * nv;
+  const size_t nb = std::max<size_t>(tiles, 2 * SS_SIMDS);
   return align_up(nb * 4) + align_up(nb * 8) + align_up((size_t)nv * 4);
 }
 
@@ -377,21 +371,11 @@ hipError_t launch_ssim(int nv, int W, int H, float weight, const float* color,
   for (int d = 0; d <= 2 * SS_R; ++d) A.w[d] = (float)(g[d] / tot);
   A.W = W;
   A.H = H;
-  // waves per workgroup: the fewest waves over the strips of a row (each strip
-  // recomputes two windows of columns), the larger workgroup on a tie (640
-  // columns: 3 x 4 waves 463 us, 4 x 3 572, 7 x 2 534, 16 x 1 585)
-  int nw = 1;
-  const auto strips_of = [&](int k) { return (W + ss_out(k) - 1) / ss_out(k); };
-  for (int k = 2; k <= SS_MAXW; ++k)
-    if (k * strips_of(k) <= nw * strips_of(nw)) nw = k;
-  A.TX = strips_of(nw);
+  const SsimShape sh = ssim_shape(nv, W, H);
+  const int nw = sh.nw;
+  A.TX = sh.strips;
   A.nv = nv;
-  // rows per workgroup: it recomputes the statistics of 12 rows, so long marches
-  // are cheaper, but about 8192 waves fill the chip (8 per SIMD); never below
-  // SS_T rows (the partials then fit the workspace)
-  const int waves = 3 * nv * A.TX * nw, most = (H + SS_T - 1) / SS_T;
-  const int segs = std::min(most, std::max(1, (8192 + waves - 1) / waves));
-  A.rows = std::max(SS_T, ((H + segs - 1) / segs + 3) / 4 * 4);
+  A.rows = sh.rows;
   const double n = 3.0 * nv * (double)W * H;
   A.weight_over_n = (float)(weight / n);
   const int nb_view = A.TX * ((H + A.rows - 1) / A.rows);

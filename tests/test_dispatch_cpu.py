@@ -40,3 +40,31 @@ def test_sort_without_scan_kernels(rule, views, want):
     setup = f"SortTab t{{}}; t.nv = {len(views)}; const int o[] = {{{','.join(map(str, off))}}};" \
             " for (int i = 0; i <= t.nv; ++i) t.sblk_off[i] = o[i];"
     assert rule("SORT_TILE == 2048") and rule("sort_folds(t)", setup) == want
+
+
+# views, width, height; most steps of a march and least waves of the call
+@pytest.mark.parametrize("nv,W,H,steps,waves", [
+    (1, 16, 16, 4, 12), (1, 64, 64, 4, 90), (1, 320, 240, 5, 700), (16, 64, 64, 5, 700),
+    (300, 32, 32, 7, 1800), (1, 40, 2000, 5, 700), (1, 640, 480, 9, 900)])
+def test_ssim_marches_of_small_calls(rule, nv, W, H, steps, waves):
+    setup = f"const SsimShape s = ssim_shape({nv}, {W}, {H});" \
+            f" const int n = 3 * {nv} * s.strips * (({H} + s.rows - 1) / s.rows) * s.nw;"
+    assert rule("s.rows / 4 + 3", setup) <= steps
+    assert waves <= rule("n", setup) <= 2048
+    # its columns and rows are covered, and the workspace holds its partials
+    assert rule("s.strips * ss_out(s.nw)", setup) >= W
+    from paper_2605_10760_amd import _lib
+    import ctypes as C
+    nb = C.c_size_t()
+    assert _lib.load().gsr_ssim_workspace_bytes(nv, W, H, C.byref(nb)) == _lib.GSR_OK
+    assert nb.value >= 12 * rule("n / s.nw", setup) + 4 * nv
+
+
+# the batches whose strips the GPU tests probe: waves of a workgroup
+@pytest.mark.parametrize("nv,W,H,nw", [
+    (172, 40, 33, 1), (172, 41, 5, 2), (58, 104, 37, 2), (58, 105, 33, 3), (35, 168, 64, 3),
+    (35, 169, 41, 4), (30, 232, 35, 4), (30, 233, 33, 3), (58, 104, 38, 2), (35, 168, 38, 3),
+    (30, 232, 38, 4), (48, 640, 480, 4)])
+def test_ssim_strips_of_batches(rule, nv, W, H, nw):
+    assert rule("s.nw", f"const SsimShape s = ssim_shape({nv}, {W}, {H});") == nw
+    assert rule("s.rows >= SS_T", f"const SsimShape s = ssim_shape({nv}, {W}, {H});")

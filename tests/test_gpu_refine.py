@@ -263,3 +263,64 @@ def test_ssim_exposure_sums_of_a_large_batch():
         part = d[:4].double()
         for i, t in enumerate((part * float(x[0, 0, 0, 0]), part)):
             assert _sum_err(de[:4, i], t) <= SSIM_ROUNDINGS * 2.0 ** -24, (k, i)
+
+
+# the strip edges of two to four waves again, in batches of more marches than the
+# device has SIMDs (smaller calls go by one-wave strips), and one wave there
+@pytest.mark.parametrize("V,H,W,nw", [(172, 33, 40, 1), (172, 5, 41, 2), (58, 37, 104, 2),
+                                      (58, 33, 105, 3), (35, 64, 168, 3), (35, 41, 169, 4),
+                                      (30, 35, 232, 4), (30, 33, 233, 3)])
+def test_ssim_grad_strip_edges_of_batches(V, H, W, nw):
+    announce(f"ssim strips of batches {V}x{H}x{W}")
+    import torch
+    from oracle.ssim import ssim, ssim_term_grad
+    from paper_2605_10760_amd import ssim_grad
+    rng = np.random.default_rng(H * 1000 + W + V)
+    c = rng.random((V, 3, H, W)).astype(np.float32)
+    tgt = np.clip(c + 0.1 * rng.standard_normal(c.shape), 0, 1).astype(np.float32)
+    ex = np.stack([rng.normal(0, 0.1, V), rng.normal(0, 0.02, V)], 1).astype(np.float32)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    d_color = torch.full((V, 3, H, W), 0.5, device="cuda")
+    d_exp = torch.zeros((V, 2), device="cuda")
+    out = torch.zeros(1, device="cuda")
+    weight = 0.2 * c.size  # gradients of order one next to the 0.5 they add to
+    ssim_grad(t(c), t(tgt), d_color, t(ex), d_exp, weight, ssim_out=out)
+    xt = np.exp(ex[:, 0])[:, None, None, None] * c.astype(np.float64) + ex[:, 1][:, None, None, None]
+    assert abs(out.item() - ssim(xt, tgt)) <= 2e-5
+    got = d_color.cpu().numpy().astype(np.float64) - 0.5
+    ge = d_exp.cpu().numpy()
+    for v in (0, V // 2, V - 1):
+        one = slice(v, v + 1)
+        ref = ssim_term_grad(c[one], tgt[one], ex[one, 0], ex[one, 1], weight / V)
+        want = ref["d_color"][0]
+        assert np.abs(got[v] - want).max() <= 1e-3 * np.abs(want).max(), v
+        for k, key in ((0, "d_a"), (1, "d_b")):
+            assert abs(ge[v, k] - ref[key][0]) <= 1e-3 * np.abs(want).sum(), (v, key)
+
+
+@pytest.mark.parametrize("V,W", [(58, 104), (35, 168), (30, 232)])
+def test_ssim_grad_non_finite_stays_local_in_batches(V, W):
+    """As for one view, in workgroups of two to four waves, which agree on the way
+    they sum: nothing but the bad pixel's two windows in its own view changes."""
+    announce(f"ssim non-finite in batches {V} W={W}")
+    import torch
+    from paper_2605_10760_amd import ssim_grad
+    H = 38
+    rng = np.random.default_rng(W)
+    c = torch.from_numpy(rng.random((V, 3, H, W)).astype(np.float32)).cuda()
+    tgt = torch.from_numpy(rng.random((V, 3, H, W)).astype(np.float32)).cuda()
+    v, pj, pi = V // 2, 17, W - 30
+    grads = []
+    for bad in (False, True):
+        if bad:
+            c[v, 1, pj, pi] = float("nan")
+        d = torch.zeros_like(c)
+        ssim_grad(c, tgt, d, None, None, float(c.numel()))
+        grads.append(d.clone())
+    local = torch.zeros_like(c, dtype=torch.bool)
+    local[v, 1, max(pj - 10, 0):pj + 11, max(pi - 10, 0):pi + 11] = True
+    a, b = grads
+    assert bool(torch.isfinite(a).all()) and bool((torch.isfinite(b) | local).all())
+    assert bool(torch.isnan(b[v, 1, pj, pi]))
+    assert float(((a - b).abs() * ~local).nan_to_num().max()) <= 1e-3 * float(a.abs().max())
+    assert torch.equal(a[:v], b[:v]) and torch.equal(a[v + 1:], b[v + 1:])
