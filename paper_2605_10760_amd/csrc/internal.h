@@ -262,6 +262,28 @@ struct RenderCfg {
   int bwd_cols;
   bool persistent;
 };
+// Whether the tiles of a call (of `blocks` 8x8 blocks each) go to a workgroup each
+// instead of a wave each, where the plan does not ask for the persistent queue.
+// The workgroup form spends more instructions per entry and far less time per
+// tile: it wins until its waves, one per block, fill the device a few times
+// over, so the line lies at their number.  A tile of one or two blocks gains
+// less from its workgroup and pays its barriers, so its line lies earlier.  One-wave
+// form | workgroup form, us, of 300k Gaussians in 640x480 views (48,000 blocks are ten
+// of them):
+//   forward, 16x16: 1 view 67 | 37, 2 69 | 55, 6 130 | 131, 16 260 | 300;
+//     32x16: 1 view 114 | 39, 6 150 | 145, 16 297 | 344; 16x8: 1 50 | 37, 2 60 | 59, 6
+//     128 | 133; 8x8: 320x240 35 | 32, 640x480 41 | 41, 2 62 | 64, 6 143 | 157;
+//   backward, 16x16: 1 view 121 | 80, 2 132 | 134, 6 270 | 343; 32x16: 1 view 164 | 97,
+//     2 165 | 161, 1200x680 147 | 181, 6 256 | 412; 16x8: 1 130 | 112, 2 160 | 174; 8x8:
+//     320x240 82 | 80, 640x480 188 | 204.
+inline bool fwd_by_workgroup(long tiles, int blocks) {
+  const long most = 5000L * blocks * blocks;
+  return tiles * blocks <= (most < 40000 ? most : 40000);
+}
+inline bool bwd_by_workgroup(long tiles, int blocks) {
+  const long most = 2500L * blocks;
+  return tiles * blocks <= (most < 10000 ? most : 10000);
+}
 hipError_t launch_tile_order(int nv, int TX, int TY, StateDev st, unsigned int* sched,
                              hipStream_t s);
 hipError_t launch_render_fwd(int nv, int W, int H, int TW, int TH, int TX, int TY,

@@ -1372,15 +1372,6 @@ static int resident_blocks(const void* kernel, int threads) {
 // its longest tile ended: 0.72 -> 0.70 ms forward, 1.46 -> 1.39 ms backward)
 constexpr int FWD_TPW = 1;
 
-// Largest call (tiles) whose tiles go to a workgroup each instead of a wave
-// each, where neither the plan asks for the persistent queue.  The workgroup
-// form spends more instructions per entry and far less time per tile.
-// Forward (16x16 tiles, one-wave form -> workgroup form): 48 tiles 94 -> 40 us,
-// 3,225 tiles (1200x680) 86 -> 64 us, 7,425 tiles 168 -> 134 us, 9,600 tiles
-// 167 -> 160 us, 57,600 tiles 684 -> 851 us.  Backward: 48 tiles 166 -> 70 us,
-// 105 tiles 270 -> 137 us, 3,225 tiles 163 -> 165 us, 7,425 tiles 309 -> 347 us.
-constexpr int FWD_COOP_TILES = 10000, BWD_COOP_TILES = 2500;
-
 template <int TW, int TH, int FB, bool NEVAL>
 static void fwd_fbn(int nv, int W, int H, int TX, int TY, bool persist, const CamDev& cam,
                     StateDev st, unsigned int* sched, float* color, float* depth, float* alpha,
@@ -1417,7 +1408,7 @@ static hipError_t fwd_t(int nv, int W, int H, int TX, int TY, const RenderCfg& r
                         const CamDev& cam, StateDev st, unsigned int* sched, float* color,
                         float* depth, float* alpha, int32_t* n_eval, hipStream_t s) {
   const int nt = nv * TX * TY;
-  if (!rc.persistent && nt <= FWD_COOP_TILES) {
+  if (!rc.persistent && fwd_by_workgroup(nt, TW * TH / 64)) {
     const auto k = n_eval ? k_render_fwd_coop<TW, TH, true> : k_render_fwd_coop<TW, TH, false>;
     hipLaunchKernelGGL(k, dim3(xcd_grid_mixed(nt)), dim3(TW * TH), 0, s, nt, W, H, TX, TY, cam, st,
                        color, depth, alpha, n_eval);
@@ -1469,7 +1460,7 @@ static hipError_t bwd_t(int nv, int W, int H, int TX, int TY, const RenderCfg& r
                         unsigned int* sched, const float* gc, const float* gd, const float* ga,
                         float* grad2d, hipStream_t s) {
   const int nt = nv * TX * TY;
-  if (!rc.persistent && nt <= BWD_COOP_TILES) {
+  if (!rc.persistent && bwd_by_workgroup(nt, TW * TH / 64)) {
     hipLaunchKernelGGL((k_render_bwd_coop<TW, TH>), dim3(xcd_grid_mixed(nt)), dim3(TW * TH), 0, s,
                        nt, W, H, TX, TY, mask, cam, st, gc, gd, ga, grad2d);
     return hipGetLastError();

@@ -68,3 +68,19 @@ def test_ssim_marches_of_small_calls(rule, nv, W, H, steps, waves):
 def test_ssim_strips_of_batches(rule, nv, W, H, nw):
     assert rule("s.nw", f"const SsimShape s = ssim_shape({nv}, {W}, {H});") == nw
     assert rule("s.rows >= SS_T", f"const SsimShape s = ssim_shape({nv}, {W}, {H});")
+
+
+# 8x8 blocks of a tile, tiles, whether a workgroup takes a tile: the faster form of
+# the two as measured (views of 640x480 or 1200x680), and the calls that the GPU
+# tests render both ways
+@pytest.mark.parametrize("blocks,tiles,fwd,bwd", [
+    (4, 48, 1, 1), (4, 1200, 1, 1), (4, 3225, 1, 0), (4, 9600, 1, 0), (4, 19200, 0, 0),
+    (8, 150, 1, 1), (8, 1200, 1, 1), (8, 1634, 1, 0), (8, 3600, 1, 0), (8, 9600, 0, 0),
+    (2, 2400, 1, 1), (2, 4800, 1, 0), (2, 14400, 0, 0), (1, 1200, 1, 1), (1, 4800, 1, 0),
+    (1, 9600, 0, 0), (1, 28800, 0, 0),
+    (4, 2450, 1, 1), (4, 12250, 0, 0), (8, 2145, 1, 0), (8, 10725, 0, 0), (1, 2450, 1, 1),
+    (1, 12250, 0, 0), (8, 1225, 1, 1), (8, 11025, 0, 0), (2, 2450, 1, 1), (2, 12250, 0, 0),
+    (4, 10816, 0, 0)])
+def test_compositing_by_workgroup(rule, blocks, tiles, fwd, bwd):
+    assert rule(f"fwd_by_workgroup({tiles}, {blocks})") == fwd
+    assert rule(f"bwd_by_workgroup({tiles}, {blocks})") == bwd

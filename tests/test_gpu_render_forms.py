@@ -258,3 +258,12 @@ def test_sort_of_one_large_view(n):
     e = r.debug_export(state, 1, n, 0)
     assert int(e["vis_off"][1]) == n
     np.testing.assert_array_equal(e["order"], np.argsort(e["zkeys"], kind="stable"))
+
+
+# the other tile shapes, and the two of eight blocks with views of 1,225 tiles, up
+# to which their backward takes a workgroup per tile
+@pytest.mark.parametrize("tile,cols,W,H,n_views", [
+    ((32, 16), 1, 1113, 555, 9), ((16, 32), 1, 555, 1111, 9), ((16, 8), 2, 779, 400, 5),
+    ((8, 16), 2, 397, 783, 5), ((32, 8), 1, 1561, 397, 5)])
+def test_forms_of_every_tile_shape(tile, cols, W, H, n_views):
+    test_wave_and_workgroup_forms(tile, cols, W, H, n_views)
