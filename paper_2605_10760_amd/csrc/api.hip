@@ -61,17 +61,6 @@ int ceil_div(long a, long b) { return (int)((a + b - 1) / b); }
 
 bool pow2_tile(int x) { return x == 8 || x == 16 || x == 32; }
 
-int auto_chunk(const gsr_plan_desc& p) {
-  if (p.chunk > 0) return p.chunk;
-  // 64..256 depth-sorted pairs per chunk: small batches (one view) need many
-  // chunks to fill the GPU; large ones use longer per-tile runs per chunk.  One
-  // view of 1M pairs: 422 us a pass with 64, 426 with 256; 8 views of 400k: 925
-  // and 905.
-  long c = 64;
-  while (c < 256 && p.max_pairs / c > 16384) c *= 2;
-  return (int)c;
-}
-
 // RAII guard that makes ctx->device current and restores the caller's.
 struct DeviceGuard {
   int prev = -1;
@@ -412,7 +401,7 @@ gsr_status gsr_plan(gsr_ctx* c, const gsr_plan_desc* p) {
   DeviceGuard g(c->device);
   free_ws(c);
   c->plan = *p;
-  c->chunk = auto_chunk(*p);
+  c->chunk = p->chunk > 0 ? p->chunk : auto_chunk((long)p->max_pairs);
   c->TX = (p->width + p->tile_w - 1) / p->tile_w;
   c->TY = (p->height + p->tile_h - 1) / p->tile_h;
   c->T = c->TX * c->TY;

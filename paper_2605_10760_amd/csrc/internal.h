@@ -30,6 +30,12 @@ inline int vis_grid(size_t bound) {
   return (int)((bound < (size_t)VIS_GRID ? bound : (size_t)VIS_GRID) + 7) / 8 * 8;
 }
 constexpr int MAX_CHUNK = 256;   // depth-sorted pairs per row-binning chunk
+// Depth-sorted pairs per chunk where the plan leaves it open: small calls need many
+// chunks to fill the device, large ones take longer runs per chunk.  Binning with
+// 64 | 128 | 256, us: 8 views of 50k pairs 31 | 32 | 32, one of 600k 39 | 36 | 38, 8 of
+// 130k 42 | 37 | 37, 48 of 25k 38 | 34 | 35, one of 1.5M 65 | 49 | 45, 8 of 200k 55 | 45 |
+// 40, one of 3M 105 | 80 | 68.
+inline int auto_chunk(long pairs) { return pairs <= 640000 ? 64 : pairs <= 1280000 ? 128 : 256; }
 constexpr int RC_SUB = 4;        // row-binning chunks per counting workgroup
 constexpr int SCHED_WORDS = 2 + 2 * 33;  // tile cursors + length-bucket counts (render.hip)
 constexpr int GSR_MAX_DEVICES = 64;  // devices with a looked-up library-held buffer

@@ -84,3 +84,9 @@ def test_ssim_strips_of_batches(rule, nv, W, H, nw):
 def test_compositing_by_workgroup(rule, blocks, tiles, fwd, bwd):
     assert rule(f"fwd_by_workgroup({tiles}, {blocks})") == fwd
     assert rule(f"bwd_by_workgroup({tiles}, {blocks})") == bwd
+
+
+@pytest.mark.parametrize("pairs,want", [(400000, 64), (800000, 128), (1000000, 128),
+                                        (1200000, 128), (1500000, 256), (3000000, 256)])
+def test_chunk_of_an_open_plan(rule, pairs, want):
+    assert rule(f"auto_chunk({pairs})") == want
