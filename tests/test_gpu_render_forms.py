@@ -8,7 +8,9 @@ run over float atomics in no fixed order in either form)."""
 import numpy as np
 import pytest
 
-from gpu_harness import RERUN_TOL, announce
+from gpu_harness import (GMAP, GRAD_TOL, IMG_TOL, RERUN_TOL, announce, check_ambiguous_pixels,
+                         grad_rel_err)
+from oracle.render import Settings, render_backward, render_view
 from synth.scenes import ROOM_HI, ROOM_LO, Scene, Views, draw_gaussians, look_at, pinhole
 
 pytestmark = pytest.mark.gpu
@@ -267,3 +269,90 @@ def test_sort_of_one_large_view(n):
     ((8, 16), 2, 397, 783, 5), ((32, 8), 1, 1561, 397, 5)])
 def test_forms_of_every_tile_shape(tile, cols, W, H, n_views):
     test_wave_and_workgroup_forms(tile, cols, W, H, n_views)
+
+
+# entries per lane of the forward and the backward, tiles per backward wave
+@pytest.mark.parametrize("fb,bb,cols", [(1, 1, 1), (2, 2, 1), (2, 4, 1), (1, 1, 2), (1, 2, 2),
+                                        (2, 4, 2)])
+def test_one_wave_options_against_oracle(fb, bb, cols):
+    """A call of more tiles than go to workgroups, so that the plan's options
+    choose the one-wave kernels of either direction: images, entry counts and the
+    gradients of two views against the oracle."""
+    import torch
+    from paper_2605_10760_amd import Rasterizer, SceneTensors, ViewTensors
+    announce(f"one-wave options fb={fb} bb={bb} cols={cols}")
+    W, H, n_views, n = 203, 205, 64, 20000
+    assert n_views * 13 * 13 * 4 > 40000  # 8x8 blocks of the call
+    scene, views = _case(n, n_views, W, H)
+    scene.opacity_logits -= 2.0  # pixels walk up to 540 entries: several rounds
+    st, vt = SceneTensors.from_numpy(scene), ViewTensors.from_numpy(views)
+    r = Rasterizer(W, H, n_views * n, n_views, fwd_batch=fb, bwd_batch=bb, bwd_cols=cols)
+    c, d, a, state, ne = r.forward(st, vt, n_eval=True)
+    c2, d2, a2, _ = r.forward(st, vt)
+    assert torch.equal(c, c2) and torch.equal(d, d2) and torch.equal(a, a2)
+    ids = (7, 40)
+    g = {k: {q: x[k].cpu().numpy() for q, x in (("color", c), ("depth", d), ("alpha", a),
+                                                ("n_eval", ne))} for k in ids}
+    rng = np.random.default_rng(12)
+    up = [np.zeros((n_views,) + s, np.float32) for s in ((3, H, W), (H, W), (H, W))]
+    for k in ids:
+        o = render_view(scene, views, k, Settings())
+        ok = ~o["ambiguous"]
+        assert o["last"].max() > 256
+        zmax = max(1.0, float(np.max(o["setup"]["pr"]["z"], initial=0.0)))
+        assert np.abs(g[k]["color"] - o["color"])[:, ok].max() <= IMG_TOL
+        assert np.abs(g[k]["alpha"] - o["alpha"])[ok].max() <= IMG_TOL
+        assert np.abs(g[k]["depth"] - o["depth"])[ok].max() <= IMG_TOL * zmax
+        np.testing.assert_array_equal(g[k]["n_eval"][ok], o["n_eval"][ok])
+        per_view = {q: {k: g[k][q]} for q in g[k]}
+        check_ambiguous_pixels(per_view, k, o, views, Settings(), zmax)
+        for u in up:
+            u[k] = rng.normal(size=u[k].shape) * ok
+    got = r.backward(st, vt, state, *[torch.from_numpy(u).cuda() for u in up])
+    ref = render_backward(scene, views, *up, view_ids=ids)
+    for k_gpu, k_ref in GMAP.items():
+        e_inf, e_2 = grad_rel_err(got[k_gpu].cpu().numpy(), ref[k_ref])
+        assert e_inf <= GRAD_TOL and e_2 <= GRAD_TOL, (k_gpu, e_inf, e_2)
+
+
+# as test_blocks_of_visible_pairs: chunks that end on a view's last pair, views that
+# see none of their pairs
+@pytest.mark.parametrize("n,n_views,chunk", [(2048, 9, 64), (2049, 64, 0), (20011, 33, 100)])
+def test_tile_lists_of_visible_pairs(n, n_views, chunk):
+    """Views that see everything, some or nothing, in one call and one call each:
+    the same rectangles, tile ranges and lists."""
+    from paper_2605_10760_amd import Rasterizer, SceneTensors, ViewTensors
+    announce(f"visible lists {n} {n_views} {chunk}")
+    W, H = 70, 53
+    scene, views = _case(n, n_views, W, H)
+    for k in range(n_views):
+        if k % 3 != 1:
+            views.viewmats[k, :, :3] = np.diag([1.0, 1.0, 1.0 if k % 3 == 0 else -1.0])
+            views.viewmats[k, :, 3] = (0.0, 0.0, 12.0 if k % 3 == 0 else -12.0)
+    scene.opacity_logits[:] = np.maximum(scene.opacity_logits, -1.0)
+    st, vt = SceneTensors.from_numpy(scene), ViewTensors.from_numpy(views)
+    big = Rasterizer(W, H, n_views * n, n_views, chunk=chunk)
+    *_, state = big.forward(st, vt)
+    counts = big.poll(state)
+    dbg = big.debug_export(state, n_views, n_views * n, counts["instances"])
+    T = dbg["TX"] * dbg["TY"]
+    one = Rasterizer(W, H, n, 1, chunk=chunk)
+    total = 0
+    for k in range(n_views):
+        *_, sk = one.forward(st, vt.select([k]))
+        ck = one.poll(sk)
+        total += ck["instances"]
+        if k >= 7 and k != n_views - 1:
+            continue
+        ek = one.debug_export(sk, 1, n, ck["instances"])
+        np.testing.assert_array_equal(dbg["rects"][k * n:(k + 1) * n], ek["rects"])
+        lens = lambda r: (r[:, 1] - r[:, 0]).astype(np.int64)
+        rg = dbg["ranges"][k * T:(k + 1) * T]
+        np.testing.assert_array_equal(lens(rg), lens(ek["ranges"]))
+        assert lens(rg).sum() == ck["instances"]
+        for t in np.nonzero(lens(rg))[0]:
+            np.testing.assert_array_equal(dbg["inst"][rg[t, 0]:rg[t, 1]].astype(np.int64) - k * n,
+                                          ek["inst"][ek["ranges"][t, 0]:ek["ranges"][t, 1]])
+        if k % 3 != 1:
+            assert (ck["instances"] > n) == (k % 3 == 0) and ck["instances"] >= 0
+    assert total == counts["instances"]
