@@ -1083,6 +1083,16 @@ gsr_status gsr_autotune(int device, const gsr_plan_desc* base, const gsr_scene* 
       }
     }
     if (check_plan(nullptr, &p) != GSR_OK) continue;
+    // an option of the one-wave kernels on a call whose tiles go to workgroups: the
+    // same kernels as without it, timed already
+    if (!p.persistent) {
+      const long nt = (long)V * ceil_div(W, p.tile_w) * ceil_div(H, p.tile_h);
+      const int nb = p.tile_w * p.tile_h / 64;
+      if ((p.fwd_batch > 1 && p.fwd_batch != best_p.fwd_batch && fwd_by_workgroup(nt, nb)) ||
+          (p.bwd_batch > 1 && p.bwd_batch != best_p.bwd_batch && bwd_by_workgroup(nt, nb)) ||
+          (ci < NT_ && p.bwd_cols > 1 && bwd_by_workgroup(nt, nb)))
+        continue;
+    }
     gsr_ctx* ctx = nullptr;
     if (gsr_create(&ctx, device) != GSR_OK) { result = GSR_E_DEVICE; break; }
     void* state = nullptr;

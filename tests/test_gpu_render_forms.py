@@ -356,3 +356,14 @@ def test_tile_lists_of_visible_pairs(n, n_views, chunk):
         if k % 3 != 1:
             assert (ck["instances"] > n) == (k % 3 == 0) and ck["instances"] >= 0
     assert total == counts["instances"]
+
+
+def test_autotune_of_a_small_call():
+    """Options of the one-wave kernels are not chosen for a call whose tiles go to
+    workgroups, where they change nothing but the noise of a timing."""
+    from paper_2605_10760_amd import SceneTensors, ViewTensors, autotune
+    announce("autotune small call")
+    scene, views = _case(3000, 2, 150, 90)
+    best = autotune(SceneTensors.from_numpy(scene), ViewTensors.from_numpy(views))
+    assert (best["fwd_batch"], best["bwd_batch"], best["bwd_cols"]) == (1, 1, 1)
+    assert best["ms"] > 0
