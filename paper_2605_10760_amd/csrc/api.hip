@@ -269,6 +269,8 @@ gsr_status build_tabs(gsr_ctx* c, const gsr_scene* sc, const gsr_views* vw, Call
   st.set_goff[sc->n_sets] = (int)sc->set_offsets[sc->n_sets];
   st.set_blk[sc->n_sets] = sb;
   st.set_voff[sc->n_sets] = nvs;
+  for (int s = 0; s < sc->n_sets; ++s)
+    st.most = std::max(st.most, st.set_voff[s + 1] - st.set_voff[s]);
   for (int v = 0; v <= nv; ++v) st.blk_off[v] = t.pt.blk_off[v];
   return GSR_OK;
 }

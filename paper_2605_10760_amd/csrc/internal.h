@@ -95,6 +95,7 @@ struct BinTab {
 
 struct SetTab {
   int ns, nv;
+  int most;                   // grad-needing views of the set that has the most
   int set_goff[MAXS + 1];     // Gaussian offsets of the sets
   int set_blk[MAXS + 1];      // PROJ_BLOCK-Gaussian blocks per set, prefix
   int set_voff[MAXS + 1];     // views of each set in view_by_set

@@ -61,18 +61,13 @@ __device__ __forceinline__ void sh_eval_grad(float x, float y, float z, float* Y
   }
 }
 
-// Normalised quaternion, scales and rotation matrix of a Gaussian (identity
-// and unit scales for an invalid slot); returns the quaternion's norm.
-__device__ __forceinline__ float rot_scale(bool valid, const float* lsv, const float* q4v,
-                                           float* qh, float* sv, float (*R)[3]) {
-  float qn = 1.f;
-  qh[0] = 1.f; qh[1] = qh[2] = qh[3] = 0.f;
-  sv[0] = sv[1] = sv[2] = 1.f;
-  if (valid) {
-    for (int k = 0; k < 3; ++k) sv[k] = expf(lsv[k]);
-    qn = sqrtf(q4v[0] * q4v[0] + q4v[1] * q4v[1] + q4v[2] * q4v[2] + q4v[3] * q4v[3]);
-    for (int k = 0; k < 4; ++k) qh[k] = q4v[k] / qn;
-  }
+// Normalised quaternion, scales and rotation matrix of a Gaussian; returns the
+// quaternion's norm.
+__device__ __forceinline__ float rot_scale(const float* lsv, const float* q4v, float* qh, float* sv,
+                                           float (*R)[3]) {
+  for (int k = 0; k < 3; ++k) sv[k] = expf(lsv[k]);
+  const float qn = sqrtf(q4v[0] * q4v[0] + q4v[1] * q4v[1] + q4v[2] * q4v[2] + q4v[3] * q4v[3]);
+  for (int k = 0; k < 4; ++k) qh[k] = q4v[k] / qn;
   const float w = qh[0], x = qh[1], y = qh[2], z = qh[3];
   R[0][0] = 1.f - 2.f * (y * y + z * z); R[0][1] = 2.f * (x * y - w * z); R[0][2] = 2.f * (x * z + w * y);
   R[1][0] = 2.f * (x * y + w * z); R[1][1] = 1.f - 2.f * (x * x + z * z); R[1][2] = 2.f * (y * z - w * x);
@@ -255,7 +250,15 @@ __device__ __forceinline__ void pair_bwd(const BwdView& w, const float* m, const
 // 1196 us), and the last workgroup to finish writes d_pose and clears them for the next call (no
 // clearing kernel, and the rounding of thousands of FP32 additions per
 // component does not reach the result).
-template <int SHD>
+// SPLIT: a loop for each way.  One loop for both keeps the registers of degrees 1 to 3
+// within 125, 124 and 167 (152, 190 and 246 with two), and the LDS of up to 26 views
+// leaves degree 3 room for three workgroups a CU: one view of 1M Gaussians 51 -> 45 us,
+// 90 -> 79 and 124 -> 109, 8 views of 400k of degree 3 151 -> 128.  Two loops are faster for
+// degree 0 (8 views of each of six submaps 162 -> 153) and, from degree 2 on, for more
+// views (64 views of 400k of degree 2 763 -> 643, 32 of 2M of degree 3 1488 -> 1318).
+constexpr size_t BWD_VIEW_BYTES = 64 + 48 + 16 + 32 + 16;  // LDS of a view
+constexpr int BWD_ONE_LOOP = 26;                           // views
+template <int SHD, bool SPLIT>
 __global__ __launch_bounds__(256) void k_project_bwd(SetTab t, SceneDev sc, CamDev cam, StateDev st,
                                                      float* grad2d, PoseAcc* pa, gsr_grads out) {
   constexpr int NB = (SHD + 1) * (SHD + 1);
@@ -272,13 +275,22 @@ __global__ __launch_bounds__(256) void k_project_bwd(SetTab t, SceneDev sc, CamD
   const bool valid = local < nset;
   const long gi = (long)t.set_goff[s] + (valid ? local : 0);
 
-  // the set's views: parameters, and per wave the visible bits and the position
-  // of the first visible pair
-  __shared__ float4 vw[MAXV][4];  // (R row, t component) x 3, (fx, fy, limits)
-  __shared__ double vlim[MAXV][2];
-  __shared__ unsigned long long vmask[MAXV][4];
-  __shared__ uint32_t vrow[MAXV][4];
-  __shared__ double psum[MAXV][6];
+  // the set's views: parameters, pose sums, and per wave the visible bits and the
+  // position of the first visible pair (SPLIT: at fixed addresses, else as many as
+  // the largest set has)
+  constexpr int NV = SPLIT ? MAXV : 1;
+  __shared__ float4 vw_s[NV][4];  // (R row, t component) x 3, (fx, fy, limits)
+  __shared__ double psum_s[NV][6], vlim_s[NV][2];
+  __shared__ unsigned long long vmask_s[NV][4];
+  __shared__ uint32_t vrow_s[NV][4];
+  extern __shared__ float4 views_lds[];
+  const int most = SPLIT ? 0 : t.most;
+  float4 (*vw)[4] = SPLIT ? vw_s : reinterpret_cast<float4(*)[4]>(views_lds);
+  double (*psum)[6] = SPLIT ? psum_s : reinterpret_cast<double(*)[6]>(vw + most);
+  double (*vlim)[2] = SPLIT ? vlim_s : reinterpret_cast<double(*)[2]>(psum + most);
+  unsigned long long (*vmask)[4] =
+      SPLIT ? vmask_s : reinterpret_cast<unsigned long long(*)[4]>(vlim + most);
+  uint32_t (*vrow)[4] = SPLIT ? vrow_s : reinterpret_cast<uint32_t(*)[4]>(vmask + most);
   if ((int)threadIdx.x < nv) {
     const int v = t.view_by_set[v0 + (int)threadIdx.x];
     const float* vm = cam.viewmats + 12 * v;
@@ -366,34 +378,65 @@ __global__ __launch_bounds__(256) void k_project_bwd(SetTab t, SceneDev sc, CamD
   int steps = (int)__popcll(see);
   for (int d = 1; d < 64; d *= 2) steps = max(steps, __shfl_xor(steps, d));
   steps = __builtin_amdgcn_readfirstlane(steps);
-  if (4 * steps < 3 * (int)__popcll(any)) {
-    // in cyclic order from view `first`
-    const int first = (lane_id() * nv) >> 6;
-    unsigned long long hi = see & (~0ull << first), lo = see & ~(~0ull << first);
-    while (hi | lo) {
-      const int k = (int)__builtin_ctzll(hi ? hi : lo);
+  // `own`: the lane's views in cyclic order from view `first` (hi, then lo); in turn:
+  // the views that see one of the wave's Gaussians
+  const bool own = 4 * steps < 3 * (int)__popcll(any);
+  if constexpr (SPLIT) {
+    if (own) {
+      const int first = (lane_id() * nv) >> 6;
+      unsigned long long hi = see & (~0ull << first), lo = see & ~(~0ull << first);
+      while (hi | lo) {
+        const int k = (int)__builtin_ctzll(hi ? hi : lo);
+        if (hi)
+          hi &= hi - 1ull;
+        else
+          lo &= lo - 1ull;
+        float g10[GRAD2D], pose[6];
+        read_row(k, g10);
+        pair_bwd<SHD>(load_view(k), m, Sd, g10, kk, G, gk, 256, pose);
+#pragma unroll
+        for (int i = 0; i < 6; ++i) unsafeAtomicAdd(&psum[k][i], (double)pose[i]);
+      }
+    } else {
+      while (any) {
+        const int k = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(any));
+        any &= any - 1ull;
+        float pose[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if ((see >> k) & 1ull) {
+          float g10[GRAD2D];
+          read_row(k, g10);
+          pair_bwd<SHD>(load_view(k), m, Sd, g10, kk, G, gk, 256, pose);
+        }
+        for (int i = 0; i < 6; ++i) pose[i] = wave_total(pose[i]);
+        if (lane_id() == 0)
+          for (int i = 0; i < 6; ++i) unsafeAtomicAdd(&psum[k][i], (double)pose[i]);
+      }
+    }
+  } else {
+    const int first = own ? (lane_id() * nv) >> 6 : 0;
+    const unsigned long long walk = own ? see : any;
+    unsigned long long hi = walk & (~0ull << first), lo = walk & ~(~0ull << first);
+    while (__ballot((hi | lo) != 0ull) != 0ull) {
+      int k = (hi | lo) != 0ull ? (int)__builtin_ctzll(hi ? hi : lo) : 0;
+      bool on = (hi | lo) != 0ull;
       if (hi)
         hi &= hi - 1ull;
       else
         lo &= lo - 1ull;
-      float g10[GRAD2D], pose[6];
-      read_row(k, g10);
-      pair_bwd<SHD>(load_view(k), m, Sd, g10, kk, G, gk, 256, pose);
-#pragma unroll
-      for (int i = 0; i < 6; ++i) unsafeAtomicAdd(&psum[k][i], (double)pose[i]);
-    }
-  } else {
-    while (any) {
-      const int k = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(any));
-      any &= any - 1ull;
+      if (!own) {
+        k = __builtin_amdgcn_readfirstlane(k);
+        on = (see >> k) & 1ull;
+      }
       float pose[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      if ((see >> k) & 1ull) {
+      if (on) {
         float g10[GRAD2D];
         read_row(k, g10);
         pair_bwd<SHD>(load_view(k), m, Sd, g10, kk, G, gk, 256, pose);
       }
-      for (int i = 0; i < 6; ++i) pose[i] = wave_total(pose[i]);
-      if (lane_id() == 0)
+      if (!own)
+        for (int i = 0; i < 6; ++i) pose[i] = wave_total(pose[i]);
+      if (own ? on : lane_id() == 0)
+#pragma unroll
         for (int i = 0; i < 6; ++i) unsafeAtomicAdd(&psum[k][i], (double)pose[i]);
     }
   }
@@ -453,7 +496,7 @@ __global__ __launch_bounds__(256) void k_project_bwd(SetTab t, SceneDev sc, CamD
     for (int k = 0; k < 3; ++k) lsv[k] = sc.log_scales[3 * gi + k];
     const float4 q4 = *reinterpret_cast<const float4*>(sc.quats + 4 * gi);
     q4v[0] = q4.x; q4v[1] = q4.y; q4v[2] = q4.z; q4v[3] = q4.w;
-    qn = rot_scale(true, lsv, q4v, qh, sv, R);
+    qn = rot_scale(lsv, q4v, qh, sv, R);
   }
   for (int i = 0; i < 3; ++i)
     for (int j = 0; j < 3; ++j) M[i][j] = R[i][j] * sv[j];
@@ -504,11 +547,13 @@ hipError_t launch_project_bwd(const SetTab& t, const SceneDev& sc, const CamDev&
                               hipStream_t s) {
   const int nb = t.set_blk[t.ns];
   if (nb == 0) return hipSuccess;
-  const auto k = sc.sh_degree == 0   ? k_project_bwd<0>
-                 : sc.sh_degree == 1 ? k_project_bwd<1>
-                 : sc.sh_degree == 2 ? k_project_bwd<2>
-                                     : k_project_bwd<3>;
-  hipLaunchKernelGGL(k, dim3(xcd_grid(nb)), dim3(256), 0, s, t, sc, cam, st, grad2d, pa, g);
+  const bool split = sc.sh_degree == 0 || (sc.sh_degree > 1 && t.most > BWD_ONE_LOOP);
+  const auto k = sc.sh_degree == 0   ? k_project_bwd<0, true>
+                 : sc.sh_degree == 1 ? k_project_bwd<1, false>
+                 : sc.sh_degree == 2 ? (split ? k_project_bwd<2, true> : k_project_bwd<2, false>)
+                                     : (split ? k_project_bwd<3, true> : k_project_bwd<3, false>);
+  hipLaunchKernelGGL(k, dim3(xcd_grid(nb)), dim3(256), split ? 0 : (size_t)t.most * BWD_VIEW_BYTES, s,
+                     t, sc, cam, st, grad2d, pa, g);
   return hipGetLastError();
 }
 

@@ -85,3 +85,12 @@ def test_pose_sums_of_own_views():
         want = g["d_means"][v::2].double().sum(0)
         err = (g["d_pose"][v, :3].double() - want).abs() / want.abs()
         assert float(err.max()) <= 1.001 * 2.0 ** -24, (v, err.tolist())
+
+
+# the degrees and numbers of views on either side of the line between one loop for
+# both ways and a loop for each
+@pytest.mark.parametrize("sizes,n_views,sh", [
+    ((300,), 1, 3), ((63, 64), 26, 3), ((257,), 27, 3), ((257,), 41, 2), ((320,), 26, 2),
+    ((64, 1), 3, 1)])
+def test_one_loop_and_two(sizes, n_views, sh):
+    test_views_in_turn_and_own_views(sizes, n_views, sh)
