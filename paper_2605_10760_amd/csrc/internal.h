@@ -65,17 +65,18 @@ struct SortTab {
 // Whether the sort goes without scan kernels: each scatter block then walks its
 // view's digit counts itself (1 KB a block of the view), which saves four launches
 // and, in each pass, one workgroup's walk down the largest view.  A pass reads the
-// sum over the views of blocks^2 KB that way, so that sum decides, against the
-// launches and the largest view; the blocks are the host's bound on the visible
-// ones.  Sort of one view that sees all (without | with scan kernels, us): 1.0M
-// pairs 125 | 137, 1.5M 165 | 179, 2M 227 | 214, 3M 420 | 281, 4M 665 | 350; 8 views
-// of 200k 92 | 98, of 400k 156 | 146, of 800k 334 | 234; 48 of 85k 143 | 148, of 170k
-// 253 | 240.  Where a quarter of the pairs is visible, as in most calls, going
-// without is 8 to 17 us faster in all of them, so the line lies where the loss of a
-// call that sees all stays below that.  Calls of more than 2048 blocks have more
+// sum over the views of (visible blocks)^2 KB that way; the host knows the bound of
+// that sum, where all is visible.  Sort, without | with scan kernels, us:
+//   all visible: one view of 1M pairs 125 | 137, 2M 224 | 211, 2.3M 296 | 231, 3M 420 |
+//     281, 4M 665 | 350; 3 views of 1M 202 | 169, 4 253 | 194; 8 of 400k 156 | 146, of 800k
+//     334 | 234; 48 of 85k 143 | 148;
+//   half of it: one view of 2M 124 | 138, 2.3M 137 | 153; 3 of 1M 106 | 123, 4 120 | 130; 8
+//     of 500k 100 | 110; a fifth: one of 3M 99 | 111, 3 of 1M 76 | 88.
+// Most calls see a fifth to a half and gain 10 to 17 us; the line lies where one that
+// sees all loses two or three times that.  Calls of more than 2048 blocks have more
 // to sort than launches to save.
 constexpr int FOLD_BLOCKS = 2048;
-constexpr long FOLD_SQUARES = 250000, FOLD_PER_BLOCK = 400;
+constexpr long FOLD_SQUARES = 750000, FOLD_PER_BLOCK = 250;
 inline bool sort_folds(const SortTab& t) {
   long squares = 0, most = 0;
   for (int v = 0; v < t.nv; ++v) {

@@ -29,8 +29,8 @@ def rule(tmp_path_factory):
 
 # pairs of each view; whether the sort goes without scan kernels
 @pytest.mark.parametrize("views,want", [
-    ([1000], 1), ([300000], 1), ([1000000], 1), ([1500000], 1), ([2000000], 0), ([3000000], 0),
-    ([4000000], 0), ([200000] * 8, 1), ([400000] * 8, 1), ([800000] * 8, 0), ([85000] * 48, 1),
+    ([1000], 1), ([300000], 1), ([1000000], 1), ([2000000], 1), ([2300000], 0), ([3000000], 0),
+    ([4000000], 0), ([1000000] * 3, 1), ([1000000] * 4, 0), ([500000] * 8, 1), ([200000] * 8, 1), ([400000] * 8, 1), ([800000] * 8, 0), ([85000] * 48, 1),
     ([170000] * 48, 0), ([278000] * 48, 0), ([3000000] * 48, 0), ([1000000] + [100] * 63, 1),
     ([3000000] + [100] * 63, 0), ([65536] * 64, 1), ([65537] * 64, 0)])
 def test_sort_without_scan_kernels(rule, views, want):

@@ -240,7 +240,7 @@ def test_key_pass_with_any_near_plane(z_near):
 
 
 # one view of the most blocks whose sort goes without scan kernels, and of one more
-@pytest.mark.parametrize("n", [738 * 2048, 738 * 2048 + 1])
+@pytest.mark.parametrize("n", [1000 * 2048, 1000 * 2048 + 1])
 def test_sort_of_one_large_view(n):
     """A large view that sees everything: its depth order is the stable order of its
     depth keys, with and without scan kernels."""
