@@ -312,6 +312,11 @@ hipError_t launch_count_blend(int nv, int W, int H, int TW, int TH, int TX, int 
                               const uint2* ranges, const uint32_t* inst, int32_t* n_blend,
                               hipStream_t s);
 hipError_t launch_zero_pose(float* d_pose, int nv, unsigned int* bwd_next, hipStream_t s);
+// Whether the projection backward has a loop for each of its two ways through the
+// views (figures at the kernel), from the degree and the most views of a set.
+inline bool bwd_by_two_loops(int sh_degree, int most) {
+  return sh_degree == 0 || (sh_degree == 2 && most > 4) || (sh_degree == 3 && most > 12);
+}
 hipError_t launch_project_bwd(const SetTab& t, const SceneDev& sc, const CamDev& cam,
                               StateDev st, float* grad2d, PoseAcc* pa,
                               const gsr_grads& g, hipStream_t s);

@@ -251,13 +251,14 @@ __device__ __forceinline__ void pair_bwd(const BwdView& w, const float* m, const
 // clearing kernel, and the rounding of thousands of FP32 additions per
 // component does not reach the result).
 // SPLIT: a loop for each way.  One loop for both keeps the registers of degrees 1 to 3
-// within 125, 124 and 167 (152, 190 and 246 with two), and the LDS of up to 26 views
-// leaves degree 3 room for three workgroups a CU: one view of 1M Gaussians 51 -> 45 us,
-// 90 -> 79 and 124 -> 109, 8 views of 400k of degree 3 151 -> 128.  Two loops are faster for
-// degree 0 (8 views of each of six submaps 162 -> 153) and, from degree 2 on, for more
-// views (64 views of 400k of degree 2 763 -> 643, 32 of 2M of degree 3 1488 -> 1318).
+// within 125, 124 and 167 (152, 190 and 246 with two), and LDS for the views there are
+// leaves degree 3 room for three workgroups a CU; two loops are faster where lanes
+// mostly take their own views, and for degree 0.  Two loops | one, us: one view of 1M
+// Gaussians of degree 1 51 | 45, 2 90 | 79, 3 124 | 109; three submaps of 200k of degree 2
+// in 2 keyframes each 75 | 70, in 4 118 | 120, in 6 154 | 162; of degree 3 in 8 226 | 198;
+// 300k of degree 3 in 12 views all around 85 | 88, 200k in 20 83 | 97; six submaps of 200k
+// of degree 0 in 8 keyframes 153 | 162, of degree 1 211 | 190.
 constexpr size_t BWD_VIEW_BYTES = 64 + 48 + 16 + 32 + 16;  // LDS of a view
-constexpr int BWD_ONE_LOOP = 26;                           // views
 template <int SHD, bool SPLIT>
 __global__ __launch_bounds__(256) void k_project_bwd(SetTab t, SceneDev sc, CamDev cam, StateDev st,
                                                      float* grad2d, PoseAcc* pa, gsr_grads out) {
@@ -547,7 +548,7 @@ hipError_t launch_project_bwd(const SetTab& t, const SceneDev& sc, const CamDev&
                               hipStream_t s) {
   const int nb = t.set_blk[t.ns];
   if (nb == 0) return hipSuccess;
-  const bool split = sc.sh_degree == 0 || (sc.sh_degree > 1 && t.most > BWD_ONE_LOOP);
+  const bool split = bwd_by_two_loops(sc.sh_degree, t.most);
   const auto k = sc.sh_degree == 0   ? k_project_bwd<0, true>
                  : sc.sh_degree == 1 ? k_project_bwd<1, false>
                  : sc.sh_degree == 2 ? (split ? k_project_bwd<2, true> : k_project_bwd<2, false>)

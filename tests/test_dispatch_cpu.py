@@ -90,3 +90,10 @@ def test_compositing_by_workgroup(rule, blocks, tiles, fwd, bwd):
                                         (1200000, 128), (1500000, 256), (3000000, 256)])
 def test_chunk_of_an_open_plan(rule, pairs, want):
     assert rule(f"auto_chunk({pairs})") == want
+
+
+@pytest.mark.parametrize("sh,views,want", [(0, 1, 1), (0, 64, 1), (1, 1, 0), (1, 64, 0), (2, 1, 0),
+                                           (2, 4, 0), (2, 6, 1), (2, 64, 1), (3, 1, 0), (3, 8, 0),
+                                           (3, 12, 0), (3, 20, 1), (3, 64, 1)])
+def test_projection_backward_loops(rule, sh, views, want):
+    assert rule(f"bwd_by_two_loops({sh}, {views})") == want
