@@ -354,9 +354,11 @@ gsr_status gsr_dedup_workspace_bytes(int64_t table_slots, size_t* out_bytes);
  * depth per pixel), viewmats [K,3,4] world->camera, intrinsics [K,4] for the
  * target's keyframes; src_means [n_src,3]; keep uint8 [n_src] (out);
  * workspace 256-byte aligned, >= gsr_dedup_workspace_bytes(table_slots),
- * overwritten.  Synchronises `stream` (GSR_E_DEVICE on one under capture);
- * n_voxels (HOST, may be NULL) gets the number of distinct voxels inserted.  GSR_E_OVERFLOW (keep not valid) when
- * the hash set ran out of slots; GSR_E_INVALID_ARG for bad parameters, or
+ * overwritten (it holds the voxels of the inputs' box as bits where the box
+ * fits, as it does for an ordinary room, else the hash set).  Synchronises
+ * `stream` (GSR_E_DEVICE on one under capture); n_voxels (HOST, may be NULL)
+ * gets the number of distinct voxels inserted.  GSR_E_OVERFLOW (keep not valid)
+ * when the hash set ran out of slots; GSR_E_INVALID_ARG for bad parameters, or
  * (found on the device; keep not valid) a voxel index outside +-2^20 per
  * axis, a non-finite input, or one box or segment of more than 2^22 voxels. */
 gsr_status gsr_dedup(const gsr_dedup_params* params, const float* tgt_means,
@@ -373,8 +375,10 @@ gsr_status gsr_dedup(const gsr_dedup_params* params, const float* tgt_means,
  * for n rows each, not aliasing the inputs: the kept rows of means,
  * log_scales, quats, opacity logits and colours; set_offsets_out is a HOST
  * array [n_sets+1] of the pruned set offsets (its last entry = rows kept).
- * Allocates a small temporary device buffer and synchronises `stream` (set-up
- * work; GSR_E_DEVICE on a stream under capture).  GSR_E_INVALID_ARG for null pointers, bad offsets or
+ * Synchronises `stream` (set-up work; GSR_E_DEVICE on a stream under capture).
+ * Its scratch is one of four 256 KiB slots that the library holds on each GPU;
+ * above about 16M Gaussians, or while every slot is taken by another call, it is
+ * allocated and freed.  GSR_E_INVALID_ARG for null pointers, bad offsets or
  * min_opacity outside (0, 1). */
 gsr_status gsr_prune(const gsr_scene* scene, float min_opacity, float* means_out,
                      float* log_scales_out, float* quats_out, float* opacity_out,
@@ -417,8 +421,9 @@ gsr_status gsr_normal_loss_grad(const float* depth, const float* normal_prior,
  * color [3,H,W] (channel planes), viewmat [3,4] world->camera, intrinsics
  * [4]: device arrays.  Outputs (device, capacity max_out rows): means_out,
  * log_scales_out, colors_out [max_out,3], quats_out [max_out,4],
- * opacity_out [max_out].  Allocates a small temporary and synchronises
- * `stream` (GSR_E_DEVICE on one under capture: gsr_seed_noalloc is for that);
+ * opacity_out [max_out].  Synchronises `stream` (GSR_E_DEVICE on one under
+ * capture: gsr_seed_noalloc is for that); its scratch is a slot as gsr_prune's,
+ * allocated above about 16M grid points or while every slot is taken.
  * *n_out (HOST) gets the number of seeded Gaussians.
  * GSR_E_OVERFLOW when that exceeds max_out (the first max_out rows are
  * written); GSR_E_INVALID_ARG for null pointers or bad sizes. */
@@ -458,9 +463,9 @@ gsr_status gsr_adam(const gsr_adam_group* groups, int32_t n_groups, double beta1
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation): gsr_seed
- * with its per-block counts in a buffer the library holds (a file-scope
- * device array, one per GPU, kept until the process ends) instead of a
- * temporary allocation.  Same inputs, outputs and kernels as gsr_seed,
+ * with its per-block counts always in one buffer the library holds (a
+ * file-scope device array, one per GPU, kept until the process ends; gsr_seed
+ * may have to allocate).  Same inputs, outputs and kernels as gsr_seed,
  * except that the number of seeded Gaussians goes to *n_out_dev, a DEVICE
  * int64 written on `stream` (no host synchronisation; the caller compares
  * it with max_out: only the first max_out rows are written).  At most

@@ -239,10 +239,11 @@ __device__ __forceinline__ unsigned long long wg_sum_before(const uint32_t* x, i
 // there are is known to the device alone, so a kernel over them has a grid of at
 // most VIS_GRID workgroups (the host's bound on their number, if smaller) that
 // walk them: a workgroup per block of the bound, most of them without a pair,
-// cost 80 us a kernel where 48 views saw 31M of 144M pairs (12.0 -> 11.15 ms a
-// pass in the four binning and eight sort kernels; 400k in 8 views 978 -> 930 us, one
-// view of 300k 372 -> 360).  An XCD takes a
-// contiguous eighth of the blocks.  Every lane of the wave must be active.
+// cost 80 us a kernel where 48 views saw 31M of 144M pairs (11.3 -> 10.4 ms a
+// pass in the row count, the row scatter and the eight sort kernels; 400k in 8
+// views 1005 -> 966 us, one view of 1M 477 -> 452, forward alone 272 -> 252, one of
+// 300k 366 -> 356).  An XCD takes a contiguous run of the blocks.  Every lane of
+// the wave must be active.
 struct VisBlocks {
   int lo, hi;   // lane v: the view's visible pairs
   int incl;     //   blocks of views 0..v

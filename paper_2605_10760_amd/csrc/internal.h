@@ -222,7 +222,7 @@ inline SsimShape ssim_shape(int nv, int W, int H) {
   }
   // waves per workgroup: the fewest waves over the strips of a row (each strip
   // recomputes two windows of columns), the larger workgroup on a tie (640
-  // columns: 3 x 4 waves 463 us, 4 x 3 572, 7 x 2 534, 16 x 1 585)
+  // columns: 3 x 4 waves 463 us, 4 x 3 572, 7 x 2 534, 16 x 1 585, measured together)
   for (int k = 2; k <= SS_MAXW; ++k)
     if (k * strips_of(k) <= s.nw * strips_of(s.nw)) s.nw = k;
   s.strips = strips_of(s.nw);

@@ -19,8 +19,9 @@
 // k_seed_*: ordered compaction (per-block counts, summed by each later block,
 // wave-ballot ranks) of the pixels with positive depth on a stride grid,
 // each writing one isotropic Gaussian at its back-projected point.
-// The allocation-free seeding variant keeps the per-block counts in a
-// file-scope device array instead of a temporary allocation.
+// The per-block counts live in file-scope device arrays: one that the
+// allocation-free variant's calls share, and a few slots of which every
+// synchronising call takes its own.
 #include <mutex>
 
 #include "common.h"

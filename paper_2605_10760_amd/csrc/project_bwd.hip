@@ -247,9 +247,9 @@ __device__ __forceinline__ void pair_bwd(const BwdView& w, const float* m, const
 // Pose sums are FP64 from the workgroup's LDS on (a chain of up to 256 FP32
 // additions in `own`, no tree, lost 4 times the rounding of the result; the FP64
 // LDS atomics are the faster ones too: 3M Gaussians of degree 3 in 32 views 1401 ->
-// 1196 us), and the last workgroup to finish writes d_pose and clears them for the next call (no
-// clearing kernel, and the rounding of thousands of FP32 additions per
-// component does not reach the result).
+// 1196 us), and the last workgroup to finish writes d_pose and clears them for the
+// next call (no clearing kernel, and the rounding of thousands of FP32 additions
+// per component does not reach the result).
 // SPLIT: a loop for each way.  One loop for both keeps the registers of degrees 1 to 3
 // within 125, 124 and 167 (152, 190 and 246 with two), and LDS for the views there are
 // leaves degree 3 room for three workgroups a CU; two loops are faster where lanes

@@ -450,9 +450,9 @@ __device__ __forceinline__ void fwd_tile(int g, int W, int H, int TX, int TY, co
 // barrier.  Grid form: wave w of workgroup b takes tile b TPW + w (XCD-aware
 // order, runs of four tiles per XCD: with a contiguous eighth of the tiles
 // each, the XCD with the densest part of the call finishes last; 48-view batch
-// 692 -> 683 us, nine uneven views at 517x389 168 -> 140 us).  Persistent form: a grid sized to the resident waves, each wave
-// taking tiles from the length-ordered queue (longest lists first) until it
-// is empty.
+// 692 -> 683 us, nine uneven views at 517x389 168 -> 140 us).  Persistent form: a
+// grid sized to the resident waves, each wave taking tiles from the length-ordered
+// queue (longest lists first) until it is empty.
 template <int TW, int TH, int FB, int TPW, bool PERSIST, bool NEVAL>
 __global__ __launch_bounds__(64 * TPW) void k_render_fwd(int ntiles, int W, int H, int TX, int TY,
                                                          CamDev cam, StateDev st,

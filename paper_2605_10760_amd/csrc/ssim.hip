@@ -25,9 +25,11 @@
 // registers (rings of 16 rows, the march unrolled by four steps).
 // One workgroup per 32 x 32 tile with blurs through LDS took 1050 us at 48 x 3
 // x 480 x 640 (bound by LDS reads: about 118 per pixel, and 310 multiply-adds
-// with the tile's halo); this form
-// 463 us (one wave per strip, 40 of its 64 columns its own: 585 us; loads at
-// their use instead of a step ahead and one chain of products at a time: 692).
+// with the tile's halo); this form took 463 us when it was chosen (one wave per
+// strip, 40 of its 64 columns its own: 585 us; loads at their use instead of a
+// step ahead and one chain of products at a time: 692).  Since its sums are
+// FP64 and its registers held to two waves a SIMD it takes 408 back to back
+// (425 before); in a trace, the clocks lower, 494.
 //
 // k_ssim_reduce: per-wave partial sums (S, and the exposure gradients) summed
 // per view in a fixed order: no float atomics on a few hot addresses.
