@@ -489,7 +489,8 @@ gsr_status gsr_seed_noalloc(const float* depth, const float* color, const float*
  * launch), then for the fastest plan so far each
  * binning chunk of 64, 128 and 256 pairs, the forward's 1 or 2 entries per
  * lane, the backward's 1, 2 or 4 entries per lane, and the grid or
- * persistent tile queue.  `best` holds tile_w, tile_h, chunk, fwd_batch,
+ * persistent tile queue; options that a call with few tiles does not read
+ * (gsr_plan_desc) are not tried on it.  `best` holds tile_w, tile_h, chunk, fwd_batch,
  * bwd_batch, persistent and bwd_cols; other fields are copied from `base` (the
  * entry capacity raised if a candidate overflowed).  Synchronises;
  * allocates its own temporary contexts and buffers. */
